@@ -142,7 +142,7 @@ def main():
 
     import torch
     from paper_2602_14016_amd import Solver
-    from paper_2602_14016_amd.roofline import CLASS_NAMES, HBM_PEAK_GBS, algorithmic_bytes, read_traffic
+    from paper_2602_14016_amd.roofline import CLASS_NAMES, HBM_PEAK_GBS, kernel_bytes, read_traffic
 
     N, B, H = args.N, args.members, args.horizon
     nu, dt, k0 = 1e-4, 2e-3, 10.0
@@ -276,7 +276,7 @@ def main():
     # roofline of the dominant kernel
     cls = args.roofline_class
     per_launch_ms = prof["total_ms"] / max(prof["timed_launches"], 1)
-    bytes_launch = algorithmic_bytes(cls, N) * B
+    bytes_launch = kernel_bytes(cls, N) * B
     achieved = bytes_launch / (per_launch_ms * 1e-3) / 1e9
     variant = tiles["adj_variant"] if cls >= 2 else tiles["row_variant"] if cls == 0 else tiles["col_variant"]
     kname = CLASS_NAMES[cls].split(" ")[0]

@@ -394,11 +394,11 @@ pa_status pa_shell_growth(pa_ctx* ctx, const double* shells, int32_t rows, int32
  * variant 3, wavefronts per workgroup, capped at 4); col_block =
  * kx columns per column-pass workgroup (1, 2, 4 or 8, with col_block times
  * threads per transform <= 512 and LDS within the device's per-workgroup
- * limit, 160 KiB on gfx950; the default stays within 64 KiB); col_split = workgroups
- * per column that share out the column's output transforms, each recomputing
- * the input transform (0: chosen per launch, 2 or 4 shares where the launch
- * has fewer than two wavefronts per SIMD without them; 1, 2 or 4: fixed,
- * capped at the launch's output count).  Results do not depend on the choice
+ * limit, 160 KiB on gfx950; the default stays within 64 KiB); col_split: 1 =
+ * one team of threads runs both signals of a column's packed pair, 2 or 4 =
+ * twin teams run one each (with fewer columns per workgroup where col_block
+ * of them would not fit), 0 = chosen per launch (twins where the launch has
+ * fewer than two wavefronts per SIMD without).  Results do not depend on the choice
  * beyond rounding of the transforms, and not at all on col_split. */
 typedef struct pa_tiles {
     int32_t row_variant, row_teams;

@@ -14,10 +14,9 @@ solver's own shape while the library times that pass's launches with HIP
 events on the solver's stream (pa_profile_start).  Forward rows are scored by
 the right-hand-side row kernel, adjoint rows by the adjoint-product row
 kernel, and the column pass by its forward plus adjoint stage launches; for
-the column pass every (variant, block) pair is tried with each share count,
-since the best count depends on the block (wide blocks fill a CU alone and
-want fewer shares).  The best of each is applied and returned.  Results depend on the choice only through the
-rounding of the transforms (not at all on the column shares).
+the column pass every (variant, block) pair is tried with each col_split (one
+team per column, or twin teams), since the best form depends on the block.  The best of each is applied and returned.  Results depend on the choice only through the
+rounding of the transforms (not at all on the column form).
 """
 
 import time

@@ -140,9 +140,9 @@ namespace {
 
 struct WS {
     cd* Y0;
-    cd* Yf[4];
-    cd* Yp[4];
-    cd* YL[2];          // Lambda and Lambda_y (adjoint cotangent fields)
+    cd* Yf[2];          // packed velocity of the current stage
+    cd* Yp[2];          // packed products of a row pass
+    cd* YL[2];          // packed adjoint cotangent (b, a)
     double* P0;         // physical scratch [B][N][N]
     double* P1;         // physical scratch [B][N][N]
     cd* omega;
@@ -150,7 +150,7 @@ struct WS {
     cd* acc;
     cd* lam;
     cd* omb;
-    cd* seg;            // segment stage fields, (4K+1) slots x 4 fields
+    cd* seg;            // segment stage fields, (4K+1) slots x 2 fields
     cd* ckpt;           // internal checkpoints
     double* jpart;      // [B][n_obs][N]
     double* J;          // [B]
@@ -218,8 +218,8 @@ WS carve(const pa_ctx* c, int n_steps, int ckpt_every, int n_obs, int m, void* b
     Carver cv{reinterpret_cast<char*>(base)};
     WS w{};
     w.Y0 = cv.take<cd>(SY);
-    for (int i = 0; i < 4; ++i) w.Yf[i] = cv.take<cd>(SY);
-    for (int i = 0; i < 4; ++i) w.Yp[i] = cv.take<cd>(SY);
+    for (int i = 0; i < 2; ++i) w.Yf[i] = cv.take<cd>(SY);
+    for (int i = 0; i < 2; ++i) w.Yp[i] = cv.take<cd>(SY);
     w.YL[0] = cv.take<cd>(SY);
     w.YL[1] = cv.take<cd>(SY);
     w.P0 = cv.take<double>(SP);
@@ -229,7 +229,7 @@ WS carve(const pa_ctx* c, int n_steps, int ckpt_every, int n_obs, int m, void* b
     w.acc = cv.take<cd>(SC);
     w.lam = cv.take<cd>(SC);
     w.omb = cv.take<cd>(SC);
-    w.seg = n_steps > 0 ? cv.take<cd>((size_t)(4 * K + 1) * 4 * SY) : nullptr;
+    w.seg = n_steps > 0 ? cv.take<cd>((size_t)(4 * K + 1) * 2 * SY) : nullptr;
     w.ckpt = cv.take<cd>((size_t)ckpt_count(c, nseg) * SC);
     w.jpart = cv.take<double>((size_t)d.B * std::max(n_obs, 1) * d.N);
     w.J = cv.take<double>(d.B);
@@ -277,11 +277,11 @@ cd* ckpt_slot(const pa_ctx* c, cd* base, int i) {
     return base + (size_t)i * c->d.B * c->d.KY * c->d.KXP;
 }
 
-// 4 stage-field pointers of segment slot (j, s)
-void seg_fields(const pa_ctx* c, const WS& w, int j, int s, cd* out[4]) {
+// stage-field pointers (the packed velocity P, Q) of segment slot (j, s)
+void seg_fields(const pa_ctx* c, const WS& w, int j, int s, cd* out[2]) {
     const size_t SY = (size_t)c->d.B * c->d.N * c->d.KXP;
     const size_t slot = (size_t)j * 4 + s;
-    for (int f = 0; f < 4; ++f) out[f] = w.seg + (slot * 4 + f) * SY;
+    for (int f = 0; f < 2; ++f) out[f] = w.seg + (slot * 2 + f) * SY;
 }
 
 // ------------------------------------------------- checkpoint schedule --
@@ -528,7 +528,7 @@ pa_status check_ws(const pa_ctx* c, void* ws, size_t bytes, int n_steps, int K, 
 
 // ------------------------------------------------------------- timing --
 // Kernel classes that pa_profile_start can time.
-enum { PROF_ROW_NL = 0, PROF_COL_FWD = 1, PROF_ROW_ADJ = 2, PROF_COL_ADJ = 3 };
+enum { PROF_ROW_SQ = 0, PROF_COL_FWD = 1, PROF_ROW_MUL = 2, PROF_COL_ADJ = 3 };
 
 template <class F>
 hipError_t timed(pa_ctx* c, int cls, F&& launch) {
@@ -588,10 +588,10 @@ Dims slice_dims(const pa_ctx* c, int lo, int hi) {
 }
 
 // Observation of range r at its slot (velocity probes and cost partials) from the
-// stage-a fields (the packed pairs (u, w_x), (v, w_y)) of the state at that step.
-pa_status observe_range(pa_ctx* c, WS& w, const ObsRange& r, int slot, cd* const fields[4], double* obs_out) {
+// stage-a field (the packed velocity) of the state at that step.
+pa_status observe_range(pa_ctx* c, WS& w, const ObsRange& r, int slot, cd* const fields[2], double* obs_out) {
     RowArgs ra{};
-    for (int i = 0; i < 4; ++i) ra.yin[i] = fields[i] + (size_t)r.b0 * per_y(c);
+    for (int i = 0; i < 2; ++i) ra.yin[i] = fields[i] + (size_t)r.b0 * per_y(c);
     ra.tw = c->tw;
     ra.obs = row_obs_args(&r, slot, obs_out, w.jpart + r.jrow0);
     PA_HIP(launch_row_obs(slice_dims(c, r.b0, r.b0 + r.nb), ra, c->stream));
@@ -599,7 +599,7 @@ pa_status observe_range(pa_ctx* c, WS& w, const ObsRange& r, int slot, cd* const
 }
 
 // Every range observed at step n.
-pa_status observe_step(pa_ctx* c, WS& w, const ObsPlan& op, int n, cd* const fields[4], double* obs_out) {
+pa_status observe_step(pa_ctx* c, WS& w, const ObsPlan& op, int n, cd* const fields[2], double* obs_out) {
     for (int i = 0; i < op.n; ++i) {
         const int slot = op.r[i].slot(n);
         if (slot >= 0) PA_TRY(observe_range(c, w, op.r[i], slot, fields, obs_out));
@@ -607,27 +607,28 @@ pa_status observe_step(pa_ctx* c, WS& w, const ObsPlan& op, int n, cd* const fie
     return PA_OK;
 }
 
-// Residual source rows (-S^T r_u, -S^T r_v, row-transformed) of the members [lo, hi) of
-// range r at its slot, into out[0..1] (full-batch buffers; the slice is written).
-pa_status source_rows(pa_ctx* c, const ObsRange& r, int slot, int lo, int hi, cd* const fields[4],
-                      cd* const out[2]) {
+// Packed residual source rows (SrcMode) of the members [lo, hi) of range r at its slot,
+// written to or added to out[0..1] (full-batch buffers; the slice is touched).
+pa_status source_rows(pa_ctx* c, const ObsRange& r, int slot, int lo, int hi, cd* const fields[2],
+                      cd* const out[2], int mode) {
     const size_t off = (size_t)lo * per_y(c);
     RowArgs rs{};
-    for (int i = 0; i < 4; ++i) rs.yin[i] = fields[i] + off;
+    for (int i = 0; i < 2; ++i) rs.yin[i] = fields[i] + off;
     rs.yout[0] = out[0] + off;
     rs.yout[1] = out[1] + off;
     rs.tw = c->tw;
     rs.obs = row_obs_args(&r, slot, nullptr, nullptr);
     if (r.values) rs.obs.values = r.values + (size_t)(lo - r.b0) * r.n_times * 2 * r.M * r.M;
-    PA_HIP(launch_row_src(slice_dims(c, lo, hi), rs, 0, c->stream));
+    PA_HIP(launch_row_src(slice_dims(c, lo, hi), rs, mode, c->stream));
     return PA_OK;
 }
 
-// Source rows at step n for the members [lo, hi): the observing ranges write their
-// members' rows; the rest of the slice is zeroed unless the ranges cover it.  Returns
-// (in *any) whether some member of the slice observes at n.
-pa_status sources_at(pa_ctx* c, WS& w, const ObsPlan& op, int n, int lo, int hi, cd* const fields[4],
-                     cd* const out[2], bool* any) {
+// Residual sources at step n for the members [lo, hi).  SRC_ADD: added to the products in
+// out.  SRC_WRITE: the observing ranges write their members' rows and the rest of the slice
+// is zeroed unless the ranges cover it; nothing is written if no member of the slice observes
+// at n (*any).
+pa_status sources_at(pa_ctx* c, const ObsPlan& op, int n, int lo, int hi, cd* const fields[2],
+                     cd* const out[2], int mode, bool* any) {
     *any = false;
     int covered = 0;
     for (int i = 0; i < op.n; ++i) {
@@ -637,7 +638,7 @@ pa_status sources_at(pa_ctx* c, WS& w, const ObsPlan& op, int n, int lo, int hi,
     }
     if (covered == 0) return PA_OK;
     *any = true;
-    if (covered < hi - lo) {
+    if (mode == SRC_WRITE && covered < hi - lo) {
         const size_t off = (size_t)lo * per_y(c), cnt = 2 * (size_t)(hi - lo) * per_y(c);
         PA_HIP(launch_fill(reinterpret_cast<double*>(out[0] + off), 0.0, cnt, c->stream));
         PA_HIP(launch_fill(reinterpret_cast<double*>(out[1] + off), 0.0, cnt, c->stream));
@@ -646,7 +647,7 @@ pa_status sources_at(pa_ctx* c, WS& w, const ObsPlan& op, int n, int lo, int hi,
         const ObsRange& r = op.r[i];
         const int a = std::max(lo, r.b0), b = std::min(hi, r.b0 + r.nb);
         const int slot = r.slot(n);
-        if (a < b && slot >= 0) PA_TRY(source_rows(c, r, slot, a, b, fields, out));
+        if (a < b && slot >= 0) PA_TRY(source_rows(c, r, slot, a, b, fields, out, mode));
     }
     return PA_OK;
 }
@@ -672,18 +673,16 @@ ColArgs col_base(const pa_ctx* c) {
     return a;
 }
 
-void set_stage_fields(ColArgs& a, cd* const f[4]) {
-    a.nout = 4;
-    a.fields[0] = F_UP;
-    a.fields[1] = F_UQ;
-    a.fields[2] = F_VP;
-    a.fields[3] = F_VQ;
-    for (int i = 0; i < 4; ++i) a.yout[i] = f[i];
+void set_stage_fields(ColArgs& a, cd* const f[2]) {
+    a.nout = 2;
+    a.fields[0] = F_ZP;
+    a.fields[1] = F_ZQ;
+    for (int i = 0; i < 2; ++i) a.yout[i] = f[i];
 }
 
 // Transform physical omega0 to the band-limited state (P omega0), write
 // checkpoint slot 0 if given, and the stage-a fields to `fields`.
-pa_status start_state(pa_ctx* c, WS& w, const double* omega0, cd* ck0, cd* const fields[4]) {
+pa_status start_state(pa_ctx* c, WS& w, const double* omega0, cd* ck0, cd* const fields[2]) {
     PA_HIP(launch_row_r2c(c->d, omega0, w.Y0, c->tw, c->stream));
     ColArgs a = col_base(c);
     a.yin[0] = w.Y0;
@@ -717,25 +716,26 @@ pa_status run_steps(pa_ctx* c, WS& w, int n0, int n1, int n_total, int K, bool s
         Dims dn = c->d;
         if (op) dn.B = op->act(n);
         for (int s = 0; s < 4; ++s) {
-            cd* fin[4];
-            cd* fout[4];
+            cd* fin[2];
+            cd* fout[2];
             if (store) {
                 seg_fields(c, w, j, s, fin);
                 if (s < 3) seg_fields(c, w, j, s + 1, fout);
                 else seg_fields(c, w, j + 1, 0, fout);
             } else {
-                for (int i = 0; i < 4; ++i) fin[i] = fout[i] = w.Yf[i];
+                for (int i = 0; i < 2; ++i) fin[i] = fout[i] = w.Yf[i];
             }
             if (s == 0 && op && observe) PA_TRY(observe_step(c, w, *op, n, fin, obs_out));
             if (dn.B < 1) continue;
             RowArgs ra{};
-            for (int i = 0; i < 4; ++i) ra.yin[i] = fin[i];
+            for (int i = 0; i < 2; ++i) ra.yin[i] = fin[i];
             ra.yout[0] = w.Yp[0];
+            ra.yout[1] = w.Yp[1];
             ra.tw = c->tw;
-            ra.obs = row_obs_args(nullptr, -1, nullptr, nullptr);
-            PA_HIP(timed(c, PROF_ROW_NL, [&] { return launch_row_nl(dn, ra, c->stream); }));
+            PA_HIP(timed(c, PROF_ROW_SQ, [&] { return launch_row_sq(dn, ra, c->stream); }));
             ColArgs a = col_base(c);
             a.yin[0] = w.Yp[0];
+            a.yin[1] = w.Yp[1];
             a.omega = w.omega;
             a.acc = w.acc;
             set_stage_fields(a, fout);
@@ -788,7 +788,7 @@ pa_status forward_sweep(pa_ctx* c, WS& w, const double* omega0, int n_steps, con
     const int n_last = store ? (n_segments(n_steps, K) - 1) * K : n_steps;   // first step of the stored segment
     bool final_obs = false;
     for (int i = 0; i < op.n; ++i) final_obs = final_obs || op.r[i].slot(n_steps) >= 0;
-    cd* f0[4] = {w.Yf[0], w.Yf[1], w.Yf[2], w.Yf[3]};
+    cd* f0[2] = {w.Yf[0], w.Yf[1]};
     if (store && n_last == 0) seg_fields(c, w, 0, 0, f0);
     PA_TRY(start_state(c, w, omega0, ckpt ? ckpt_slot(c, ckpt, 0) : nullptr, f0));
     // Sobolev term (lambda/2) int |grad u0|^2 = (lambda/2) int omega0^2 (periodic, divergence-free),
@@ -800,7 +800,7 @@ pa_status forward_sweep(pa_ctx* c, WS& w, const double* omega0, int n_steps, con
         if (store) {
             // stage-a fields of the state at n_last (in w.omega) into segment slot (0, 0), for
             // every member: a member whose horizon is n_last is observed from them
-            cd* s0[4];
+            cd* s0[2];
             seg_fields(c, w, 0, 0, s0);
             ColArgs a = col_base(c);
             a.state_in = w.omega;
@@ -808,7 +808,7 @@ pa_status forward_sweep(pa_ctx* c, WS& w, const double* omega0, int n_steps, con
             PA_HIP(launch_col(c->d, COL_FROM_STATE, a, c->stream));
         }
     }
-    cd* fH[4] = {w.Yf[0], w.Yf[1], w.Yf[2], w.Yf[3]};
+    cd* fH[2] = {w.Yf[0], w.Yf[1]};
     if (store) {
         PA_TRY(run_steps(c, w, n_last, n_steps, n_steps, K, true, &op, true, obs_out, tgt, true));
         seg_fields(c, w, n_steps - n_last, 0, fH);
@@ -822,39 +822,26 @@ pa_status forward_sweep(pa_ctx* c, WS& w, const double* omega0, int n_steps, con
 // Adjoint stage of step n: row products + column transposes for stage
 // `mode`, for the members [0, op->act(n)) (all members without op).  At
 // stage n of a step that members observe, their residual source rows are
-// formed from the same stage fields and enter the column pass as two extra
-// inputs (zero for the other members of the launch).
-pa_status adj_stage(pa_ctx* c, WS& w, cd* const fields[4], int mode, const ObsPlan* op, int n, int final_out,
+// formed from the same stage field and added to the products.
+pa_status adj_stage(pa_ctx* c, WS& w, cd* const fields[2], int mode, const ObsPlan* op, int n, int final_out,
                     const double* scale) {
     Dims dn = c->d;
     if (op) dn.B = op->act(n);
     RowArgs ra{};
-    for (int i = 0; i < 4; ++i) ra.yin[i] = fields[i];
-    ra.yin[4] = w.YL[0];
-    ra.yin[5] = w.YL[1];
+    for (int i = 0; i < 2; ++i) ra.yin[i] = fields[i];
+    ra.yin[2] = w.YL[0];
+    ra.yin[3] = w.YL[1];
     ra.yout[0] = w.Yp[0];
     ra.yout[1] = w.Yp[1];
     ra.tw = c->tw;
-    ra.obs = row_obs_args(nullptr, -1, nullptr, nullptr);
-    PA_HIP(timed(c, PROF_ROW_ADJ, [&] { return launch_row_adj(dn, ra, c->stream); }));
+    PA_HIP(timed(c, PROF_ROW_MUL, [&] { return launch_row_mul(dn, ra, c->stream); }));
+    if (mode == COL_ADJ_N && op && op->values) {
+        bool any = false;
+        PA_TRY(sources_at(c, *op, n, 0, dn.B, fields, w.Yp, SRC_ADD, &any));
+    }
     ColArgs a = col_base(c);
     a.yin[0] = w.Yp[0];
     a.yin[1] = w.Yp[1];
-    a.nin = 2;
-    a.inmul[0] = IN_PAIRP;
-    a.inmul[1] = IN_PAIRQ;
-    if (mode == COL_ADJ_N && op && op->values) {
-        bool any = false;
-        cd* const out[2] = {w.Yp[2], w.Yp[3]};
-        PA_TRY(sources_at(c, w, *op, n, 0, dn.B, fields, out, &any));
-        if (any) {
-            a.yin[2] = w.Yp[2];
-            a.yin[3] = w.Yp[3];
-            a.nin = 4;
-            a.inmul[2] = IN_IKY_INVK2;
-            a.inmul[3] = IN_MIKX_INVK2;
-        }
-    }
     a.lam = w.lam;
     a.omb = w.omb;
     a.final_out = final_out;
@@ -865,12 +852,11 @@ pa_status adj_stage(pa_ctx* c, WS& w, cd* const fields[4], int mode, const ObsPl
         a.nout = 1;
     } else {
         a.nout = 2;
-        a.fields[0] = F_LP;
+        a.fields[0] = F_WP;
         a.yout[1] = w.YL[1];
-        a.fields[1] = F_LQ;
+        a.fields[1] = F_WQ;
     }
-    const int cmode = (mode == COL_ADJ_N && a.nin > 2) ? COL_ADJ_NSRC : mode;
-    PA_HIP(timed(c, PROF_COL_ADJ, [&] { return launch_col(dn, cmode, a, c->stream); }));
+    PA_HIP(timed(c, PROF_COL_ADJ, [&] { return launch_col(dn, mode, a, c->stream); }));
     return PA_OK;
 }
 
@@ -900,7 +886,7 @@ pa_status record_shells(pa_ctx* c, WS& w, const Shells& sh, int row) {
 // lambda = the residual sources of the members observed there, or a unit
 // u-impulse at (ix, iy) (impulse), else zero.  Writes lambda and the Lambda
 // fields of the slice (with final_out the gradient field, times scale).
-pa_status terminal(pa_ctx* c, WS& w, const ObsPlan* op, int step, cd* const fields[4], int impulse, int ix,
+pa_status terminal(pa_ctx* c, WS& w, const ObsPlan* op, int step, cd* const fields[2], int impulse, int ix,
                    int iy, bool final_out, const double* scale, int lo, int hi) {
     const size_t offY = (size_t)lo * per_y(c), offC = (size_t)lo * per_c(c);
     const size_t nY = (size_t)(hi - lo) * per_y(c), nC = (size_t)(hi - lo) * per_c(c);
@@ -915,10 +901,10 @@ pa_status terminal(pa_ctx* c, WS& w, const ObsPlan* op, int step, cd* const fiel
         ra.obs = row_obs_args(nullptr, -1, nullptr, nullptr);
         ra.obs.imp_x = ix;
         ra.obs.imp_y = iy;
-        PA_HIP(launch_row_src(ds, ra, 1, c->stream));
+        PA_HIP(launch_row_src(ds, ra, SRC_IMPULSE, c->stream));
         any = true;
     } else if (op && op->values) {
-        PA_TRY(sources_at(c, w, *op, step, lo, hi, fields, src, &any));
+        PA_TRY(sources_at(c, *op, step, lo, hi, fields, src, SRC_WRITE, &any));
     }
     if (!any) {
         PA_HIP(launch_fill(reinterpret_cast<double*>(w.lam + offC), 0.0, 2 * nC, c->stream));
@@ -929,9 +915,6 @@ pa_status terminal(pa_ctx* c, WS& w, const ObsPlan* op, int step, cd* const fiel
     ColArgs a = col_base(c);
     a.yin[0] = src[0] + offY;
     a.yin[1] = src[1] + offY;
-    a.nin = 2;
-    a.inmul[0] = IN_IKY_INVK2;
-    a.inmul[1] = IN_MIKX_INVK2;
     a.lam = w.lam + offC;
     a.final_out = final_out ? 1 : 0;
     a.scale = scale ? scale + lo : nullptr;
@@ -941,9 +924,9 @@ pa_status terminal(pa_ctx* c, WS& w, const ObsPlan* op, int step, cd* const fiel
         a.nout = 1;
     } else {
         a.nout = 2;
-        a.fields[0] = F_LP;
+        a.fields[0] = F_WP;
         a.yout[1] = w.YL[1] + offY;
-        a.fields[1] = F_LQ;
+        a.fields[1] = F_WQ;
     }
     PA_HIP(launch_col(ds, COL_ADJ_SRC, a, c->stream));
     return PA_OK;
@@ -980,16 +963,14 @@ pa_status backward_sweep(pa_ctx* c, WS& w, const cd* ckpt, int n_steps, int K, c
     // end at step 0: the gradient field straight from their sources, from the state in slot 0
     auto finish_idle = [&](int lo) -> pa_status {
         if (lo >= B) return PA_OK;
-        cd* f0[4] = {w.Yf[0], w.Yf[1], w.Yf[2], w.Yf[3]};
+        cd* f0[2] = {w.Yf[0], w.Yf[1]};
         const size_t offY = (size_t)lo * per_y(c);
         ColArgs a = col_base(c);
         a.state_in = ckpt_slot(c, ck, 0) + (size_t)lo * per_c(c);
-        a.nout = 4;
-        a.fields[0] = F_UP;
-        a.fields[1] = F_UQ;
-        a.fields[2] = F_VP;
-        a.fields[3] = F_VQ;
-        for (int i = 0; i < 4; ++i) a.yout[i] = f0[i] + offY;
+        a.nout = 2;
+        a.fields[0] = F_ZP;
+        a.fields[1] = F_ZQ;
+        for (int i = 0; i < 2; ++i) a.yout[i] = f0[i] + offY;
         PA_HIP(launch_col(slice_dims(c, lo, B), COL_FROM_STATE, a, c->stream));
         return terminal(c, w, op, 0, f0, impulse, ix, iy, true, scale, lo, B);
     };
@@ -1018,7 +999,7 @@ pa_status backward_sweep(pa_ctx* c, WS& w, const cd* ckpt, int n_steps, int K, c
         const int n0 = seg * K, n1 = std::min(n_steps, n0 + K), L = n1 - n0;
         const bool last = seg == nseg - 1;
         if (recompute) {
-            cd* f0[4];
+            cd* f0[2];
             seg_fields(c, w, 0, 0, f0);
             ColArgs a = col_base(c);
             a.state_in = src;
@@ -1033,12 +1014,12 @@ pa_status backward_sweep(pa_ctx* c, WS& w, const cd* ckpt, int n_steps, int K, c
             const int n = n0 + j;
             const int hi = act(n), lo = (n + 1 >= n_steps) ? 0 : act(n + 1);
             if (hi > lo) {
-                cd* fm[4];
+                cd* fm[2];
                 seg_fields(c, w, j + 1, 0, fm);
                 PA_TRY(terminal(c, w, op, n + 1, fm, impulse, ix, iy, false, scale, lo, hi));
                 if (n + 1 == n_steps) PA_TRY(record_shells(c, w, sh, 0));
             }
-            cd* fs[4];
+            cd* fs[2];
             seg_fields(c, w, j, 3, fs);
             PA_TRY(adj_stage(c, w, fs, COL_ADJ_C, op, n, 0, nullptr));
             seg_fields(c, w, j, 2, fs);
@@ -1069,7 +1050,7 @@ pa_status backward_sweep(pa_ctx* c, WS& w, const cd* ckpt, int n_steps, int K, c
                 continue;
             }
             // advance: the stage-a fields of the start state into w.Yf (a live start has them there)
-            cd* f0[4] = {w.Yf[0], w.Yf[1], w.Yf[2], w.Yf[3]};
+            cd* f0[2] = {w.Yf[0], w.Yf[1]};
             if (act_.src >= 0) {
                 ColArgs a = col_base(c);
                 a.state_in = src;

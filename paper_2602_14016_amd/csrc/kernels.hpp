@@ -11,12 +11,13 @@
 //                    real transform, kx = 0..Kc kept: the hand-off between the
 //                    row pass (physical space, x contiguous) and the column
 //                    pass (spectral space, transform along y).
-//   packed y-fields  the fields that row passes read in pairs (A, B) -- the
-//                    RK stage fields (u, w_x), (v, w_y) and the adjoint's
-//                    (Lam_x, Lam_y) -- are stored as P = A + i B and
-//                    Q = A - i B (each [B][N][KXP]): entry e of the row's full
-//                    complex signal A + i B is P[e] for e <= Kc and conj(Q[N-e])
-//                    for e >= N - Kc, one 16-byte load either way.
+//   packed y-fields  two real fields (A, B) that a row pass reads as one complex
+//                    signal A + i B -- the velocity (u, v) of an RK stage, and
+//                    the adjoint's (b, a) (see col_pass_kernel) -- are stored as
+//                    P = A + i B and Q = A - i B (each [B][N][KXP]): entry e of
+//                    the row's full complex signal is P[e] for e <= Kc and
+//                    conj(Q[N-e]) for e >= N - Kc, one 16-byte load either way.
+//                    Row passes store their products in the same form.
 // Every 2D transform is a row pass + a column pass over Y; pointwise spectral
 // work (projection, Poisson inversion, velocity, derivatives, Lawson RK4
 // combine, adjoint transposes) is fused into the column pass, products of
@@ -33,20 +34,14 @@ struct Dims {
     int var, tpb;    // forward row passes: FFT plan variant (0..3; 3 = pipelined), rows (waves) per workgroup
     int avar, atpb;  // adjoint row passes: FFT plan variant (0..3), rows (waves) per workgroup
     int cvar, cb;    // column pass: FFT plan variant, kx columns per workgroup
-    int csplit;      // column pass: workgroups per column sharing its outputs (0: chosen per launch)
+    int csplit;      // column pass: a pair's signals on one team (1) or twin teams (2, 4); 0: chosen per launch
     int cus;         // compute units of the device (persistent grids)
     int lds_max;     // bytes of LDS a workgroup may use on the device (column blocks beyond 64 KiB)
 };
 
 // Column-pass outputs: the field itself, or one half of a packed pair
-// (P = A + i B, Q = A - i B) with (A, B) = (u, w_x), (v, w_y) or (Lam_x, Lam_y).
-enum FieldKind : int { F_OMEGA = 0, F_UP = 1, F_UQ = 2, F_VP = 3, F_VQ = 4, F_LP = 5, F_LQ = 6 };
-
-// Multiplier applied to an adjoint column input after its y-transform.  The
-// adjoint row pass stores its two products (G1, G2) unsplit, as P = Z and
-// Q = conj Z(-k) of Z = F_x(G1 + i G2), so G1 = (P + Q)/2 and G2 = (P - Q)/(2i),
-// and the column pass's 1/|k|^2 G1 + G2 becomes P (1/|k|^2 - i)/2 + Q (1/|k|^2 + i)/2.
-enum InMul : int { IN_PAIRP = 0, IN_PAIRQ = 1, IN_IKY_INVK2 = 2, IN_MIKX_INVK2 = 3 };
+// (P = A + i B, Q = A - i B) with (A, B) = (u, v) or the adjoint's (b, a).
+enum FieldKind : int { F_OMEGA = 0, F_ZP = 1, F_ZQ = 2, F_WP = 3, F_WQ = 4 };
 
 enum ColMode : int {
     COL_INIT = 0,     // Y -> P omega0 -> state (+checkpoint) -> derived fields
@@ -55,17 +50,14 @@ enum ColMode : int {
     COL_FROM_STATE = 6,   // compact state -> derived fields (no input transform)
     COL_ADJ_C = 7, COL_ADJ_B = 8, COL_ADJ_A = 9, COL_ADJ_N = 10,  // adjoint stages
     COL_ADJ_SRC = 11, // terminal source -> lambda_H
-    COL_FIRST_GUESS = 12, // probe velocities (u, v grids) -> band-limited vorticity
-    COL_ADJ_NSRC = 13     // adjoint stage n at an observed step: two more inputs (residual sources)
+    COL_FIRST_GUESS = 12  // probe velocities (u, v grids) -> band-limited vorticity
 };
 
 struct ColArgs {
-    const cd* yin[4];        // inputs (Y layout)
-    int nin;                 // adjoint modes: number of inputs
-    int inmul[4];            // adjoint modes: InMul per input
-    cd* yout[4];             // derived outputs (Y layout)
+    const cd* yin[2];        // inputs (Y layout): one field, or a packed pair P, Q
+    cd* yout[2];             // derived outputs (Y layout)
     int nout;
-    int fields[4];           // FieldKind per output
+    int fields[2];           // FieldKind per output
     cd* omega;               // compact state (rw)
     cd* acc;                 // compact RK4 accumulator (rw)
     cd* lam;                 // compact adjoint lambda_{n+1} / lambda_n
@@ -85,9 +77,7 @@ struct ColArgs {
     int mult_per_member;     // COL_FILTER: multiplier table per member
     int lowpass;             // COL_FIRST_GUESS: keep |kx|, |ky| <= lowpass
     cd* omega_out;           // COL_D: the new state, in a buffer other than omega (null: in place)
-    int split;               // set by the launcher: the derived fields of a column are shared out
-                             // over this many workgroups (blockIdx.z, round robin); the first also
-                             // writes the compact outputs
+    int cb;                  // set by the launcher: kx columns per workgroup
 };
 
 struct RowObs {
@@ -96,12 +86,17 @@ struct RowObs {
     const double* values;    // [B][n_times][2][M][M] or null
     double* obs_out;         // [B][n_times][2][M][M] or null
     double* jpart;           // [B][n_times][M] or null
-    int imp_x, imp_y;        // impulse source (row_src mode 1)
+    int imp_x, imp_y;        // impulse source (SRC_IMPULSE)
 };
 
+// Adjoint source rows: residuals of an observed step over every row (zero off
+// the probes), a unit u-impulse, or residuals added to the packed products of
+// the observed rows.
+enum SrcMode : int { SRC_WRITE = 0, SRC_IMPULSE = 1, SRC_ADD = 2 };
+
 struct RowArgs {
-    const cd* yin[6];
-    cd* yout[4];
+    const cd* yin[4];        // packed (u, v), then (adjoint rows) packed (b, a)
+    cd* yout[2];             // packed products
     const double* phys_in;
     double* phys_out;
     const cd* tw;
@@ -113,10 +108,10 @@ template <int N>
 struct Launch {
     static hipError_t row_r2c(const Dims& d, const double* in, cd* out, const cd* tw, hipStream_t s);
     static hipError_t row_c2r(const Dims& d, const cd* in, double* out, const cd* tw, hipStream_t s);
-    static hipError_t row_nl(const Dims& d, const RowArgs& a, hipStream_t s);
+    static hipError_t row_sq(const Dims& d, const RowArgs& a, hipStream_t s);
     static hipError_t row_obs(const Dims& d, const RowArgs& a, hipStream_t s);
-    static hipError_t row_adj(const Dims& d, const RowArgs& a, hipStream_t s);
-    static hipError_t row_src(const Dims& d, const RowArgs& a, int impulse, hipStream_t s);
+    static hipError_t row_mul(const Dims& d, const RowArgs& a, hipStream_t s);
+    static hipError_t row_src(const Dims& d, const RowArgs& a, int mode, hipStream_t s);
     static hipError_t col(const Dims& d, int mode, const ColArgs& a, hipStream_t s);
     static int threads(int var);
 };
@@ -127,10 +122,10 @@ int fft_threads(int N, int var);
 // launchers (kernels.hip)
 hipError_t launch_row_r2c(const Dims& d, const double* in, cd* out, const cd* tw, hipStream_t s);
 hipError_t launch_row_c2r(const Dims& d, const cd* in, double* out, const cd* tw, hipStream_t s);
-hipError_t launch_row_nl(const Dims& d, const RowArgs& a, hipStream_t s);
+hipError_t launch_row_sq(const Dims& d, const RowArgs& a, hipStream_t s);
 hipError_t launch_row_obs(const Dims& d, const RowArgs& a, hipStream_t s);
-hipError_t launch_row_adj(const Dims& d, const RowArgs& a, hipStream_t s);
-hipError_t launch_row_src(const Dims& d, const RowArgs& a, int impulse, hipStream_t s);
+hipError_t launch_row_mul(const Dims& d, const RowArgs& a, hipStream_t s);
+hipError_t launch_row_src(const Dims& d, const RowArgs& a, int mode, hipStream_t s);
 hipError_t launch_col(const Dims& d, int mode, const ColArgs& a, hipStream_t s);
 
 // small kernels (misc.hip)

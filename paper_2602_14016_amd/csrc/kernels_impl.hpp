@@ -295,228 +295,179 @@ __global__ void __launch_bounds__(256) row_c2r_kernel(Dims d, const cd* __restri
     }
 }
 
-// Right-hand side products of one row:  q = u w_x + v w_y.  Inputs
-// yin[0..3] = the packed pairs (u, w_x) P, Q and (v, w_y) P, Q of the stage,
-// output yout[0] = row transform of q.
-// Every input load is issued before the first transform, so the memory
-// latency is paid once per kernel rather than once per transform.
-// Observations are formed by row_obs_kernel from the same fields.
+// The row passes work on velocities only.  With div u = 0 the advection term is
+//   u . grad w = (d_xx - d_yy)(u v) + d_xy(v^2 - u^2),
+// so a right-hand side needs two fields in physical space instead of the four
+// of u w_x + v w_y.  They travel as the one complex signal z = u + i v, whose
+// square z^2 = (u^2 - v^2) + i 2 u v holds both products: two transforms per
+// row, two fields read and two written (2 + 2 against 4 + 1 and 2.5).  Its
+// transpose multiplies by conj(z): with a = (d_yy - d_xx) Lam and
+// b = 2 d_xy Lam (as multipliers kx^2 - ky^2 and -2 kx ky of the spectrum),
+//   N'(w)^T Lam = U^T(a v + b u) + V^T(a u - b v),
+// and (a v + b u) + i (a u - b v) = (b + i a) conj(z).  On the de-aliased band
+// both identities hold exactly (every alias of a product falls outside it).
+// The passes are bound by HBM traffic at large batches (64 x 256^2: 464 instead
+// of 548 bytes per grid point and forward + adjoint step).  Per launch there,
+// advective form -> this one: forward rows 27.3 -> 21.6 us (4.2 TB/s), adjoint
+// rows 38.7 -> 28.0 us (4.8 TB/s); the tape holds half the fields.
+
+// z^2 and w conj(z)
+__device__ __forceinline__ cd csq(cd z) { return mk((z.x - z.y) * (z.x + z.y), 2.0 * z.x * z.y); }
+
+// Whether a row pass reads its twiddles from the LDS table instead of holding
+// them in registers: the eight-value plans at 512 and 1024 points have 14 and
+// 19 factors per thread, which spill beside two signals at three waves per SIMD.
 template <int N, int V>
-__device__ __forceinline__ void row_nl_body(const Dims& d, const RowArgs& a) {
+constexpr bool row_tw_lds() { return (N == 1024 || N == 512) && Plan<N, V>::E >= 8; }
+
+// Right-hand side products of one row.  Inputs yin[0..1] = the packed velocity
+// (u, v), outputs yout[0..1] = the row transform Z of z^2, unsplit
+// (pair_store): Z and conj Z(-k).  Observations are formed by row_obs_kernel
+// from the same field.
+template <int N, int V>
+constexpr int sq_waves() { return Plan<N, V>::E <= 4 ? 5 : Plan<N, V>::E <= 8 ? 4 : 2; }
+
+template <int N, int V>
+__global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(sq_waves<N, V>())))
+row_sq_kernel(Dims d, RowArgs a) {
     const cd* __restrict__ tw_g = a.tw;
     PA_TEAM_SETUP(N, V, N)
-    const int y = wi;
-    const size_t roff = ((size_t)b * N + y) * kx_pad<N>();
-    cd z1[E], z2[E];
-    packed_load<N, V>(z1, a.yin[0] + roff, a.yin[1] + roff, t);   // u + i w_x
-    packed_load<N, V>(z2, a.yin[2] + roff, a.yin[3] + roff, t);   // v + i w_y
-    RowTw<N, V> tr;   // the three transforms of the row share the thread's twiddles
-    row_twiddles<N, V>(tr, t, tw_g, tw_lds);
-    row_fft<N, V, true, WL>(z1, t, lds, tr);
-    row_fft<N, V, true, WL>(z2, t, lds, tr);
+    const size_t roff = ((size_t)b * N + wi) * kx_pad<N>();
     cd z[E];
-#pragma unroll
-    for (int m = 0; m < E; ++m) z[m] = mk(z1[m].x * z1[m].y + z2[m].x * z2[m].y, 0.0);
-    row_fft<N, V, false, WL>(z, t, lds, tr);
-    cd* o = a.yout[0] + roff;
-#pragma unroll
-    for (int m = 0; m < E; ++m) {
-        const int k = t + T * m;
-        if (slot_low<N, V>(m) && k <= band<N>()) o[k] = z[m];
-    }
-}
-
-// Occupancy hint for the right-hand-side row pass: three waves per SIMD (168
-// VGPRs).  With 8 register slots per thread (one row per team) the row's data
-// and its twiddle factors in registers fit; at four waves (128 VGPRs) the
-// twiddles spill, and reading them from LDS instead is 3.5 % slower at 256^2.
-// The two-row kernel of the 4-slot plan holds both rows' loads.
-template <int N, int V>
-constexpr int nl_waves() { return Plan<N, V>::E <= 8 ? 3 : 1; }
-
-// Two rows per team: q of both rows is real, so one complex transform of
-// q_a + i q_b, split into the two half spectra, replaces two transforms of
-// real signals (2.5 transforms per row instead of 3).  Used with the
-// four-values-per-thread plan, where both rows' signals fit in registers.
-template <int N, int V>
-__device__ __forceinline__ void row_nl_pair_body(const Dims& d, const RowArgs& a) {
-    const cd* __restrict__ tw_g = a.tw;
-    PA_TEAM_SETUP(N, V, N / 2)
-    constexpr int KXP = kx_pad<N>();
-    const size_t ra = ((size_t)b * N + 2 * wi) * KXP, rb = ra + KXP;
-    cd z1[E], z2[E], y1[E], y2[E];
-    packed_load<N, V>(z1, a.yin[0] + ra, a.yin[1] + ra, t);   // row a: u + i w_x
-    packed_load<N, V>(z2, a.yin[2] + ra, a.yin[3] + ra, t);   //        v + i w_y
-    packed_load<N, V>(y1, a.yin[0] + rb, a.yin[1] + rb, t);   // row b
-    packed_load<N, V>(y2, a.yin[2] + rb, a.yin[3] + rb, t);
-    cd z[E];
-    if constexpr (wave256<N, V>()) {
-        RowTw<N, V> tr;
-        row_twiddles<N, V>(tr, t, tw_g, tw_lds);
-        row_fft<N, V, true, WL>(z1, t, lds, tr);
-        row_fft<N, V, true, WL>(z2, t, lds, tr);
-        row_fft<N, V, true, WL>(y1, t, lds, tr);
-        row_fft<N, V, true, WL>(y2, t, lds, tr);
-#pragma unroll
-        for (int m = 0; m < E; ++m)
-            z[m] = mk(z1[m].x * z1[m].y + z2[m].x * z2[m].y, y1[m].x * y1[m].y + y2[m].x * y2[m].y);
-        row_fft<N, V, false, WL>(z, t, lds, tr);
-    } else {
+    packed_load<N, V>(z, a.yin[0] + roff, a.yin[1] + roff, t);
+    if constexpr (row_tw_lds<N, V>()) {
         const cd* twl = stage_twiddles<N, V>(tw_lds, tw_g);
-        fft<N, V, true, WL>(z1, t, lds, twl);
-        fft<N, V, true, WL>(z2, t, lds, twl);
-        fft<N, V, true, WL>(y1, t, lds, twl);
-        fft<N, V, true, WL>(y2, t, lds, twl);
+        fft<N, V, true, WL>(z, t, lds, twl);
 #pragma unroll
-        for (int m = 0; m < E; ++m)
-            z[m] = mk(z1[m].x * z1[m].y + z2[m].x * z2[m].y, y1[m].x * y1[m].y + y2[m].x * y2[m].y);
+        for (int m = 0; m < E; ++m) z[m] = csq(z[m]);
         fft<N, V, false, WL>(z, t, lds, twl);
+    } else {
+        RowTw<N, V> tr;   // both transforms share the thread's twiddles
+        row_twiddles<N, V>(tr, t, tw_g, tw_lds);
+        row_fft<N, V, true, WL>(z, t, lds, tr);
+#pragma unroll
+        for (int m = 0; m < E; ++m) z[m] = csq(z[m]);
+        row_fft<N, V, false, WL>(z, t, lds, tr);
     }
-    split_store<N, V, WL>(z, t, lds, a.yout[0] + ra, a.yout[0] + rb);
+    pair_store<N, V>(z, t, a.yout[0] + roff, a.yout[1] + roff);
 }
 
-// Variant 2 runs two rows per team where its plan has four values per thread
-// (16 to 256 points); with eight values the two rows' signals spill.
-template <int N>
-__host__ __device__ constexpr bool nl_pairs() { return Plan<N, 2>::E == 4; }
-
-template <int N, int V>
-__global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(nl_waves<N, V>())))
-row_nl_kernel(Dims d, RowArgs a) {
-    if constexpr (V == 2 && nl_pairs<N>()) row_nl_pair_body<N, V>(d, a);
-    else row_nl_body<N, V>(d, a);
-}
-
-// Observation of one step: team per observed row; yin[0..3] = the stage's
-// packed pairs (u, w_x) and (v, w_y); u and v are the real parts of their row
-// transforms.
+// Observation of one step: team per observed row; yin[0..1] = the packed
+// velocity of the state.
 template <int N, int V>
 __global__ void __launch_bounds__(256) row_obs_kernel(Dims d, RowArgs a) {
     const cd* __restrict__ tw_g = a.tw;
     PA_TEAM_SETUP(N, V, a.obs.M)
     const int y = wi * a.obs.stride;
     const size_t roff = ((size_t)b * N + y) * kx_pad<N>();
-    cd z1[E], z2[E];
-    packed_load<N, V>(z1, a.yin[0] + roff, a.yin[1] + roff, t);
-    packed_load<N, V>(z2, a.yin[2] + roff, a.yin[3] + roff, t);
+    cd z[E];
+    packed_load<N, V>(z, a.yin[0] + roff, a.yin[1] + roff, t);
     const cd* twl = stage_twiddles<N, V>(tw_lds, tw_g);
-    fft<N, V, true, WL>(z1, t, lds, twl);
-    fft<N, V, true, WL>(z2, t, lds, twl);
+    fft<N, V, true, WL>(z, t, lds, twl);
     double part = 0.0;
 #pragma unroll
     for (int m = 0; m < E; ++m) {
-        part += observe_comp(a.obs, b, y, t + T * m, 0, z1[m].x);
-        part += observe_comp(a.obs, b, y, t + T * m, 1, z2[m].x);
+        part += observe_comp(a.obs, b, y, t + T * m, 0, z[m].x);
+        part += observe_comp(a.obs, b, y, t + T * m, 1, z[m].y);
     }
     const double s = team_sum<N, V, WL>(part, t, lds);
     if (t == 0) store_jpart(a.obs, b, y, s);
 }
 
-// Occupancy hint for the adjoint row pass: with 8 register slots per thread
-// its three input signals fit the 168 VGPRs of three waves per SIMD (a couple
-// of spilled values at most); with 16 slots the hint would spill heavily.
+// Occupancy hint for the adjoint row pass (two signals per thread).
 template <int N, int V>
-constexpr int adj_waves() { return Plan<N, V>::E <= 8 ? 3 : 1; }
+constexpr int mul_waves() { return Plan<N, V>::E <= 4 ? 4 : Plan<N, V>::E <= 8 ? 3 : 1; }
 
-// The 1024-point plans of eight values per thread (two wavefronts per row)
-// read their twiddles from the LDS table in the adjoint rows: their 19
-// register factors would spill 64 values per thread at three waves per SIMD,
-// and from LDS the kernel fits in 162 VGPRs.  Measured at 1024^2 with four
-// and eight members: 69.0 -> 55.0 and 131 -> 96 us per launch.  The forward
-// rows keep register twiddles (there LDS is 6-7 % slower).
+// Adjoint products of one row.  Inputs yin[0..1] = the packed velocity (u, v)
+// of the stage state, yin[2..3] = the packed pair (b, a) of the cotangent;
+// outputs yout[0..1] = the row transform Z of (b + i a) conj(z), unsplit.
 template <int N, int V>
-constexpr bool adj_tw_lds() { return (N == 1024 || N == 512) && Plan<N, V>::E == 8; }
-
-// Adjoint products of one row.  The transpose of the tangent right-hand side
-// applied to lambda, with Lam = P lambda, is on the de-aliased band
-//   (1/|k|^2) F[w_x Lam_y - w_y Lam_x] + F[u Lam_x + v Lam_y]
-// (the product rule holds on the band because the 2/3 rule keeps every alias
-// outside it, and u_x + v_y = 0).  Inputs yin[0..3] = the packed pairs (u, w_x)
-// and (v, w_y) of the stage state, yin[4..5] = the packed pair (Lam_x, Lam_y).
-// Outputs: the row transform Z of G1 + i G2, G1 = w_x Lam_y - w_y Lam_x and
-// G2 = u Lam_x + v Lam_y, unsplit (pair_store): yout[0] = Z, yout[1] = conj Z(-k).
-template <int N, int V>
-__global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(adj_waves<N, V>())))
-row_adj_kernel(Dims d, RowArgs a) {
+__global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(mul_waves<N, V>())))
+row_mul_kernel(Dims d, RowArgs a) {
     const cd* __restrict__ tw_g = a.tw;
     PA_TEAM_SETUP(N, V, N)
-    const int y = wi;
-    const size_t roff = ((size_t)b * N + y) * kx_pad<N>();
-    cd L[E], z1[E], z2[E];   // (Lam_x, Lam_y), (u, w_x), (v, w_y)
-    packed_load<N, V>(L, a.yin[4] + roff, a.yin[5] + roff, t);
-    packed_load<N, V>(z1, a.yin[0] + roff, a.yin[1] + roff, t);
-    packed_load<N, V>(z2, a.yin[2] + roff, a.yin[3] + roff, t);
-    cd G[E];   // (G1, G2)
-    auto products = [&]() {
-#pragma unroll
-        for (int m = 0; m < E; ++m)
-            G[m] = mk(z1[m].y * L[m].y - z2[m].y * L[m].x, z1[m].x * L[m].x + z2[m].x * L[m].y);
-    };
-    if constexpr (adj_tw_lds<N, V>()) {
+    const size_t roff = ((size_t)b * N + wi) * kx_pad<N>();
+    cd w[E], z[E];
+    packed_load<N, V>(w, a.yin[2] + roff, a.yin[3] + roff, t);
+    packed_load<N, V>(z, a.yin[0] + roff, a.yin[1] + roff, t);
+    if constexpr (row_tw_lds<N, V>()) {
         const cd* twl = stage_twiddles<N, V>(tw_lds, tw_g);
-        fft<N, V, true, WL>(L, t, lds, twl);
-        fft<N, V, true, WL>(z1, t, lds, twl);
-        fft<N, V, true, WL>(z2, t, lds, twl);
-        products();
-        fft<N, V, false, WL>(G, t, lds, twl);
+        fft<N, V, true, WL>(w, t, lds, twl);
+        fft<N, V, true, WL>(z, t, lds, twl);
+#pragma unroll
+        for (int m = 0; m < E; ++m) w[m] = cmulc(w[m], z[m]);
+        fft<N, V, false, WL>(w, t, lds, twl);
     } else {
-        RowTw<N, V> tr;   // the four transforms of the row share the thread's twiddles
+        RowTw<N, V> tr;   // the three transforms of the row share the thread's twiddles
         row_twiddles<N, V>(tr, t, tw_g, tw_lds);
-        row_fft<N, V, true, WL>(L, t, lds, tr);
-        row_fft<N, V, true, WL>(z1, t, lds, tr);
-        row_fft<N, V, true, WL>(z2, t, lds, tr);
-        products();
-        row_fft<N, V, false, WL>(G, t, lds, tr);
+        row_fft<N, V, true, WL>(w, t, lds, tr);
+        row_fft<N, V, true, WL>(z, t, lds, tr);
+#pragma unroll
+        for (int m = 0; m < E; ++m) w[m] = cmulc(w[m], z[m]);
+        row_fft<N, V, false, WL>(w, t, lds, tr);
     }
-    pair_store<N, V>(G, t, a.yout[0] + roff, a.yout[1] + roff);
+    pair_store<N, V>(w, t, a.yout[0] + roff, a.yout[1] + roff);
 }
 
-// Adjoint source rows.  mode 0: observation residual at one observed step
-// (yin[0..3] = the packed pairs (u, w_x), (v, w_y) of that state); mode 1:
-// unit u-impulse at (imp_x, imp_y).
-// Outputs yout[0] = row transform of -S^T r_u, yout[1] = of -S^T r_v.
-template <int N, int V>
-__global__ void __launch_bounds__(256) row_src_kernel(Dims d, RowArgs a, int impulse) {
+// Adjoint source rows: the row transform Z of r_u + i r_v on the probes of one
+// observed step (yin[0..1] = the packed velocity of that state) or of a unit
+// u-impulse at (imp_x, imp_y), in the form of the adjoint products, whose
+// U^T and V^T it shares.  SRC_WRITE and SRC_IMPULSE cover every row of the
+// member; SRC_ADD covers the observed rows (team per observed row) and adds to
+// the products already there.
+template <int N, int V, int MODE>
+__global__ void __launch_bounds__(256) row_src_kernel(Dims d, RowArgs a) {
     const cd* __restrict__ tw_g = a.tw;
-    PA_TEAM_SETUP(N, V, N)
-    const int y = wi;
-    const size_t roff = ((size_t)b * N + y) * kx_pad<N>();
+    PA_TEAM_SETUP(N, V, MODE == SRC_ADD ? a.obs.M : N)
     const RowObs& o = a.obs;
-    cd z[E], z2[E];
-    if (!impulse) {
-        packed_load<N, V>(z, a.yin[0] + roff, a.yin[1] + roff, t);
-        packed_load<N, V>(z2, a.yin[2] + roff, a.yin[3] + roff, t);
-    }
+    const int y = MODE == SRC_ADD ? wi * o.stride : wi;
+    const size_t roff = ((size_t)b * N + y) * kx_pad<N>();
+    cd z[E];
+    if constexpr (MODE != SRC_IMPULSE) packed_load<N, V>(z, a.yin[0] + roff, a.yin[1] + roff, t);
     const cd* twl = stage_twiddles<N, V>(tw_lds, tw_g);
-    if (!impulse) {
-        fft<N, V, true, WL>(z, t, lds, twl);
-        fft<N, V, true, WL>(z2, t, lds, twl);
-    }
+    if constexpr (MODE != SRC_IMPULSE) fft<N, V, true, WL>(z, t, lds, twl);
 #pragma unroll
     for (int m = 0; m < E; ++m) {
         const int x = t + T * m;
-        double A = 0.0, Bv = 0.0;
-        if (impulse) {
-            if (x == o.imp_x && y == o.imp_y) A = -1.0;
-        } else if (o.values && (y % o.stride) == 0 && (x % o.stride) == 0) {
+        cd r = czero();
+        if constexpr (MODE == SRC_IMPULSE) {
+            if (x == o.imp_x && y == o.imp_y) r.x = 1.0;
+        } else if ((y % o.stride) == 0 && (x % o.stride) == 0) {
             const int i = x / o.stride, j = y / o.stride, M = o.M;
             const size_t base = (((size_t)b * o.n_times + o.slot) * 2) * M * M + (size_t)j * M + i;
-            A = -(z[m].x - o.values[base]);
-            Bv = -(z2[m].x - o.values[base + (size_t)M * M]);
+            r = mk(z[m].x - o.values[base], z[m].y - o.values[base + (size_t)M * M]);
         }
-        z[m] = mk(A, Bv);
+        z[m] = r;
     }
     fft<N, V, false, WL>(z, t, lds, twl);
-    split_store<N, V, WL>(z, t, lds, a.yout[0] + roff, a.yout[1] + roff);
+    cd* const outP = a.yout[0] + roff;
+    cd* const outQ = a.yout[1] + roff;
+    if constexpr (MODE == SRC_ADD) {
+        constexpr int K = band<N>();
+#pragma unroll
+        for (int m = 0; m < E; ++m) {
+            const int k = t + T * m, kn = (N - k) & (N - 1);
+            if (k <= K) outP[k] = cadd(outP[k], z[m]);
+            if (kn <= K) outQ[kn] = cadd(outQ[kn], mk(z[m].x, -z[m].y));
+        }
+    } else {
+        pair_store<N, V>(z, t, outP, outQ);
+    }
+}
+
+template <int N, int V> constexpr auto row_src_write = &row_src_kernel<N, V, SRC_WRITE>;
+template <int N, int V> constexpr auto row_src_impulse = &row_src_kernel<N, V, SRC_IMPULSE>;
+template <int N, int V> constexpr auto row_src_add = &row_src_kernel<N, V, SRC_ADD>;
+
+// Returns v unchanged, opaquely: index arithmetic derived from it is neither
+// hoisted out of a loop nor kept from an earlier phase of a kernel (where its
+// results would occupy registers across the transforms) but recomputed.
+__device__ __forceinline__ int opaque(int v) {
+    asm volatile("" : "+v"(v));
+    return v;
 }
 
 // ---------------------------------------------------------- column pass --
-
-__device__ __forceinline__ int band_row(int q, int N, int K, int KY) {
-    if (q <= K) return q;
-    if (q >= N - K) return q - N + KY;
-    return -1;
-}
 
 // Position of workgroup `id` of a one-dimensional grid of `n` in an order in
 // which each XCD holds a contiguous run: workgroup id runs on XCD id % XCDS
@@ -529,293 +480,387 @@ __device__ __forceinline__ unsigned xcd_order(unsigned id, unsigned n) {
     return (x < r ? x * (q + 1) : r * (q + 1) + (x - r) * q) + k;
 }
 
-// Occupancy hint for the column pass: three waves per SIMD (168 VGPRs) for the
+// Compact outputs and tables of a column launch, at the workgroup's member and
+// first column.
+struct ColPtrs {
+    cd *om, *ac, *ck, *lm, *ob;
+    const cd *p0, *p1;       // compact operands: (omega_n, acc) forward, (lambda, omega-bar) adjoint
+    const double* ik2;
+    double ex, sc;
+};
+
+template <int MODE>
+struct ColTraits {
+    static constexpr bool FWD = MODE >= COL_A && MODE <= COL_D;
+    static constexpr bool ADJ = MODE >= COL_ADJ_C && MODE <= COL_ADJ_SRC;
+    static constexpr bool PAIR_IN = FWD || ADJ || MODE == COL_FIRST_GUESS;
+    static constexpr bool NEED0 = FWD || MODE == COL_FROM_STATE || (ADJ && MODE != COL_ADJ_N && MODE != COL_ADJ_SRC);
+    static constexpr bool NEED1 = (FWD && MODE != COL_A) || (ADJ && MODE != COL_ADJ_C && MODE != COL_ADJ_SRC);
+};
+
+template <int MODE>
+__device__ __forceinline__ ColPtrs col_ptrs(const ColArgs& a, size_t cmem, int b, int kx0, int kx) {
+    using M = ColTraits<MODE>;
+    ColPtrs q;
+    q.om = a.omega ? (MODE == COL_D && a.omega_out ? a.omega_out : a.omega) + cmem : nullptr;
+    q.ac = a.acc ? a.acc + cmem : nullptr;
+    q.ck = a.ckpt ? a.ckpt + cmem : nullptr;
+    q.lm = M::ADJ ? a.lam + cmem : nullptr;
+    q.ob = M::ADJ && a.omb ? a.omb + cmem : nullptr;
+    q.p0 = M::FWD ? a.omega + cmem : M::ADJ ? a.lam + cmem : a.state_in + cmem;
+    q.p1 = M::FWD ? a.acc + cmem : a.omb + cmem;
+    q.ik2 = a.invk2 + kx0;
+    q.ex = a.ex2[kx];
+    q.sc = M::ADJ && a.scale ? a.scale[b] : 1.0;
+    return q;
+}
+
+// What a mode's transformed inputs P, Q give (0 off the band and for the mean):
+// the nonlinear term of a forward stage, the cotangent of an adjoint stage, the
+// vorticity of probe velocities, or the one input itself.
+template <int MODE>
+__device__ __forceinline__ cd col_pair_value(const ColArgs& a, const ColPtrs& q, bool ins, unsigned ci, int kx, int ky_,
+                                             cd P, cd Q) {
+    const double dkx = (double)kx, ky = (double)ky_;
+    if constexpr (ColTraits<MODE>::FWD) {
+        // -P u . grad w = beta (P + Q) + alpha (P - Q)/i with the spectra of z^2,
+        // alpha = (kx^2 - ky^2)/4, beta = -kx ky/2
+        const double al = 0.25 * (dkx * dkx - ky * ky), be = -0.5 * dkx * ky;
+        return ins ? mk(be * (P.x + Q.x) + al * (P.y - Q.y), be * (P.y + Q.y) - al * (P.x - Q.x)) : czero();
+    } else if constexpr (ColTraits<MODE>::ADJ) {
+        // U^T and V^T of the products, ((kx - i ky) P - (kx + i ky) Q) / (2 |k|^2)
+        const double f = ins ? 0.5 * q.ik2[ci] : 0.0;
+        return ins ? mk(f * (dkx * (P.x - Q.x) + ky * (P.y + Q.y)), f * (dkx * (P.y - Q.y) - ky * (P.x + Q.x))) : czero();
+    } else if constexpr (MODE == COL_FIRST_GUESS) {
+        // vorticity of the low-passed probe velocity: i kx v_hat - i ky u_hat on S
+        const bool keep = ins && kx <= a.lowpass && ky_ <= a.lowpass && -ky_ <= a.lowpass;
+        return keep ? mk(-dkx * Q.y + ky * P.y, dkx * Q.x - ky * P.x) : czero();
+    } else {
+        return ins ? P : czero();
+    }
+}
+
+// The rest of a mode's spectral work: its pair value nl and compact operands
+// s0, s1 in, compact outputs written at ci (when `on`: the mode lies in the
+// band), the value handed to the output transforms returned.  r is the compact
+// row, ins: in the band and not the mean.
+template <int N, int MODE>
+__device__ __forceinline__ cd col_mode_update(const ColArgs& a, const ColPtrs& q, bool on, bool ins, unsigned ci,
+                                              int b, int kx, int r, int ky_, cd nl, cd s0, cd s1) {
+    constexpr int KXP = kx_pad<N>(), KY = 2 * band<N>() + 1;
+    const double h = a.h;
+    const double e2 = q.ex * a.ey2[r], e1 = e2 * e2;
+    if constexpr (MODE == COL_INIT) {
+        if (on) {
+            if (q.om) stc(q.om, ci, nl);
+            if (q.ck) stc(q.ck, ci, nl);
+        }
+        return nl;
+    } else if constexpr (MODE == COL_FILTER) {
+        const size_t mi = (a.mult_per_member ? (size_t)b * KY * KXP : 0) + (size_t)r * KXP + kx;
+        return cscale(nl, a.mult[mi]);
+    } else if constexpr (MODE == COL_FIRST_GUESS) {
+        return nl;
+    } else if constexpr (MODE == COL_FROM_STATE) {
+        const cd w = ins ? s0 : czero();
+        if (on && q.om) stc(q.om, ci, w);
+        return w;
+    } else if constexpr (ColTraits<MODE>::FWD) {
+        if (a.nf > 0 && kx == 0 && (ky_ == a.nf || ky_ == -a.nf)) nl.x += a.forcing;
+        if constexpr (MODE == COL_A) {
+            if (on && q.ac) stc(q.ac, ci, cscale(nl, e1));
+            return cscale(mk(s0.x + 0.5 * h * nl.x, s0.y + 0.5 * h * nl.y), e2);
+        } else if constexpr (MODE == COL_D) {
+            const double h6 = h / 6.0;
+            const cd w = mk(e1 * s0.x + h6 * (s1.x + nl.x), e1 * s0.y + h6 * (s1.y + nl.y));
+            if (on) {
+                if (q.om) stc(q.om, ci, w);
+                if (q.ck) stc(q.ck, ci, w);
+            }
+            return w;
+        } else {
+            if (on && q.ac) stc(q.ac, ci, mk(s1.x + 2.0 * e2 * nl.x, s1.y + 2.0 * e2 * nl.y));
+            if constexpr (MODE == COL_B) return mk(e2 * s0.x + 0.5 * h * nl.x, e2 * s0.y + 0.5 * h * nl.y);
+            else return mk(e1 * s0.x + h * e2 * nl.x, e1 * s0.y + h * e2 * nl.y);
+        }
+    } else {
+        const cd wb = nl;
+        if constexpr (MODE == COL_ADJ_C) {
+            if (on && q.ob) stc(q.ob, ci, mk(e1 * (s0.x + wb.x), e1 * (s0.y + wb.y)));
+            return mk((h / 3.0) * e2 * s0.x + h * e2 * wb.x, (h / 3.0) * e2 * s0.y + h * e2 * wb.y);
+        } else if constexpr (MODE == COL_ADJ_B) {
+            if (on && q.ob) stc(q.ob, ci, mk(s1.x + e2 * wb.x, s1.y + e2 * wb.y));
+            return mk((h / 3.0) * e2 * s0.x + 0.5 * h * wb.x, (h / 3.0) * e2 * s0.y + 0.5 * h * wb.y);
+        } else if constexpr (MODE == COL_ADJ_A) {
+            if (on && q.ob) stc(q.ob, ci, mk(s1.x + e2 * wb.x, s1.y + e2 * wb.y));
+            return mk((h / 6.0) * e1 * s0.x + 0.5 * h * e2 * wb.x, (h / 6.0) * e1 * s0.y + 0.5 * h * e2 * wb.y);
+        } else {   // stage n, COL_ADJ_SRC
+            cd ln = wb;
+            if constexpr (MODE == COL_ADJ_N) ln = mk(s1.x + wb.x, s1.y + wb.y);
+            if (on && q.lm) stc(q.lm, ci, ln);
+            return a.final_out ? cscale(ln, q.sc) : cscale(ln, h / 6.0);
+        }
+    }
+}
+
+// Derived fields of a mode: 1_S * multiplier * w / N^2.  The two halves
+// A + i B (second = false) and A - i B of a packed pair are formed before the
+// transform (it is linear): velocity u +- i v has (+-kx + i ky) / |k|^2, the
+// cotangent b +- i a has -2 kx ky +- i (kx^2 - ky^2).
+template <int N>
+__device__ __forceinline__ cd col_field(int kind, bool second, bool ins, const ColPtrs& q, unsigned ci, int kx, int ky_,
+                                        cd w) {
+    if (!ins) return czero();
+    const double dkx = (double)kx, ky = (double)ky_;
+    const cd s = cscale(w, 1.0 / ((double)N * (double)N));
+    if (kind == F_OMEGA) return s;
+    double fr, fi;
+    if (kind == F_ZP) {
+        const double ik2 = q.ik2[ci];
+        fr = (second ? -dkx : dkx) * ik2;
+        fi = ky * ik2;
+    } else {
+        fr = -2.0 * dkx * ky;
+        fi = second ? ky * ky - dkx * dkx : dkx * dkx - ky * ky;
+    }
+    return mk(s.x * fr - s.y * fi, s.x * fi + s.y * fr);
+}
+
+// Two forms of the column pass, with the same arithmetic per value, so a
+// result does not depend on the form:
+//
+// col_pass_kernel: a thread runs both signals (P, then Q) of a pair one after
+// the other.  A workgroup needs one exchange area per column, so three
+// workgroups of eight 256-point columns share a CU: the form for launches that
+// fill the chip (64 x 256^2: 28.9 us per forward stage and 27.3 per adjoint
+// stage, 4.6 and 4.8 TB/s, against 31.0 and 29.4 on twin teams).
+//
+// col_twin_kernel: the two signals run on twin teams of one workgroup: thread
+// t of column c of twin 0 holds P[t + T m], its twin the same entries of Q.  The
+// spectral work of a mode needs both, so between the transforms the twins trade
+// halves: pair p of registers (p, E-1-p) is exchanged such that twin 0 holds P
+// and Q of entry t + T p (ky >= 0) and twin 1 those of entry t + T (E-1-p)
+// (ky < 0).  Each mode is then loaded, combined and written once, and the same
+// exchange hands the output pair back to the transforms.  Twins sit 16 lanes
+// apart, so the exchange is one v_permlane16_swap per register pair and no LDS;
+// pairs that lie in the de-aliased gap are not exchanged at all.  The chain of a
+// launch is two transforms instead of four: the form for launches with too few
+// columns to fill the chip (forward stage against one team per column: one
+// 256^2 member 8.1 against 11.2 us, 32 members 18.3 against 22.6; eight 512^2
+// members 21.9 against 25.6; one 1024^2 member 22.3 against 25.5).
+template <int N>
+__device__ __forceinline__ void twin_swap(double& a, double& b, int twin, int lanes) {
+    if constexpr (N >= 64) {
+        lane_swap16(a, b);
+    } else {   // the smallest grids: teams of fewer than 16 lanes per twin
+        const double got = __shfl_xor(twin ? a : b, lanes);
+        if (twin) a = got;
+        else b = got;
+    }
+}
+template <int N>
+__device__ __forceinline__ void twin_swap(cd& a, cd& b, int twin, int lanes) {
+    twin_swap<N>(a.x, b.x, twin, lanes);
+    twin_swap<N>(a.y, b.y, twin, lanes);
+}
+
+// Most threads of a twin workgroup: plans of up to eight values per thread fit
+// 128 VGPRs.
+template <int N, int V>
+constexpr int twin_threads() { return Plan<N, V>::E <= 8 ? 1024 : 512; }
+
+template <int N>
+__host__ __device__ constexpr size_t col_lds(int areas) { return ((size_t)areas * lds_team<N>() + N) * sizeof(cd); }
+
+// One-dimensional grid of (member, column block), block fastest.  The hardware
+// hands workgroups to the XCDs round robin by id; each XCD is given a
+// contiguous run of that order instead, so that the column blocks of one
+// 128-byte line meet in one L2 rather than fetching and writing the line from
+// several.
+#define PA_COL_SETUP(N)                                                               \
+    constexpr int K = band<N>(), KXP = kx_pad<N>(), KY = 2 * K + 1;                   \
+    using MT = ColTraits<MODE>;                                                       \
+    const unsigned wg = xcd_order(blockIdx.x, gridDim.x);                             \
+    const unsigned nblk = (unsigned)(KXP / CB);                                       \
+    const int b = (int)(wg / nblk);                                                   \
+    const int kx0 = (int)(wg % nblk) * CB;   /* uniform first column of the block */  \
+    const int kx = kx0 + c;                                                           \
+    const bool colok = kx <= K;                                                       \
+    const size_t ymem = (size_t)b * N * KXP + kx0;                                    \
+    const size_t cmem = (size_t)b * KY * KXP + kx0;                                   \
+    auto yoff = [&](int m, int t_) { return (unsigned)c + (unsigned)(t_ + T * m) * (unsigned)KXP; };
+
+template <int N, int V, int MODE>
+__global__ void __launch_bounds__((twin_threads<N, V>())) col_twin_kernel(Dims d, ColArgs a) {
+    constexpr int T = Plan<N, V>::T, E = Plan<N, V>::E, EP = E / 2;
+    extern __shared__ cd smem[];
+    const int CB = a.cb;
+    const int lanes = N >= 64 ? 16 : (CB * T < 16 ? CB * T : 16);   // lanes of one twin in a row
+    const int twin = ((int)threadIdx.x / lanes) & 1;
+    const int idx = (int)threadIdx.x % lanes + (int)threadIdx.x / (2 * lanes) * lanes;
+    const int c = idx % CB, t = idx / CB;
+    cd* lds = smem + (twin * CB + c) * lds_team<N>();
+    PA_COL_SETUP(N)
+    // the mode this thread works on in pair p: its entry, whether it lies in the band, its compact row
+    auto pair_on = [](int p) { return T * p <= K; };   // folds at compile time
+    auto ky_of = [&](int p, int t_) { return twin ? t_ + T * (E - 1 - p) - N : t_ + T * p; };
+    auto in_band = [&](int p, int t_) { return colok && ky_of(p, t_) <= K && -ky_of(p, t_) <= K; };
+    auto row_of = [&](int p, int t_) { return in_band(p, t_) ? ky_of(p, t_) + (twin ? KY : 0) : 0; };
+    auto cidx = [&](int p, int t_) { return (unsigned)c + (unsigned)row_of(p, t_) * (unsigned)KXP; };
+
+    // ---- issue every global load first: the input column and the operands of the
+    // thread's modes.  Loads are unconditional at in-bounds addresses (padding
+    // columns kx < KXP, compact row 0 for modes off the band) and their results
+    // selected, so no load sits in a branch.
+    cd v[E];
+    if constexpr (MODE != COL_FROM_STATE) {
+        const bool has = MT::PAIR_IN || twin == 0;   // a single field: the other twin's signal is zero
+        const cd* __restrict__ src = (MT::PAIR_IN && twin ? a.yin[1] : a.yin[0]) + ymem;
+#pragma unroll
+        for (int m = 0; m < E; ++m) {
+            const cd x = ldc(src, yoff(m, t));
+            v[m] = colok && has ? x : czero();
+        }
+    }
+    const ColPtrs q = col_ptrs<MODE>(a, cmem, b, kx0, kx);
+    cd s0[EP], s1[EP];
+#pragma unroll
+    for (int p = 0; p < EP; ++p) {
+        s0[p] = s1[p] = czero();
+        if (!pair_on(p)) continue;
+        if constexpr (MT::NEED0) s0[p] = ldc(q.p0, cidx(p, t));
+        if constexpr (MT::NEED1) s1[p] = ldc(q.p1, cidx(p, t));
+    }
+    const cd* twl = stage_twiddles<N, V>(smem + 2 * CB * lds_team<N>(), a.tw);
+    if constexpr (MODE != COL_FROM_STATE) {
+        fft<N, V, false>(v, t, lds, twl);
+#pragma unroll
+        for (int p = 0; p < EP; ++p)
+            if (pair_on(p)) twin_swap<N>(v[p], v[E - 1 - p], twin, lanes);
+    }
+    const int kind = a.nout > 0 ? a.fields[0] : F_OMEGA;
+    const int tu = opaque(t);
+#pragma unroll
+    for (int p = 0; p < EP; ++p) {
+        cd& P = v[p];
+        cd& Q = v[E - 1 - p];
+        if (!pair_on(p)) {
+            P = Q = czero();
+            continue;
+        }
+        const bool on = in_band(p, tu);
+        const unsigned ci = cidx(p, tu);
+        const int r = row_of(p, tu), ky = ky_of(p, tu);
+        const bool ins = on && !(kx == 0 && r == 0);
+        const cd nl = col_pair_value<MODE>(a, q, ins, ci, kx, ky, P, Q);
+        const cd w = col_mode_update<N, MODE>(a, q, on, ins, ci, b, kx, r, ky, nl, s0[p], s1[p]);
+        P = col_field<N>(kind, false, ins, q, ci, kx, ky, w);
+        Q = kind == F_OMEGA ? czero() : col_field<N>(kind, true, ins, q, ci, kx, ky, w);
+    }
+    if (a.nout < 1) return;   // uniform over the grid
+#pragma unroll
+    for (int p = 0; p < EP; ++p)
+        if (pair_on(p)) twin_swap<N>(v[p], v[E - 1 - p], twin, lanes);
+    fft<N, V, true>(v, t, lds, twl);
+    if (colok && twin < a.nout) {
+        cd* __restrict__ out = (twin ? a.yout[1] : a.yout[0]) + ymem;
+#pragma unroll
+        for (int m = 0; m < E; ++m) stc(out, yoff(m, tu), v[m]);
+    }
+}
+
+// Occupancy hint for col_pass_kernel: three waves per SIMD (168 VGPRs) for the
 // plans of up to eight values per thread; sixteen values per thread are left
 // unconstrained (a cap there spills hundreds of bytes).
 template <int N, int V>
 constexpr int col_waves() { return Plan<N, V>::E <= 8 ? 3 : 1; }
 
-// Up to 512 threads: CB columns of T threads each (CB * T <= 512).
+// Up to 512 threads: CB columns of T threads each.
 template <int N, int V, int MODE>
-__global__ void __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(col_waves<N, V>()))) col_kernel(Dims d, ColArgs a) {
+__global__ void __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(col_waves<N, V>())))
+col_pass_kernel(Dims d, ColArgs a) {
     constexpr int T = Plan<N, V>::T, E = Plan<N, V>::E;
-    constexpr bool FWD_STAGE = MODE >= COL_A && MODE <= COL_D;
-    constexpr bool ADJ = (MODE >= COL_ADJ_C && MODE <= COL_ADJ_SRC) || MODE == COL_ADJ_NSRC;
-    constexpr bool STAGE_N = MODE == COL_ADJ_N || MODE == COL_ADJ_NSRC;
     extern __shared__ cd smem[];
-    const int CB = d.cb;
+    const int CB = a.cb;
     const int c = threadIdx.x % CB, t = threadIdx.x / CB;
     cd* lds = smem + c * lds_team<N>();
-    // One-dimensional grid of (member, column block, share) in that order,
-    // share fastest.  The hardware hands workgroups to the XCDs round robin by
-    // id; each XCD is given a contiguous run of that order instead, so that the
-    // column blocks of one 128-byte line and the shares of one column meet in
-    // one L2 rather than fetching and writing the line from several.
-    const unsigned wg = xcd_order(blockIdx.x, gridDim.x);
-    const int zs = (int)(wg % (unsigned)a.split);   // share of the derived fields
-    const unsigned cbk = wg / (unsigned)a.split;
-    const unsigned nblk = (unsigned)(d.KXP / CB);
-    const int b = (int)(cbk / nblk);
-    const bool writer = zs == 0;               // the share that writes the compact outputs
-    const int kx0 = (int)(cbk % nblk) * CB;    // uniform first column of the block
-    const int kx = kx0 + c;
-    constexpr int K = band<N>(), KXP = kx_pad<N>(), KY = 2 * K + 1;
-    const bool colok = kx <= K;
-    // uniform bases (scalar registers) + 32-bit lane offsets
-    const size_t ymem = (size_t)b * N * KXP + kx0;
-    const size_t cmem = (size_t)b * KY * KXP + kx0;
-    const unsigned ylane = (unsigned)c;         // + y * KXP
-    const double* __restrict__ ik2t = a.invk2 + kx0;
-    const double dkx = (double)kx;
-    const double ex = a.ex2[kx];
-    const double h = a.h;
-    auto yoff = [&](int m) { return ylane + (unsigned)(t + T * m) * (unsigned)KXP; };
-    // compact row of slot m, -1 off the band (gap slots fold to -1 at compile time)
-    auto rowof = [&](int m) { return (slot_in_band<N, V>(m) && colok) ? band_row(t + T * m, N, K, KY) : -1; };
-    auto inS = [&](int r) { return r >= 0 && !(kx == 0 && r == 0); };
-    auto cidx = [&](int r) { return (unsigned)c + (unsigned)r * (unsigned)KXP; };
-
-    // ---- issue every global load first: input column(s) and compact operands.
-    // Loads are unconditional at in-bounds addresses (padding columns kx < KXP,
-    // compact row 0 for rows off the band) and their results selected, so no
-    // load sits in a branch.
-    cd v0[E];          // first input column
-    cd v1[E];          // second input column (adjoint)
-    cd s0[E], s1[E];   // compact operands: (omega_n, acc) forward, (lambda, omega-bar) adjoint
-    if constexpr (MODE != COL_FROM_STATE) {
-        const cd* __restrict__ src = a.yin[0] + ymem;
+    PA_COL_SETUP(N)
+    auto in_band = [&](int m, int t_) {
+        return slot_in_band<N, V>(m) && colok && (t_ + T * m <= K || t_ + T * m >= N - K);
+    };
+    auto row_of = [&](int m, int t_) { return in_band(m, t_) ? (t_ + T * m <= K ? t_ + T * m : t_ + T * m - N + KY) : 0; };
+    auto cidx = [&](int m, int t_) { return (unsigned)c + (unsigned)row_of(m, t_) * (unsigned)KXP; };
+    auto ky_of = [&](int m, int t_) { return t_ + T * m <= K ? t_ + T * m : t_ + T * m - N; };
+    auto load = [&](cd* v, const cd* yin) {
+        const cd* __restrict__ src = yin + ymem;
 #pragma unroll
         for (int m = 0; m < E; ++m) {
-            const cd x = ldc(src, yoff(m));
-            v0[m] = colok ? x : czero();
-        }
-    }
-    if constexpr (ADJ || MODE == COL_FIRST_GUESS) {
-        const cd* __restrict__ src = a.yin[1] + ymem;
-#pragma unroll
-        for (int m = 0; m < E; ++m) {
-            const cd x = ldc(src, yoff(m));
-            v1[m] = colok ? x : czero();
-        }
-    }
-    // compact operands; the adjoint modes issue them after their first input
-    // transform, which keeps two input columns, the accumulator and these
-    // operands from being live at once (the registers set the occupancy)
-    const bool need1 = (FWD_STAGE && MODE != COL_A) || (ADJ && MODE != COL_ADJ_C && MODE != COL_ADJ_SRC);
-    const bool need0 = !(ADJ && (STAGE_N || MODE == COL_ADJ_SRC));
-    auto load_compact = [&](bool do0, bool do1) {
-        const cd* __restrict__ p0 = FWD_STAGE ? a.omega + cmem : ADJ ? a.lam + cmem : a.state_in + cmem;
-        const cd* __restrict__ p1 = FWD_STAGE ? a.acc + cmem : (ADJ && MODE != COL_ADJ_SRC) ? a.omb + cmem : nullptr;
-#pragma unroll
-        for (int m = 0; m < E; ++m) {
-            if (do0) s0[m] = czero();
-            if (do1) s1[m] = czero();
-            if (!slot_in_band<N, V>(m)) continue;
-            const int r = rowof(m);
-            const unsigned ci = cidx(r >= 0 ? r : 0);
-            if (do0 && need0) {
-                const cd x = ldc(p0, ci);
-                s0[m] = r >= 0 ? x : czero();
-            }
-            if (do1 && need1) {
-                const cd x = ldc(p1, ci);
-                s1[m] = r >= 0 ? x : czero();
-            }
+            const cd x = ldc(src, yoff(m, t));
+            v[m] = colok ? x : czero();
         }
     };
-    if constexpr (FWD_STAGE || MODE == COL_FROM_STATE) load_compact(true, true);
+    // inputs first, unconditional at in-bounds addresses (as in col_twin_kernel)
+    cd v0[E], v1[E];
+    if constexpr (MODE != COL_FROM_STATE) load(v0, a.yin[0]);
+    if constexpr (MT::PAIR_IN) load(v1, a.yin[1]);
+    const ColPtrs q = col_ptrs<MODE>(a, cmem, b, kx0, kx);
+    cd s0[E], s1[E];
+    auto load_compact = [&]() {
+        const int tc = opaque(t);
+#pragma unroll
+        for (int m = 0; m < E; ++m) {
+            if (!slot_in_band<N, V>(m)) continue;
+            if constexpr (MT::NEED0) s0[m] = ldc(q.p0, cidx(m, tc));
+            if constexpr (MT::NEED1) s1[m] = ldc(q.p1, cidx(m, tc));
+        }
+    };
+#pragma unroll
+    for (int m = 0; m < E; ++m) s0[m] = s1[m] = czero();
     const cd* twl = stage_twiddles<N, V>(smem + CB * lds_team<N>(), a.tw);
-
+    // a stage's compact operand is in flight during the second input transform; a stage
+    // with two issues them once the inputs are combined (held through a transform, or
+    // beside both transformed inputs, they spill under the three-wave cap)
+    constexpr bool BOTH = MT::NEED0 && MT::NEED1;
+    if constexpr (MODE != COL_FROM_STATE) fft<N, V, false>(v0, t, lds, twl);
+    if constexpr (!BOTH) load_compact();
+    if constexpr (MT::PAIR_IN) fft<N, V, false>(v1, t, lds, twl);
     cd w[E];   // spectral values handed to the output transforms
-
-    if constexpr (MODE <= COL_FILTER) {
-        fft<N, V, false>(v0, t, lds, twl);
-        cd* __restrict__ om = (writer && a.omega) ? (MODE == COL_D && a.omega_out ? a.omega_out : a.omega) + cmem
-                                                  : nullptr;
-        cd* __restrict__ ac = (writer && a.acc) ? a.acc + cmem : nullptr;
-        cd* __restrict__ ck = (writer && a.ckpt) ? a.ckpt + cmem : nullptr;
+    const int tp = opaque(t);
 #pragma unroll
-        for (int m = 0; m < E; ++m) {
-            const int r = rowof(m);
-            if (r < 0) { w[m] = czero(); continue; }
-            const unsigned ci = cidx(r);
-            const bool ins = inS(r);
-            if constexpr (MODE == COL_INIT) {
-                const cd s = ins ? v0[m] : czero();
-                if (om) stc(om, ci, s);
-                if (ck) stc(ck, ci, s);
-                w[m] = s;
-            } else if constexpr (MODE == COL_FILTER) {
-                const size_t mi = (a.mult_per_member ? (size_t)b * KY * KXP : 0) + (size_t)r * KXP + kx;
-                w[m] = ins ? cscale(v0[m], a.mult[mi]) : czero();
-            } else {
-                const int ky = (r <= K) ? r : r - KY;
-                cd nl = ins ? mk(-v0[m].x, -v0[m].y) : czero();
-                if (a.nf > 0 && kx == 0 && (ky == a.nf || ky == -a.nf)) nl.x += a.forcing;
-                const double e2 = ex * a.ey2[r];
-                const double e1 = e2 * e2;
-                const cd wn = s0[m];
-                if constexpr (MODE == COL_A) {
-                    if (ac) stc(ac, ci, cscale(nl, e1));
-                    w[m] = cscale(mk(wn.x + 0.5 * h * nl.x, wn.y + 0.5 * h * nl.y), e2);
-                } else if constexpr (MODE == COL_B) {
-                    const cd q = s1[m];
-                    if (ac) stc(ac, ci, mk(q.x + 2.0 * e2 * nl.x, q.y + 2.0 * e2 * nl.y));
-                    w[m] = mk(e2 * wn.x + 0.5 * h * nl.x, e2 * wn.y + 0.5 * h * nl.y);
-                } else if constexpr (MODE == COL_C) {
-                    const cd q = s1[m];
-                    if (ac) stc(ac, ci, mk(q.x + 2.0 * e2 * nl.x, q.y + 2.0 * e2 * nl.y));
-                    w[m] = mk(e1 * wn.x + h * e2 * nl.x, e1 * wn.y + h * e2 * nl.y);
-                } else {   // COL_D
-                    const cd q = s1[m];
-                    const double h6 = h / 6.0;
-                    const cd s = mk(e1 * wn.x + h6 * (q.x + nl.x), e1 * wn.y + h6 * (q.y + nl.y));
-                    if (om) stc(om, ci, s);
-                    if (ck) stc(ck, ci, s);
-                    w[m] = s;
-                }
-            }
-        }
-    } else if constexpr (MODE == COL_FIRST_GUESS) {
-        // vorticity of the low-passed probe velocity: i kx v_hat - i ky u_hat on S
-        fft<N, V, false>(v0, t, lds, twl);
-        fft<N, V, false>(v1, t, lds, twl);
-#pragma unroll
-        for (int m = 0; m < E; ++m) {
-            const int r = rowof(m);
-            const int ky = (r <= K) ? r : r - KY;
-            const bool keep = inS(r) && kx <= a.lowpass && ky <= a.lowpass && -ky <= a.lowpass;
-            w[m] = keep ? mk(-dkx * v1[m].y + (double)ky * v0[m].y, dkx * v1[m].x - (double)ky * v0[m].x) : czero();
-        }
-    } else if constexpr (MODE == COL_FROM_STATE) {
-        cd* __restrict__ om = (writer && a.omega) ? a.omega + cmem : nullptr;
-#pragma unroll
-        for (int m = 0; m < E; ++m) {
-            const int r = rowof(m);
-            if (r < 0) { w[m] = czero(); continue; }
-            const cd s = inS(r) ? s0[m] : czero();
-            if (om) stc(om, cidx(r), s);
-            w[m] = s;
-        }
-    } else {
-        // adjoint: wbar = 1_S sum_p mult_p F_y(yin[p]), mult_p selected by inmul[p]
-        auto accumulate = [&](cd* v, int mk_) {
-#pragma unroll
-            for (int m = 0; m < E; ++m) {
-                const int r = rowof(m);
-                if (!inS(r)) continue;
-                const double ky = (double)((r <= K) ? r : r - KY);
-                const double ik2 = ik2t[cidx(r)];
-                if (mk_ == IN_PAIRP) {          // v (1/|k|^2 - i) / 2
-                    w[m].x += 0.5 * (ik2 * v[m].x + v[m].y);
-                    w[m].y += 0.5 * (ik2 * v[m].y - v[m].x);
-                } else if (mk_ == IN_PAIRQ) {   // v (1/|k|^2 + i) / 2
-                    w[m].x += 0.5 * (ik2 * v[m].x - v[m].y);
-                    w[m].y += 0.5 * (ik2 * v[m].y + v[m].x);
-                } else {
-                    const double f = (mk_ == IN_IKY_INVK2) ? ky * ik2 : -dkx * ik2;   // i f v
-                    w[m].x -= f * v[m].y;
-                    w[m].y += f * v[m].x;
-                }
-            }
-        };
-#pragma unroll
-        for (int m = 0; m < E; ++m) w[m] = czero();
-        fft<N, V, false>(v0, t, lds, twl);
-        accumulate(v0, a.inmul[0]);
-        // compact operands in flight during the second input transform: a
-        // stage's only one, or of two (B and A) lambda, up to 256 points; from
-        // 512 points the pair is issued after it (lambda live through the
-        // transform spills there under the three-wave cap)
-        const bool both = need0 && need1;
-        if (!both || N <= 256) load_compact(true, !both);
-        fft<N, V, false>(v1, t, lds, twl);
-        accumulate(v1, a.inmul[1]);
-        if (both) load_compact(N > 256, true);
-        // observation sources enter at stage n of an observed step only (two more inputs)
-        if constexpr (MODE == COL_ADJ_NSRC)
-        for (int p = 2; p < a.nin; ++p) {
-            const cd* __restrict__ src = a.yin[p] + ymem;
-#pragma unroll
-            for (int m = 0; m < E; ++m) {
-                const cd x = ldc(src, yoff(m));
-                v0[m] = colok ? x : czero();
-            }
-            fft<N, V, false>(v0, t, lds, twl);
-            accumulate(v0, a.inmul[p]);
-        }
-        const double sc = a.scale ? a.scale[b] : 1.0;
-        cd* __restrict__ lm_p = writer ? a.lam + cmem : nullptr;
-        cd* __restrict__ ob_p = (writer && a.omb) ? a.omb + cmem : nullptr;
-#pragma unroll
-        for (int m = 0; m < E; ++m) {
-            const int r = rowof(m);
-            if (r < 0) { w[m] = czero(); continue; }
-            const unsigned ci = cidx(r);
-            const cd wb = w[m];   // zero off the band by construction
-            const double e2 = ex * a.ey2[r];
-            const double e1 = e2 * e2;
-            if constexpr (MODE == COL_ADJ_C) {
-                const cd lm = s0[m];
-                if (ob_p) stc(ob_p, ci, mk(e1 * (lm.x + wb.x), e1 * (lm.y + wb.y)));
-                w[m] = mk((h / 3.0) * e2 * lm.x + h * e2 * wb.x, (h / 3.0) * e2 * lm.y + h * e2 * wb.y);
-            } else if constexpr (MODE == COL_ADJ_B) {
-                const cd lm = s0[m], ob = s1[m];
-                if (ob_p) stc(ob_p, ci, mk(ob.x + e2 * wb.x, ob.y + e2 * wb.y));
-                w[m] = mk((h / 3.0) * e2 * lm.x + 0.5 * h * wb.x, (h / 3.0) * e2 * lm.y + 0.5 * h * wb.y);
-            } else if constexpr (MODE == COL_ADJ_A) {
-                const cd lm = s0[m], ob = s1[m];
-                if (ob_p) stc(ob_p, ci, mk(ob.x + e2 * wb.x, ob.y + e2 * wb.y));
-                w[m] = mk((h / 6.0) * e1 * lm.x + 0.5 * h * e2 * wb.x, (h / 6.0) * e1 * lm.y + 0.5 * h * e2 * wb.y);
-            } else {   // stage n (with or without sources), COL_ADJ_SRC
-                cd ln = wb;
-                if constexpr (STAGE_N) {
-                    const cd ob = s1[m];
-                    ln = mk(ob.x + wb.x, ob.y + wb.y);
-                }
-                if (lm_p) stc(lm_p, ci, ln);
-                w[m] = a.final_out ? cscale(ln, sc) : cscale(ln, h / 6.0);
-            }
-        }
+    for (int m = 0; m < E; ++m) {
+        const bool ins = in_band(m, tp) && !(kx == 0 && row_of(m, tp) == 0);
+        w[m] = MODE != COL_FROM_STATE && slot_in_band<N, V>(m)
+                   ? col_pair_value<MODE>(a, q, ins, cidx(m, tp), kx, ky_of(m, tp), v0[m], MT::PAIR_IN ? v1[m] : czero())
+                   : czero();
     }
-
-    // derived fields: 1_S * multiplier * w / N^2, inverse transform along y; a
-    // packed pair half A +- i B is formed from the two multipliers before the
-    // transform (the transform is linear)
-    const double inv_n2 = 1.0 / ((double)N * (double)N);
-    for (int o = zs; o < a.nout; o += a.split) {
-        const int f = a.fields[o];
+    if constexpr (BOTH) {
+        asm volatile("" ::: "memory");
+        load_compact();
+    }
+    const int tu = opaque(t);
+#pragma unroll
+    for (int m = 0; m < E; ++m) {
+        if (!slot_in_band<N, V>(m)) continue;
+        const bool on = in_band(m, tu);
+        const int r = row_of(m, tu);
+        const bool ins = on && !(kx == 0 && r == 0);
+        w[m] = col_mode_update<N, MODE>(a, q, on, ins, cidx(m, tu), b, kx, r, ky_of(m, tu), w[m], s0[m], s1[m]);
+    }
+    for (int o = 0; o < a.nout; ++o) {
         cd v[E];
+        const int to = opaque(t);
 #pragma unroll
         for (int m = 0; m < E; ++m) {
-            const int r = rowof(m);
-            if (!inS(r)) { v[m] = czero(); continue; }
-            const double ky = (double)((r <= K) ? r : r - KY);
-            const cd s = cscale(w[m], inv_n2);
-            const double ik2 = ik2t[(unsigned)c + (unsigned)r * (unsigned)KXP];
-            if (f == F_OMEGA) {
-                v[m] = s;
-            } else {
-                cd A, Bf;
-                if (f == F_UP || f == F_UQ) {          // (u, w_x) = (i ky / k^2, i kx) s
-                    A = cscale(mul_i(s), ky * ik2);
-                    Bf = cscale(mul_i(s), dkx);
-                } else if (f == F_VP || f == F_VQ) {   // (v, w_y) = (-i kx / k^2, i ky) s
-                    A = cscale(mul_i(s), -dkx * ik2);
-                    Bf = cscale(mul_i(s), ky);
-                } else {                               // (Lam_x, Lam_y) = (i kx, i ky) s
-                    A = cscale(mul_i(s), dkx);
-                    Bf = cscale(mul_i(s), ky);
-                }
-                const bool plus = f == F_UP || f == F_VP || f == F_LP;
-                v[m] = plus ? mk(A.x - Bf.y, A.y + Bf.x) : mk(A.x + Bf.y, A.y - Bf.x);
-            }
+            const bool ins = in_band(m, to) && !(kx == 0 && row_of(m, to) == 0);
+            v[m] = slot_in_band<N, V>(m)
+                       ? col_field<N>(a.fields[0], o == 1, ins, q, cidx(m, to), kx, ky_of(m, to), w[m])
+                       : czero();
         }
         fft<N, V, true>(v, t, lds, twl);
         if (colok) {
             cd* __restrict__ out = a.yout[o] + ymem;
 #pragma unroll
-            for (int m = 0; m < E; ++m) stc(out, yoff(m), v[m]);
+            for (int m = 0; m < E; ++m) stc(out, yoff(m, to), v[m]);
         }
     }
 }
@@ -851,14 +896,6 @@ struct Pipe {
 
 __device__ __forceinline__ void vm_wait() { asm volatile("s_waitcnt vmcnt(0)" ::: "memory"); }
 
-// Returns v unchanged, opaquely: index arithmetic derived from it inside a
-// loop is not hoisted out of the loop (where its results would occupy
-// registers for the loop's whole lifetime) but recomputed per iteration.
-__device__ __forceinline__ int opaque(int v) {
-    asm volatile("" : "+v"(v));
-    return v;
-}
-
 // Global->LDS loads of one row group of NF fields into the wave's stage
 // buffer (lane l of a load lands at the load's LDS base + l).  The LDS base
 // of these loads goes to M0 and must be uniform over the wavefront: the
@@ -867,7 +904,7 @@ __device__ __forceinline__ int opaque(int v) {
 // never merges a masked load with a load of another LDS base (the merged
 // instruction would take one lane's base for every lane).
 template <int N, int NF>
-__device__ __forceinline__ void pipe_fetch(cd* stage, const cd* const (&src)[NF], size_t off, int lane) {
+__device__ __forceinline__ void pipe_fetch(cd* stage, const cd* (&src)[NF], size_t off, int lane) {
     using P = Pipe<N>;
     constexpr int FULL = P::SPAN / 64, TAIL = P::SPAN % 64;
 #pragma unroll
@@ -888,10 +925,12 @@ __device__ __forceinline__ void pipe_fetch(cd* stage, const cd* const (&src)[NF]
     }
 }
 
-template <int N>
-__global__ void __launch_bounds__(256) row_nl_pipe_kernel(Dims d, RowArgs a, int n_groups) {
+// Both products share the loop: ADJ multiplies by the cotangent pair, else the
+// velocity is squared.
+template <int N, bool ADJ>
+__device__ __forceinline__ void row_pipe_body(const RowArgs& a, int n_groups) {
     using P = Pipe<N>;
-    constexpr int V = PIPE_V, T = P::T, E = P::E, KXP = P::KXP, NF = 4, WL_ = true;
+    constexpr int V = PIPE_V, T = P::T, E = P::E, KXP = P::KXP, NF = ADJ ? 4 : 2, WL_ = true;
     extern __shared__ cd smem[];
     const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63, team = lane / T, t0 = lane % T;
     const int wpg = blockDim.x >> 6;
@@ -901,70 +940,20 @@ __global__ void __launch_bounds__(256) row_nl_pipe_kernel(Dims d, RowArgs a, int
     row_twiddles<N, V>(tr, t0, a.tw, smem + wpg * P::template wave_lds<NF>());
     const int nw = gridDim.x * wpg;
     int g = blockIdx.x * wpg + wave;
-    const cd* const src[NF] = {a.yin[0], a.yin[1], a.yin[2], a.yin[3]};   // packed (u, w_x), (v, w_y)
-    const cd* const row = stage + team * KXP;
-    cd z1[E], z2[E];
-    if (g < n_groups) {
-        pipe_fetch<N, NF>(stage, src, P::offset(g), lane);
-        vm_wait();
-        packed_load<N, V>(z1, row, row + P::SPAN, t0);
-        wave_lds_sync();
-        packed_load<N, V>(z2, row + 2 * P::SPAN, row + 3 * P::SPAN, t0);
-        wave_lds_sync();
-        if (g + nw < n_groups) pipe_fetch<N, NF>(stage, src, P::offset(g + nw), lane);
-    }
-    for (; g < n_groups; g += nw) {
-        const int t = opaque(t0);
-        row_fft<N, V, true, WL_>(z1, t, lds, tr);
-        row_fft<N, V, true, WL_>(z2, t, lds, tr);
-        cd z[E];
+    const cd* src[NF];   // packed (u, v), then packed (b, a)
 #pragma unroll
-        for (int m = 0; m < E; ++m) z[m] = mk(z1[m].x * z1[m].y + z2[m].x * z2[m].y, 0.0);
-        row_fft<N, V, false, WL_>(z, t, lds, tr);
-        const int gn = g + nw;
-        if (gn < n_groups) {
-            vm_wait();
-            packed_load<N, V>(z1, row, row + P::SPAN, t);
-            wave_lds_sync();
-            packed_load<N, V>(z2, row + 2 * P::SPAN, row + 3 * P::SPAN, t);
-            wave_lds_sync();
-            if (gn + nw < n_groups) pipe_fetch<N, NF>(stage, src, P::offset(gn + nw), lane);
-        }
-        cd* o = a.yout[0] + P::offset(g) + team * KXP;
-#pragma unroll
-        for (int m = 0; m < E; ++m) {
-            const int k = t + T * m;
-            if (slot_low<N, V>(m) && k <= band<N>()) o[k] = z[m];
-        }
-    }
-}
-
-template <int N>
-__global__ void __launch_bounds__(256) row_adj_pipe_kernel(Dims d, RowArgs a, int n_groups) {
-    using P = Pipe<N>;
-    constexpr int V = PIPE_V, T = P::T, E = P::E, KXP = P::KXP, NF = 6, WL_ = true;
-    extern __shared__ cd smem[];
-    const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63, team = lane / T, t0 = lane % T;
-    const int wpg = blockDim.x >> 6;
-    cd* const stage = smem + wave * P::template wave_lds<NF>();
-    cd* const lds = stage + NF * P::SPAN + team * lds_team<N>();
-    RowTw<N, V> tr;
-    row_twiddles<N, V>(tr, t0, a.tw, smem + wpg * P::template wave_lds<NF>());
-    const int nw = gridDim.x * wpg;
-    int g = blockIdx.x * wpg + wave;
-    // packed (Lam_x, Lam_y), (u, w_x), (v, w_y)
-    const cd* const src[NF] = {a.yin[4], a.yin[5], a.yin[0], a.yin[1], a.yin[2], a.yin[3]};
+    for (int f = 0; f < NF; ++f) src[f] = a.yin[f];
     const cd* const row = stage + team * KXP;
-    cd L[E], z1[E], z2[E];
-    // one signal pair at a time: LDS latency is short, and the raw values of
-    // all three pairs in flight at once would double the registers held
+    cd w[E], z[E];
+    // one signal at a time: LDS latency is short, and the raw values of both
+    // in flight at once would double the registers held
     auto read_inputs = [&](int t) {
-        packed_load<N, V>(L, row, row + P::SPAN, t);
+        packed_load<N, V>(z, row, row + P::SPAN, t);
         wave_lds_sync();
-        packed_load<N, V>(z1, row + 2 * P::SPAN, row + 3 * P::SPAN, t);
-        wave_lds_sync();
-        packed_load<N, V>(z2, row + 4 * P::SPAN, row + 5 * P::SPAN, t);
-        wave_lds_sync();
+        if constexpr (ADJ) {
+            packed_load<N, V>(w, row + 2 * P::SPAN, row + 3 * P::SPAN, t);
+            wave_lds_sync();
+        }
     };
     if (g < n_groups) {
         pipe_fetch<N, NF>(stage, src, P::offset(g), lane);
@@ -974,14 +963,12 @@ __global__ void __launch_bounds__(256) row_adj_pipe_kernel(Dims d, RowArgs a, in
     }
     for (; g < n_groups; g += nw) {
         const int t = opaque(t0);
-        row_fft<N, V, true, WL_>(L, t, lds, tr);
-        row_fft<N, V, true, WL_>(z1, t, lds, tr);
-        row_fft<N, V, true, WL_>(z2, t, lds, tr);
-        cd G[E];
+        cd q[E];
+        if constexpr (ADJ) row_fft<N, V, true, WL_>(w, t, lds, tr);
+        row_fft<N, V, true, WL_>(z, t, lds, tr);
 #pragma unroll
-        for (int m = 0; m < E; ++m)
-            G[m] = mk(z1[m].y * L[m].y - z2[m].y * L[m].x, z1[m].x * L[m].x + z2[m].x * L[m].y);
-        row_fft<N, V, false, WL_>(G, t, lds, tr);
+        for (int m = 0; m < E; ++m) q[m] = ADJ ? cmulc(w[m], z[m]) : csq(z[m]);
+        row_fft<N, V, false, WL_>(q, t, lds, tr);
         const int gn = g + nw;
         if (gn < n_groups) {
             vm_wait();
@@ -989,8 +976,18 @@ __global__ void __launch_bounds__(256) row_adj_pipe_kernel(Dims d, RowArgs a, in
             if (gn + nw < n_groups) pipe_fetch<N, NF>(stage, src, P::offset(gn + nw), lane);
         }
         const size_t ro = P::offset(g) + team * KXP;
-        pair_store<N, V>(G, t, a.yout[0] + ro, a.yout[1] + ro);
+        pair_store<N, V>(q, t, a.yout[0] + ro, a.yout[1] + ro);
     }
+}
+
+template <int N>
+__global__ void __launch_bounds__(256) row_sq_pipe_kernel(Dims d, RowArgs a, int n_groups) {
+    row_pipe_body<N, false>(a, n_groups);
+}
+
+template <int N>
+__global__ void __launch_bounds__(256) row_mul_pipe_kernel(Dims d, RowArgs a, int n_groups) {
+    row_pipe_body<N, true>(a, n_groups);
 }
 
 // Persistent grid: as many workgroups as can be resident (occupancy query,
@@ -1065,70 +1062,67 @@ hipError_t Launch<N>::row_c2r(const Dims& d, const cd* in, double* out, const cd
     PA_ROW_LAUNCH(d.var, d.tpb, row_c2r_kernel, N / 2, d, in, out, tw);
 }
 template <int N>
-hipError_t Launch<N>::row_nl(const Dims& d, const RowArgs& a, hipStream_t s) {
-    // variant 3 without a pipelined kernel for N falls back to the variant-2 kernel launched with
-    // one team per row below, which must then be the one-row kernel
-    static_assert(Pipe<N>::OK || !nl_pairs<N>(), "the variant-3 fallback would launch the two-row kernel");
+hipError_t Launch<N>::row_sq(const Dims& d, const RowArgs& a, hipStream_t s) {
     if constexpr (Pipe<N>::OK)
-        if (d.var == 3) return pipe_launch<N, 4>(row_nl_pipe_kernel<N>, d.tpb, d, a, s);
-    if (d.var == 2 && nl_pairs<N>()) PA_ROW_LAUNCH(d.var, d.tpb, row_nl_kernel, N / 2, d, a);   // two rows per team
-    PA_ROW_LAUNCH(d.var, d.tpb, row_nl_kernel, N, d, a);
+        if (d.var == 3) return pipe_launch<N, 2>(row_sq_pipe_kernel<N>, d.tpb, d, a, s);
+    PA_ROW_LAUNCH(d.var, d.tpb, row_sq_kernel, N, d, a);
 }
 template <int N>
 hipError_t Launch<N>::row_obs(const Dims& d, const RowArgs& a, hipStream_t s) {
     PA_ROW_LAUNCH(d.var, d.tpb, row_obs_kernel, a.obs.M, d, a);
 }
 template <int N>
-hipError_t Launch<N>::row_adj(const Dims& d, const RowArgs& a, hipStream_t s) {
+hipError_t Launch<N>::row_mul(const Dims& d, const RowArgs& a, hipStream_t s) {
     if constexpr (Pipe<N>::OK)
-        if (d.avar == 3) return pipe_launch<N, 6>(row_adj_pipe_kernel<N>, d.atpb, d, a, s);
-    PA_ROW_LAUNCH(d.avar, d.atpb, row_adj_kernel, N, d, a);
+        if (d.avar == 3) return pipe_launch<N, 4>(row_mul_pipe_kernel<N>, d.atpb, d, a, s);
+    PA_ROW_LAUNCH(d.avar, d.atpb, row_mul_kernel, N, d, a);
 }
 template <int N>
-hipError_t Launch<N>::row_src(const Dims& d, const RowArgs& a, int impulse, hipStream_t s) {
-    PA_ROW_LAUNCH(d.avar, d.atpb, row_src_kernel, N, d, a, impulse);
+hipError_t Launch<N>::row_src(const Dims& d, const RowArgs& a, int mode, hipStream_t s) {
+    if (mode == SRC_ADD) PA_ROW_LAUNCH(d.avar, d.atpb, row_src_add, a.obs.M, d, a);
+    if (mode == SRC_IMPULSE) PA_ROW_LAUNCH(d.avar, d.atpb, row_src_impulse, N, d, a);
+    PA_ROW_LAUNCH(d.avar, d.atpb, row_src_write, N, d, a);
 }
 
-// Workgroups that share out one column's derived fields.  A launch whose
-// columns cannot keep two wavefronts per SIMD busy (small batches of large
-// grids: 1024^2 has 344 columns) is latency-bound by each column's chain of
-// transforms; each share recomputes the input transform(s) and combine and
-// runs its part of the output transforms, so the chain is shorter and more
-// wavefronts are in flight.  The derived fields are the same whatever the
-// split (each share runs the same operations), so results do not depend on it.
-// d.csplit > 0 fixes the number of shares (capped at the output count);
-// 0 picks 1, 2 or 4 from the wavefronts the launch has without a split.
+template <class Kern>
+hipError_t col_launch(Kern kernel, const Dims& d, const ColArgs& a, unsigned threads, size_t lds, hipStream_t s) {
+    // Workgroups beyond 64 KiB of LDS: the kernel's dynamic LDS limit is raised
+    // to the device's once per instantiation.
+    if (lds > 65536) {
+        static const hipError_t raised = hipFuncSetAttribute(
+            reinterpret_cast<const void*>(kernel), hipFuncAttributeMaxDynamicSharedMemorySize, d.lds_max);
+        if (raised != hipSuccess) return raised;
+    }
+    launch_kernel(kernel, dim3((unsigned)(d.KXP / a.cb) * (unsigned)d.B), dim3(threads), lds, s, d, a);
+    return hipGetLastError();
+}
+
+// Whether a launch runs its pairs on twin teams (see col_twin_kernel).  The
+// tile's col_split fixes it (1: no, 2 or 4: yes); 0 decides by the wavefronts
+// that one team per column would give the launch.  Below two per SIMD twins are
+// faster (32 x 256^2 at 1.4: 18.3 against 22.6 us; 8 x 512^2 at 1.4: 21.9
+// against 25.6), above one team is (64 x 256^2 at 2.8: 28.9 against 31.0;
+// 4 x 1024^2 at 2.7: 41.3 against 54).
 template <int N, int V>
-int col_split(const Dims& d, int nout) {
-    if (nout <= 1) return 1;
-    if (d.csplit > 0) return std::min(d.csplit, nout);
+bool col_twins(const Dims& d) {
+    if (d.csplit > 0) return d.csplit > 1;
     const long waves = (long)(d.KXP / d.cb) * d.B * ((d.cb * Plan<N, V>::T + 63) / 64);
-    const long target = 8L * std::max(d.cus, 1);   // two wavefronts per SIMD
-    int split = 1;
-    while (split < nout && waves * split < target) split *= 2;
-    return std::min(split, nout);
+    return waves < 8L * std::max(d.cus, 1);   // two wavefronts per SIMD
 }
 
 template <int N, int V, int MODE>
 hipError_t col_mode(const Dims& d, const ColArgs& a, hipStream_t s) {
+    constexpr int T = Plan<N, V>::T;
     ColArgs ak = a;
-    ak.split = col_split<N, V>(d, a.nout);
-    const dim3 grid((unsigned)(d.KXP / d.cb) * (unsigned)d.B * (unsigned)ak.split);
-    const dim3 block((unsigned)(d.cb * Plan<N, V>::T));
-    const size_t lds = ((size_t)d.cb * lds_team<N>() + N) * sizeof(cd);
-    // Column blocks wider than 64 KiB of LDS (1024-point columns, four or more
-    // per workgroup): the kernel's dynamic LDS limit is raised to the
-    // device's once per instantiation.  Such a block fills a CU alone, so it
-    // pays only where a launch has few columns (one 1024^2 member: 25.1
-    // against 26.8 us per forward stage); the autotuner decides.
-    if (lds > 65536) {
-        static const hipError_t raised = hipFuncSetAttribute(
-            reinterpret_cast<const void*>(&col_kernel<N, V, MODE>), hipFuncAttributeMaxDynamicSharedMemorySize,
-            d.lds_max);
-        if (raised != hipSuccess) return raised;
+    ak.cb = d.cb;
+    if (col_twins<N, V>(d)) {
+        // at least the columns that fill 16 lanes per twin, at most what threads and LDS allow
+        while (N >= 64 && ak.cb * T < 16) ak.cb *= 2;
+        while (ak.cb > 1 && (2 * ak.cb * T > twin_threads<N, V>() || col_lds<N>(2 * ak.cb) > (size_t)d.lds_max))
+            ak.cb /= 2;
+        return col_launch(col_twin_kernel<N, V, MODE>, d, ak, (unsigned)(2 * ak.cb * T), col_lds<N>(2 * ak.cb), s);
     }
-    launch_kernel(col_kernel<N, V, MODE>, grid, block, lds, s, d, ak);
-    return hipGetLastError();
+    return col_launch(col_pass_kernel<N, V, MODE>, d, ak, (unsigned)(ak.cb * T), col_lds<N>(ak.cb), s);
 }
 
 template <int N, int V>
@@ -1145,7 +1139,6 @@ hipError_t col_variant(const Dims& d, int mode, const ColArgs& a, hipStream_t s)
         case COL_ADJ_B: return col_mode<N, V, COL_ADJ_B>(d, a, s);
         case COL_ADJ_A: return col_mode<N, V, COL_ADJ_A>(d, a, s);
         case COL_ADJ_N: return col_mode<N, V, COL_ADJ_N>(d, a, s);
-        case COL_ADJ_NSRC: return col_mode<N, V, COL_ADJ_NSRC>(d, a, s);
         case COL_ADJ_SRC: return col_mode<N, V, COL_ADJ_SRC>(d, a, s);
         case COL_FIRST_GUESS: return col_mode<N, V, COL_FIRST_GUESS>(d, a, s);
         default: return hipErrorInvalidValue;

@@ -30,10 +30,19 @@ from .roofline import field_bytes, kernel_source_sha
 def kernel_rw_bytes(name, N):
     """Algorithmic (read, write) bytes per member of one dispatch of kernel `name`, or None."""
     Yb, Cb = field_bytes(N)
-    if name.startswith("row_nl"):
+    if name.startswith("row_sq"):
+        return 2 * Yb, 2 * Yb
+    if name.startswith("row_mul"):
+        return 4 * Yb, 2 * Yb
+    if name.startswith("row_nl"):      # kernels of the advective form, in earlier profiles
         return 4 * Yb, Yb
     if name.startswith("row_adj"):
         return 6 * Yb, 2 * Yb
+    m = re.match(r"col_pass_kernel<\d+, \d+, (\d+)>", name)
+    if m:
+        comp = {1: (1, 1), 2: (2, 1), 3: (2, 1), 4: (2, 1), 7: (1, 1), 8: (2, 1), 9: (2, 1), 10: (1, 1)}
+        mode = comp.get(int(m.group(1)))
+        return mode and (2 * Yb + mode[0] * Cb, 2 * Yb + mode[1] * Cb)
     m = re.match(r"col_kernel<\d+, \d+, (\d+)>", name)
     if not m:
         return None

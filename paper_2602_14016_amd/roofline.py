@@ -1,15 +1,20 @@
-"""Algorithmic byte model of the hot kernels and the HBM-traffic record.
+"""Byte models of the hot kernels and the HBM-traffic record.
 
 Kernel classes are those the library's launch timer knows (pa_profile_start):
 0 the right-hand-side row pass, 1 the forward-stage column pass, 2 the
 adjoint-product row pass, 3 the adjoint-stage column pass.
 
-Algorithmic bytes count what a kernel must move per member and launch, with
-every field read or written once: Yb is one field in the Y layout restricted
-to the retained band, N rows of Kc + 1 complex values; Cb is one compact
-spectral state, (2 Kc + 1) x (Kc + 1) complex values.  Padding columns and
-repeated reads are not counted, so achieved = algorithmic bytes / time is a
-lower bound on the bandwidth a kernel actually draws.
+kernel_bytes counts what a kernel must move per member and launch, with every
+field read or written once: Yb is one field in the Y layout restricted to the
+retained band, N rows of Kc + 1 complex values; Cb is one compact spectral
+state, (2 Kc + 1) x (Kc + 1) complex values.  Padding columns and repeated
+reads are not counted, so kernel_bytes / time is a lower bound on the
+bandwidth a kernel actually draws.
+
+algorithmic_bytes is the same count for the passes in advective form (u, v,
+w_x, w_y in physical space), which the kernels computed before they worked on
+velocities only.  It is the yardstick of the profiles taken on those kernels
+(row_nl_kernel, row_adj_kernel, col_kernel).
 """
 
 import hashlib
@@ -19,8 +24,8 @@ HERE = os.path.dirname(os.path.abspath(__file__))
 ROOT = os.path.dirname(HERE)
 HBM_PEAK_GBS = 8000.0   # MI355X HBM3E
 
-CLASS_NAMES = {0: "row_nl_kernel", 1: "col_kernel (forward stages)", 2: "row_adj_kernel",
-               3: "col_kernel (adjoint stages)"}
+CLASS_NAMES = {0: "row_sq_kernel", 1: "col_pass_kernel (forward stages)", 2: "row_mul_kernel",
+               3: "col_pass_kernel (adjoint stages)"}
 
 
 def field_bytes(N):
@@ -30,7 +35,7 @@ def field_bytes(N):
 
 
 def algorithmic_bytes(cls, N):
-    """Bytes per member of one launch of kernel class cls."""
+    """Bytes per member of one launch of class cls in the advective form."""
     Yb, Cb = field_bytes(N)
     return {0: 5 * Yb,                  # read U, V, Wx, Wy; write q
             1: 5 * Yb + 2.75 * Cb,      # read q; write U, V, Wx, Wy; state and accumulator (mean over stages A-D)
@@ -38,17 +43,13 @@ def algorithmic_bytes(cls, N):
             3: 4 * Yb + 2.5 * Cb}[cls]  # read the two products; write Lambda, Lambda_y; adjoint accumulators
 
 
-# per column-pass mode (col_kernel<N, V, MODE>): bytes per member
-def column_mode_bytes(mode, N):
+def kernel_bytes(cls, N):
+    """Bytes per member of one launch of kernel class cls: each input and output once."""
     Yb, Cb = field_bytes(N)
-    return {1: 5 * Yb + 2 * Cb,    # stage A: read q, omega; write acc, 4 fields
-            2: 5 * Yb + 3 * Cb,    # stage B: read q, omega, acc; write acc, 4 fields
-            3: 5 * Yb + 3 * Cb,    # stage C
-            4: 5 * Yb + 3 * Cb,    # stage D: read q, omega, acc; write omega, 4 fields
-            7: 4 * Yb + 2 * Cb,    # adjoint C: read 2 products, lambda; write omega-bar, 2 fields
-            8: 4 * Yb + 3 * Cb,    # adjoint B: read 2 products, lambda, omega-bar; write omega-bar, 2 fields
-            9: 4 * Yb + 3 * Cb,    # adjoint A
-            10: 4 * Yb + 2 * Cb}.get(mode)  # adjoint n: read 2 products, omega-bar; write lambda, 2 fields
+    return {0: 4 * Yb,                  # read the velocity pair; write the pair of products
+            1: 4 * Yb + 2.75 * Cb,      # read the products; write the velocity pair; state and accumulator
+            2: 6 * Yb,                  # read the velocity and cotangent pairs; write the products
+            3: 4 * Yb + 2.5 * Cb}[cls]  # read the products; write the cotangent pair; adjoint accumulators
 
 
 # the sources that define and instantiate the row and column kernels, and the
