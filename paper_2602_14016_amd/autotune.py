@@ -4,19 +4,21 @@ Knobs (pa_set_tiles), one set per pass: the register plan of the 1D
 transforms (variant 0: more elements per thread; 1: more threads per
 transform; 2: four elements per thread where the length allows; 3, row
 passes only: variant 2's plan in persistent wavefronts that prefetch their
-next rows into LDS) and the workgroup shape (rows per workgroup for the forward and the adjoint row
-passes, kx columns per workgroup for the column pass), and for the column
-pass the number of workgroups that share out each column's output transforms
-(0: chosen per launch from the wavefronts it has; 1, 2 or 4 fixed).  The three passes are
-separate kernels reading and writing fixed layouts, so each is tuned on its
-own: every candidate runs a short batched forward + adjoint solve of the
-solver's own shape while the library times that pass's launches with HIP
-events on the solver's stream (pa_profile_start).  Forward rows are scored by
-the right-hand-side row kernel, adjoint rows by the adjoint-product row
-kernel, and the column pass by its forward plus adjoint stage launches; for
-the column pass every (variant, block) pair is tried with each col_split (one
-team per column, or twin teams), since the best form depends on the block.  The best of each is applied and returned.  Results depend on the choice only through the
-rounding of the transforms (not at all on the column form).
+next rows into LDS), the workgroup shape (rows per workgroup for the forward
+and the adjoint row passes, kx columns per workgroup for the column pass) and
+for the column pass whether a column's two signals run on one team or on twin
+teams (0: chosen per launch from the wavefronts it has; 1: one; 2 or 4:
+twins).  The three passes are separate kernels reading and writing fixed
+layouts, so each is tuned on its own: every candidate runs a short batched
+forward + adjoint solve of the solver's own shape while the library times that
+pass's launches with HIP events on the solver's stream (pa_profile_start).
+Forward rows are scored by the right-hand-side row kernel, adjoint rows by the
+adjoint-product row kernel, and the column pass by its forward plus adjoint
+stage launches; for the column pass every (variant, block) pair is tried with
+each col_split, since the best form depends on the block.  The best of each is
+applied and returned.  Results depend on the choice only through the rounding
+of the transforms (not at all on the column form).  Grids up to 64^2 run their
+time loop in one kernel without these passes: their tiles are left as they are.
 """
 
 import time
@@ -75,6 +77,7 @@ def autotune(solver, omega0=None, n_steps=8, reps=2, verbose=False):
     for name, variants, vkey, bkey, classes in searches:
         splits = COL_SPLITS if name == "col" else (None,)
         best = None
+        kept = solver.get_tiles()
         for v in variants:
             for blk in BLOCKS:
                 try:
@@ -89,6 +92,8 @@ def autotune(solver, omega0=None, n_steps=8, reps=2, verbose=False):
                                   | ({} if sp is None else {"split": sp}))
                     if best is None or ms < best[0]:
                         best = (ms, v, blk, sp)
+        if best[0] == 0.0:   # the solve launches no such pass (grids up to 64^2): keep its tiles
+            best = (0.0, kept[vkey], kept[bkey], kept["col_split"] if splits != (None,) else None)
         chosen[vkey], chosen[bkey] = best[1], best[2]
         solver.set_tiles(**{vkey: best[1], bkey: best[2]})
         if best[3] is not None:

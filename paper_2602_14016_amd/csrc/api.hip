@@ -18,6 +18,7 @@
 
 #include "../../include/pa.h"
 #include "kernels.hpp"
+#include "small.hpp"
 
 using namespace pa;
 
@@ -150,7 +151,8 @@ struct WS {
     cd* acc;
     cd* lam;
     cd* omb;
-    cd* seg;            // segment stage fields, (4K+1) slots x 2 fields
+    cd* seg;            // segment stage fields, (4K+1) slots x 2 fields (up to 64^2: x one physical velocity)
+    cd* zf;             // up to 64^2: physical velocity of the current state
     cd* ckpt;           // internal checkpoints
     double* jpart;      // [B][n_obs][N]
     double* J;          // [B]
@@ -208,6 +210,13 @@ int n_segments(int n_steps, int K) { return n_steps <= 0 ? 0 : (int)(((int64_t)n
 bool plan_mode(const pa_ctx* c, int nseg) { return c->ckpt_slots > 0 && c->ckpt_slots <= nseg; }
 int ckpt_count(const pa_ctx* c, int nseg) { return plan_mode(c, nseg) ? c->ckpt_slots : nseg + 1; }
 
+// Complex values of one stage slot of the segment store: the packed velocity
+// in the Y layout, or up to 64^2 the physical one.
+size_t slot_values(const pa_ctx* c) {
+    const Dims& d = c->d;
+    return (size_t)d.B * d.N * (small_grid(d.N) ? d.N : 2 * d.KXP);
+}
+
 WS carve(const pa_ctx* c, int n_steps, int ckpt_every, int n_obs, int m, void* base) {
     const Dims& d = c->d;
     const size_t SY = (size_t)d.B * d.N * d.KXP;
@@ -229,7 +238,8 @@ WS carve(const pa_ctx* c, int n_steps, int ckpt_every, int n_obs, int m, void* b
     w.acc = cv.take<cd>(SC);
     w.lam = cv.take<cd>(SC);
     w.omb = cv.take<cd>(SC);
-    w.seg = n_steps > 0 ? cv.take<cd>((size_t)(4 * K + 1) * 2 * SY) : nullptr;
+    w.seg = n_steps > 0 ? cv.take<cd>((size_t)(4 * K + 1) * slot_values(c)) : nullptr;
+    w.zf = small_grid(d.N) ? cv.take<cd>(SP) : nullptr;
     w.ckpt = cv.take<cd>((size_t)ckpt_count(c, nseg) * SC);
     w.jpart = cv.take<double>((size_t)d.B * std::max(n_obs, 1) * d.N);
     w.J = cv.take<double>(d.B);
@@ -283,6 +293,9 @@ void seg_fields(const pa_ctx* c, const WS& w, int j, int s, cd* out[2]) {
     const size_t slot = (size_t)j * 4 + s;
     for (int f = 0; f < 2; ++f) out[f] = w.seg + (slot * 2 + f) * SY;
 }
+
+// up to 64^2: the physical velocity of segment slot (j, 0)
+cd* small_slot(const pa_ctx* c, const WS& w, int j) { return w.seg + (size_t)j * 4 * slot_values(c); }
 
 // ------------------------------------------------- checkpoint schedule --
 // Binomial checkpointing (Griewank 1992; Griewank & Walther 2000).  With the
@@ -681,14 +694,14 @@ void set_stage_fields(ColArgs& a, cd* const f[2]) {
 }
 
 // Transform physical omega0 to the band-limited state (P omega0), write
-// checkpoint slot 0 if given, and the stage-a fields to `fields`.
+// checkpoint slot 0 if given, and the stage-a fields to `fields` if given.
 pa_status start_state(pa_ctx* c, WS& w, const double* omega0, cd* ck0, cd* const fields[2]) {
     PA_HIP(launch_row_r2c(c->d, omega0, w.Y0, c->tw, c->stream));
     ColArgs a = col_base(c);
     a.yin[0] = w.Y0;
     a.omega = w.omega;
     a.ckpt = ck0;
-    set_stage_fields(a, fields);
+    if (fields) set_stage_fields(a, fields);
     PA_HIP(launch_col(c->d, COL_INIT, a, c->stream));
     return PA_OK;
 }
@@ -758,6 +771,140 @@ pa_status run_steps(pa_ctx* c, WS& w, int n0, int n1, int n_total, int K, bool s
     return PA_OK;
 }
 
+// ---- grids up to 64^2: runs of steps in one launch (small.hpp) ----
+// Bounds the time of one launch; any split into launches gives the same bits.
+constexpr int SMALL_STEPS = 2048;
+
+SmallArgs small_base(const pa_ctx* c, cd* state, int nb) {
+    SmallArgs a{};
+    a.tw = c->tw;
+    a.invk2 = c->invk2;
+    a.ex2 = c->ex2;
+    a.ey2 = c->ey2;
+    a.h = c->ph.dt;
+    a.forcing = c->forcing;
+    a.nf = c->nf;
+    a.B = nb;
+    a.stride_b = c->d.B;
+    a.state = state;
+    return a;
+}
+
+// whether some range observes step n
+bool observed(const ObsPlan& op, int n) {
+    for (int i = 0; i < op.n; ++i)
+        if (op.r[i].slot(n) >= 0) return true;
+    return false;
+}
+
+// Every range observed at step n, from the velocity z of its state.
+pa_status small_observe_step(pa_ctx* c, WS& w, const ObsPlan& op, int n, const cd* z, double* obs_out) {
+    const size_t nn = (size_t)c->d.N * c->d.N;
+    for (int i = 0; i < op.n; ++i) {
+        const ObsRange& r = op.r[i];
+        const int slot = r.slot(n);
+        if (slot < 0) continue;
+        PA_HIP(launch_small_observe(c->d.N, r.nb, z + (size_t)r.b0 * nn,
+                                    row_obs_args(&r, slot, obs_out, w.jpart + r.jrow0), c->stream));
+    }
+    return PA_OK;
+}
+
+// run_steps for these grids: one launch from one observed step, checkpoint
+// boundary or change of the active members to the next.  The velocity of the
+// state at n1 is left in w.zf with final_z, in slot (n1 - n0, 0) with store.
+pa_status small_run_steps(pa_ctx* c, WS& w, int n0, int n1, int n_total, int K, bool store, const ObsPlan* op,
+                          bool observe, double* obs_out, CkptTarget ckpt, bool final_z) {
+    const int nseg = n_segments(n_total, K), B = c->d.B;
+    auto act = [&](int n) { return op ? op->act(n) : B; };
+    auto seen = [&](int n) { return op && observe && observed(*op, n); };
+    auto ckpt_at = [&](int n) -> cd* {   // n > n0
+        if (!ckpt.base || !(n % K == 0 || n == n_total)) return nullptr;
+        const int bi = n == n_total ? nseg : n / K;
+        const int slot = ckpt.map ? (*ckpt.map)[(size_t)bi] : bi;
+        return slot >= 0 ? ckpt_slot(c, ckpt.base, slot) : nullptr;
+    };
+    for (int n = n0, e; n < n1; n = e) {
+        const bool obs_here = seen(n);
+        cd* const z_here = store ? small_slot(c, w, n - n0) : w.zf;
+        if (obs_here && n == n0 && (!store || act(n) < B)) {
+            // the start's velocity: every member's, as one whose horizon is n0 is observed from it
+            SmallArgs a = small_base(c, w.omega, B);
+            a.z_out = z_here;
+            PA_HIP(launch_small_forward(c->d, a, c->stream));
+        }
+        if (obs_here && !store) PA_TRY(small_observe_step(c, w, *op, n, z_here, obs_out));
+        e = n + 1;
+        while (e < n1 && e - n < SMALL_STEPS && !seen(e) && !ckpt_at(e) && act(e) == act(n)) ++e;
+        if (act(n) > 0) {
+            SmallArgs a = small_base(c, w.omega, act(n));
+            a.steps = e - n;
+            a.store = store ? z_here : nullptr;
+            a.ckpt = ckpt_at(e);
+            a.z_out = !store && (e < n1 ? seen(e) : final_z) ? w.zf : nullptr;
+            PA_HIP(launch_small_forward(c->d, a, c->stream));
+        }
+        if (obs_here && store) PA_TRY(small_observe_step(c, w, *op, n, z_here, obs_out));
+    }
+    return PA_OK;
+}
+
+// Source fields of the members [lo, hi) at step n into w.P0, w.P1 (zero off the
+// probes and for members that do not observe), or a unit u-impulse; *any as in sources_at.
+pa_status small_sources(pa_ctx* c, WS& w, const ObsPlan* op, int n, int lo, int hi, const cd* z, int impulse, int ix,
+                        int iy, bool* any) {
+    const size_t nn = (size_t)c->d.N * c->d.N;
+    *any = false;
+    if (impulse) {
+        RowObs o = row_obs_args(nullptr, -1, nullptr, nullptr);
+        o.imp_x = ix;
+        o.imp_y = iy;
+        *any = true;
+        PA_HIP(launch_small_source(c->d.N, hi - lo, nullptr, o, w.P0 + lo * nn, w.P1 + lo * nn, c->stream));
+        return PA_OK;
+    }
+    if (!op || !op->values) return PA_OK;
+    int covered = 0;
+    for (int i = 0; i < op->n; ++i) {
+        const ObsRange& r = op->r[i];
+        const int a = std::max(lo, r.b0), b = std::min(hi, r.b0 + r.nb);
+        if (a < b && r.slot(n) >= 0) covered += b - a;
+    }
+    if (covered == 0) return PA_OK;
+    *any = true;
+    if (covered < hi - lo) {
+        PA_HIP(launch_fill(w.P0 + lo * nn, 0.0, (size_t)(hi - lo) * nn, c->stream));
+        PA_HIP(launch_fill(w.P1 + lo * nn, 0.0, (size_t)(hi - lo) * nn, c->stream));
+    }
+    for (int i = 0; i < op->n; ++i) {
+        const ObsRange& r = op->r[i];
+        const int a = std::max(lo, r.b0), b = std::min(hi, r.b0 + r.nb), slot = r.slot(n);
+        if (a >= b || slot < 0) continue;
+        RowObs o = row_obs_args(&r, slot, nullptr, nullptr);
+        o.values = r.values + (size_t)(a - r.b0) * r.n_times * 2 * r.M * r.M;
+        PA_HIP(launch_small_source(c->d.N, b - a, z + a * nn, o, w.P0 + a * nn, w.P1 + a * nn, c->stream));
+    }
+    return PA_OK;
+}
+
+// terminal() for these grids: lambda of the members [lo, hi) at step `step`.
+pa_status small_terminal(pa_ctx* c, WS& w, const ObsPlan* op, int step, const cd* z, int impulse, int ix, int iy, int lo,
+                         int hi) {
+    const size_t nn = (size_t)c->d.N * c->d.N, offC = (size_t)lo * per_c(c);
+    bool any = false;
+    PA_TRY(small_sources(c, w, op, step, lo, hi, z, impulse, ix, iy, &any));
+    if (!any) {
+        PA_HIP(launch_fill(reinterpret_cast<double*>(w.lam + offC), 0.0, 2 * (size_t)(hi - lo) * per_c(c), c->stream));
+        return PA_OK;
+    }
+    SmallArgs a = small_base(c, w.lam + offC, hi - lo);
+    a.from_source = 1;
+    a.src_u = w.P0 + lo * nn;
+    a.src_v = w.P1 + lo * nn;
+    PA_HIP(launch_small_adjoint(c->d, a, c->stream));
+    return PA_OK;
+}
+
 // Physical field from a compact state.
 pa_status state_to_phys(pa_ctx* c, WS& w, const cd* state, double* out) {
     ColArgs a = col_base(c);
@@ -788,32 +935,46 @@ pa_status forward_sweep(pa_ctx* c, WS& w, const double* omega0, int n_steps, con
     const int n_last = store ? (n_segments(n_steps, K) - 1) * K : n_steps;   // first step of the stored segment
     bool final_obs = false;
     for (int i = 0; i < op.n; ++i) final_obs = final_obs || op.r[i].slot(n_steps) >= 0;
+    const bool small = small_grid(c->d.N);
     cd* f0[2] = {w.Yf[0], w.Yf[1]};
     if (store && n_last == 0) seg_fields(c, w, 0, 0, f0);
-    PA_TRY(start_state(c, w, omega0, ckpt ? ckpt_slot(c, ckpt, 0) : nullptr, f0));
+    PA_TRY(start_state(c, w, omega0, ckpt ? ckpt_slot(c, ckpt, 0) : nullptr, small ? nullptr : f0));
     // Sobolev term (lambda/2) int |grad u0|^2 = (lambda/2) int omega0^2 (periodic, divergence-free),
     // exact on the grid for the band-limited P omega0: 4 pi^2 lambda * (1/2) sum |omega_hat|^2 / N^4
     const bool reg = c->sobolev > 0.0 && op.values && op.n > 0;
     if (reg) PA_HIP(launch_state_energy(c->d, w.omega, 4.0 * M_PI * M_PI * c->sobolev, w.J2, c->stream));
-    if (n_last > 0) {
-        PA_TRY(run_steps(c, w, 0, n_last, n_steps, K, false, &op, true, obs_out, tgt, !store && final_obs));
-        if (store) {
-            // stage-a fields of the state at n_last (in w.omega) into segment slot (0, 0), for
-            // every member: a member whose horizon is n_last is observed from them
-            cd* s0[2];
-            seg_fields(c, w, 0, 0, s0);
-            ColArgs a = col_base(c);
-            a.state_in = w.omega;
-            set_stage_fields(a, s0);
-            PA_HIP(launch_col(c->d, COL_FROM_STATE, a, c->stream));
+    if (small) {
+        PA_TRY(small_run_steps(c, w, 0, n_last, n_steps, K, false, &op, true, obs_out, tgt, !store && final_obs));
+        if (store) PA_TRY(small_run_steps(c, w, n_last, n_steps, n_steps, K, true, &op, true, obs_out, tgt, false));
+        if (final_obs) {
+            if (n_steps == 0) {
+                SmallArgs a = small_base(c, w.omega, c->d.B);
+                a.z_out = w.zf;
+                PA_HIP(launch_small_forward(c->d, a, c->stream));
+            }
+            PA_TRY(small_observe_step(c, w, op, n_steps, store ? small_slot(c, w, n_steps - n_last) : w.zf, obs_out));
         }
+    } else {
+        if (n_last > 0) {
+            PA_TRY(run_steps(c, w, 0, n_last, n_steps, K, false, &op, true, obs_out, tgt, !store && final_obs));
+            if (store) {
+                // stage-a fields of the state at n_last (in w.omega) into segment slot (0, 0), for
+                // every member: a member whose horizon is n_last is observed from them
+                cd* s0[2];
+                seg_fields(c, w, 0, 0, s0);
+                ColArgs a = col_base(c);
+                a.state_in = w.omega;
+                set_stage_fields(a, s0);
+                PA_HIP(launch_col(c->d, COL_FROM_STATE, a, c->stream));
+            }
+        }
+        cd* fH[2] = {w.Yf[0], w.Yf[1]};
+        if (store) {
+            PA_TRY(run_steps(c, w, n_last, n_steps, n_steps, K, true, &op, true, obs_out, tgt, true));
+            seg_fields(c, w, n_steps - n_last, 0, fH);
+        }
+        if (final_obs) PA_TRY(observe_step(c, w, op, n_steps, fH, obs_out));
     }
-    cd* fH[2] = {w.Yf[0], w.Yf[1]};
-    if (store) {
-        PA_TRY(run_steps(c, w, n_last, n_steps, n_steps, K, true, &op, true, obs_out, tgt, true));
-        seg_fields(c, w, n_steps - n_last, 0, fH);
-    }
-    if (final_obs) PA_TRY(observe_step(c, w, op, n_steps, fH, obs_out));
     if (op.values && op.n > 0) PA_TRY(reduce_cost(c, w, op));
     if (reg) PA_HIP(launch_axpy(c->d.B, 1, nullptr, 1.0, w.J2, w.J, nullptr, c->stream));
     return PA_OK;
@@ -990,6 +1151,39 @@ pa_status backward_sweep(pa_ctx* c, WS& w, const cd* ckpt, int n_steps, int K, c
     }
     if (!w.seg) return fail(PA_EINVAL, "workspace carved without a segment buffer");
     if (plan && !last_ready) return fail(PA_EINVAL, "a schedule's backward sweep follows its forward sweep");
+    // The same for grids up to 64^2: one launch from one step with sources, joining members or
+    // recorded shells to the next.
+    auto reverse_small = [&](int n0, int n1, const cd* src, bool recompute) -> pa_status {
+        if (recompute) {
+            if (src != w.omega)
+                PA_HIP(launch_copy(reinterpret_cast<double*>(w.omega), reinterpret_cast<const double*>(src),
+                                   2 * (size_t)act(n0) * per_c(c), c->stream));
+            PA_TRY(small_run_steps(c, w, n0, n1, n_steps, K, true, op, false, nullptr, CkptTarget(), false));
+        }
+        auto seen = [&](int n) { return !impulse && op && op->values && observed(*op, n); };
+        for (int e = n1; e > n0;) {
+            const int hi = act(e - 1), lo = e >= n_steps ? 0 : act(e);
+            if (hi > lo) {
+                PA_TRY(small_terminal(c, w, op, e, small_slot(c, w, e - n0), impulse, ix, iy, lo, hi));
+                if (e == n_steps) PA_TRY(record_shells(c, w, sh, 0));
+            }
+            int n = e - 1;
+            while (n > n0 && e - n < SMALL_STEPS && !sh.out && !seen(n) && act(n - 1) == hi) --n;
+            SmallArgs a = small_base(c, w.lam, hi);
+            a.steps = e - n;
+            a.store = small_slot(c, w, n - n0);
+            bool any = false;
+            if (seen(n)) PA_TRY(small_sources(c, w, op, n, 0, hi, a.store, 0, ix, iy, &any));
+            if (any) {
+                a.src_u = w.P0;
+                a.src_v = w.P1;
+            }
+            PA_HIP(launch_small_adjoint(c->d, a, c->stream));
+            PA_TRY(record_shells(c, w, sh, n_steps - n));
+            e = n;
+        }
+        return PA_OK;
+    };
     // Recompute segment `seg` keeping its stage fields (from state src; src ==
     // w.omega is the live state), unless its fields are already stored, then
     // run the adjoint steps through it.  Members join the sweep at the step
@@ -998,6 +1192,7 @@ pa_status backward_sweep(pa_ctx* c, WS& w, const cd* ckpt, int n_steps, int K, c
     auto reverse_segment = [&](int seg, const cd* src, bool recompute) -> pa_status {
         const int n0 = seg * K, n1 = std::min(n_steps, n0 + K), L = n1 - n0;
         const bool last = seg == nseg - 1;
+        if (small_grid(c->d.N)) return reverse_small(n0, n1, src, recompute);
         if (recompute) {
             cd* f0[2];
             seg_fields(c, w, 0, 0, f0);
@@ -1049,6 +1244,16 @@ pa_status backward_sweep(pa_ctx* c, WS& w, const cd* ckpt, int n_steps, int K, c
                 PA_TRY(reverse_segment(act_.a, src, true));
                 continue;
             }
+            if (small_grid(c->d.N)) {
+                if (act_.src >= 0)
+                    PA_HIP(launch_copy(reinterpret_cast<double*>(w.omega), reinterpret_cast<const double*>(src),
+                                       2 * (size_t)B * per_c(c), c->stream));
+                if (act_.dst >= 0) end_slot[(size_t)act_.b] = act_.dst;
+                PA_TRY(small_run_steps(c, w, act_.a * K, std::min(n_steps, act_.b * K), n_steps, K, false, nullptr,
+                                       false, nullptr, CkptTarget{ck, &end_slot}, false));
+                end_slot[(size_t)act_.b] = -1;
+                continue;
+            }
             // advance: the stage-a fields of the start state into w.Yf (a live start has them there)
             cd* f0[2] = {w.Yf[0], w.Yf[1]};
             if (act_.src >= 0) {
@@ -1063,6 +1268,15 @@ pa_status backward_sweep(pa_ctx* c, WS& w, const cd* ckpt, int n_steps, int K, c
                              nullptr, CkptTarget{ck, &end_slot}, true));
             end_slot[(size_t)act_.b] = -1;
         }
+    }
+    if (small_grid(c->d.N) && grad_out) {
+        ColArgs a = col_base(c);
+        a.state_in = w.lam;
+        a.scale = scale;
+        a.nout = 1;
+        a.fields[0] = F_OMEGA;
+        a.yout[0] = w.YL[0];
+        PA_HIP(launch_col(slice_dims(c, 0, act(0)), COL_FROM_STATE, a, c->stream));
     }
     PA_TRY(finish_idle(act(0)));
     if (grad_out) PA_HIP(launch_row_c2r(c->d, w.YL[0], grad_out, c->tw, c->stream));

@@ -511,7 +511,7 @@ __device__ __forceinline__ ColPtrs col_ptrs(const ColArgs& a, size_t cmem, int b
     q.p1 = M::FWD ? a.acc + cmem : a.omb + cmem;
     q.ik2 = a.invk2 + kx0;
     q.ex = a.ex2[kx];
-    q.sc = M::ADJ && a.scale ? a.scale[b] : 1.0;
+    q.sc = (M::ADJ || MODE == COL_FROM_STATE) && a.scale ? a.scale[b] : 1.0;
     return q;
 }
 
@@ -564,7 +564,7 @@ __device__ __forceinline__ cd col_mode_update(const ColArgs& a, const ColPtrs& q
     } else if constexpr (MODE == COL_FROM_STATE) {
         const cd w = ins ? s0 : czero();
         if (on && q.om) stc(q.om, ci, w);
-        return w;
+        return cscale(w, q.sc);
     } else if constexpr (ColTraits<MODE>::FWD) {
         if (a.nf > 0 && kx == 0 && (ky_ == a.nf || ky_ == -a.nf)) nl.x += a.forcing;
         if constexpr (MODE == COL_A) {
