@@ -1124,6 +1124,12 @@ pa_status backward_sweep(pa_ctx* c, WS& w, const cd* ckpt, int n_steps, int K, c
     // end at step 0: the gradient field straight from their sources, from the state in slot 0
     auto finish_idle = [&](int lo) -> pa_status {
         if (lo >= B) return PA_OK;
+        if (small_grid(c->d.N)) {
+            SmallArgs a = small_base(c, ckpt_slot(c, ck, 0) + (size_t)lo * per_c(c), B - lo);
+            a.z_out = w.zf + (size_t)lo * c->d.N * c->d.N;   // no steps: the state is only read
+            PA_HIP(launch_small_forward(c->d, a, c->stream));
+            return small_terminal(c, w, op, 0, w.zf, impulse, ix, iy, lo, B);
+        }
         cd* f0[2] = {w.Yf[0], w.Yf[1]};
         const size_t offY = (size_t)lo * per_y(c);
         ColArgs a = col_base(c);
@@ -1135,6 +1141,18 @@ pa_status backward_sweep(pa_ctx* c, WS& w, const cd* ckpt, int n_steps, int K, c
         PA_HIP(launch_col(slice_dims(c, lo, B), COL_FROM_STATE, a, c->stream));
         return terminal(c, w, op, 0, f0, impulse, ix, iy, true, scale, lo, B);
     };
+    // up to 64^2: the gradient's y-field from lambda_0 (the other grids' last column launch writes it)
+    auto small_gradient_field = [&]() -> pa_status {
+        if (!small_grid(c->d.N)) return PA_OK;
+        ColArgs a = col_base(c);
+        a.state_in = w.lam;
+        a.scale = scale;
+        a.nout = 1;
+        a.fields[0] = F_OMEGA;
+        a.yout[0] = w.YL[0];
+        PA_HIP(launch_col(c->d, COL_FROM_STATE, a, c->stream));
+        return PA_OK;
+    };
     if (n_steps == 0) {
         bool obs0 = impulse != 0;
         for (int i = 0; op && op->values && i < op->n; ++i) obs0 = obs0 || op->r[i].slot(0) >= 0;
@@ -1145,6 +1163,7 @@ pa_status backward_sweep(pa_ctx* c, WS& w, const cd* ckpt, int n_steps, int K, c
         }
         PA_TRY(finish_idle(0));
         PA_TRY(record_shells(c, w, sh, 0));
+        if (grad_out) PA_TRY(small_gradient_field());
         if (grad_out) PA_HIP(launch_row_c2r(c->d, w.YL[0], grad_out, c->tw, c->stream));
         if (grad_out) PA_TRY(add_sobolev_gradient(c, w, ckpt, op, impulse, scale, grad_out));
         return PA_OK;
@@ -1269,16 +1288,8 @@ pa_status backward_sweep(pa_ctx* c, WS& w, const cd* ckpt, int n_steps, int K, c
             end_slot[(size_t)act_.b] = -1;
         }
     }
-    if (small_grid(c->d.N) && grad_out) {
-        ColArgs a = col_base(c);
-        a.state_in = w.lam;
-        a.scale = scale;
-        a.nout = 1;
-        a.fields[0] = F_OMEGA;
-        a.yout[0] = w.YL[0];
-        PA_HIP(launch_col(slice_dims(c, 0, act(0)), COL_FROM_STATE, a, c->stream));
-    }
     PA_TRY(finish_idle(act(0)));
+    if (grad_out) PA_TRY(small_gradient_field());
     if (grad_out) PA_HIP(launch_row_c2r(c->d, w.YL[0], grad_out, c->tw, c->stream));
     if (grad_out) PA_TRY(add_sobolev_gradient(c, w, ckpt, op, impulse, scale, grad_out));
     return PA_OK;
