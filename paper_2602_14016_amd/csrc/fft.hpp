@@ -201,6 +201,10 @@ template <> struct Plan<1024, 0> { static constexpr int NS = 3, T = 64,  E = 16;
 template <> struct Plan<1024, 1> { static constexpr int NS = 4, T = 128, E = 8;  static constexpr int R[4] = {8, 8, 4, 4}; };
 template <> struct Plan<1024, 2> { static constexpr int NS = 4, T = 128, E = 8;  static constexpr int R[4] = {8, 8, 4, 4}; };
 
+// Plan 3 (row products at 1024 points): the wavefront transform fft1024_wave,
+// sixteen values per thread.
+template <> struct Plan<1024, 3> { static constexpr int NS = 3, T = 64, E = 16; static constexpr int R[4] = {16, 4, 16, 1}; };
+
 // LDS footprint of one team's exchange area (one padding slot per 16 entries).
 template <int N>
 __host__ __device__ constexpr int lds_team() { return N + N / 16 + 1; }
@@ -464,6 +468,33 @@ __device__ __forceinline__ void lane_swap16(double& a, double& b) {
     b = __builtin_bit_cast(double, ((unsigned long long)hi[1] << 32) | (unsigned long long)lo[1]);
 }
 
+// Lanes with bit 3 set trade a with the b of lanes without (rotation by 8 in rows of 16).
+__device__ __forceinline__ void lane_swap8(double& a, double& b) {
+    const unsigned long long ua = __builtin_bit_cast(unsigned long long, a);
+    const unsigned long long ub = __builtin_bit_cast(unsigned long long, b);
+    const int al = (int)ua, ah = (int)(ua >> 32), bl = (int)ub, bh = (int)(ub >> 32);
+    const unsigned nal = (unsigned)__builtin_amdgcn_update_dpp(al, bl, 0x128, 0xf, 0xc, false);
+    const unsigned nah = (unsigned)__builtin_amdgcn_update_dpp(ah, bh, 0x128, 0xf, 0xc, false);
+    const unsigned nbl = (unsigned)__builtin_amdgcn_update_dpp(bl, al, 0x128, 0xf, 0x3, false);
+    const unsigned nbh = (unsigned)__builtin_amdgcn_update_dpp(bh, ah, 0x128, 0xf, 0x3, false);
+    a = __builtin_bit_cast(double, ((unsigned long long)nah << 32) | nal);
+    b = __builtin_bit_cast(double, ((unsigned long long)nbh << 32) | nbl);
+}
+
+// Trades register bit BIT of eight values with lane bit LANE (5, 4 or 3).
+template <int BIT, int LANE>
+__device__ __forceinline__ void digit_trade(cd* v) {
+#pragma unroll
+    for (int r = 0; r < 8; ++r) {
+        if (r & (1 << BIT)) continue;
+        cd& a = v[r];
+        cd& b = v[r | (1 << BIT)];
+        if constexpr (LANE == 5) { lane_swap32(a.x, b.x); lane_swap32(a.y, b.y); }
+        else if constexpr (LANE == 4) { lane_swap16(a.x, b.x); lane_swap16(a.y, b.y); }
+        else { lane_swap8(a.x, b.x); lane_swap8(a.y, b.y); }
+    }
+}
+
 template <bool INV>
 __device__ __forceinline__ cd tw_apply(cd a, cd w) { return INV ? cmulc(a, w) : cmul(a, w); }
 
@@ -518,6 +549,95 @@ __device__ __forceinline__ void fft256_wave(cd* v, int t, cd* lds, const Tw256& 
     }
     // stage on i0: register m now holds X[t + 64 m]
     dft4<INV>(v[0], v[1], v[2], v[3]);
+}
+
+// ---- 1024 and 512 points on one wavefront, one LDS exchange per transform ----
+// A row of N points is held by 64 lanes, E = N / 64 values per lane: entry
+// t + 64 m in register m of lane t.  Three stages:
+//   * radix E over m gives k_a; twiddles w_N^(k_a t);
+//   * the high part t_hi of the lane trades places with low register bits by
+//     lane swaps (1024: two bits; 512: three), radix 4 or 8 over t_hi gives
+//     k_b; twiddles w_64^(k_b t_lo);
+//   * one exchange through LDS puts t_lo into the register and k_a + E k_b on
+//     the lanes, radix E over t_lo gives k_c.
+// Entry k = k_a + E k_b + 64 k_c ends in register k_c of lane k mod 64: natural
+// order, so the transforms chain with the pointwise products.  The exchange
+// writes and reads with sixteen neighbouring lanes on sixteen bank groups (the
+// slot's low four bits XOR t_lo, doubled at 512).  The Stockham plans of these
+// lengths exchange two or three times per transform, at 1024 points across two
+// wavefronts: 275 KB of LDS traffic per 1024-point row of a forward launch,
+// 94 KB here (times: row_plan3_launch; eight 512^2 members 15.6 -> 14.7 us per
+// forward row launch and 21.4 -> 19.4 per adjoint one, sixteen 32.5 -> 30.2).
+// tw: the table of stage_wave in LDS.
+template <int N>
+__device__ __forceinline__ const cd* stage_wave(cd* lds_tw, const cd* __restrict__ tw) {
+    constexpr int E = N / 64, R = 64 / E;   // radix of the middle stage; t_lo < E
+    constexpr int FIRST = (E - 1) * 64, COUNT = FIRST + (R - 1) * E;
+    for (int i = threadIdx.x; i < COUNT; i += blockDim.x) {
+        const int j = i - FIRST;
+        const int n = j < 0 ? (i / 64 + 1) * (i % 64) : N / 64 * (j / E + 1) * (j % E);
+        lds_tw[i] = tw[n & (N - 1)];
+    }
+    lds_sync();
+    return lds_tw;
+}
+
+template <bool INV>
+__device__ __forceinline__ void fft1024_wave(cd* v, int t, cd* lds, const cd* __restrict__ tw) {
+    dft16<INV>(v);
+#pragma unroll
+    for (int k = 1; k < 16; ++k) v[k] = tw_apply<INV>(v[k], tw[(k - 1) * 64 + t]);
+#pragma unroll
+    for (int r = 0; r < 16; r += 2) {   // register bit 0 <-> lane bit 4
+        lane_swap16(v[r].x, v[r + 1].x);
+        lane_swap16(v[r].y, v[r + 1].y);
+    }
+#pragma unroll
+    for (int r = 0; r < 16; ++r) {      // register bit 1 <-> lane bit 5
+        if (r & 2) continue;
+        lane_swap32(v[r].x, v[r + 2].x);
+        lane_swap32(v[r].y, v[r + 2].y);
+    }
+    const int t_lo = t & 15, a_lo = t >> 4;   // the lane's high bits now hold the low bits of k_a
+    cd wb[4];
+#pragma unroll
+    for (int k = 1; k < 4; ++k) wb[k] = tw[15 * 64 + (k - 1) * 16 + t_lo];
+#pragma unroll
+    for (int hi = 0; hi < 4; ++hi) {
+        cd* u = v + hi * 4;
+        dft<4, INV>(u);
+#pragma unroll
+        for (int k = 1; k < 4; ++k) u[k] = tw_apply<INV>(u[k], wb[k]);
+#pragma unroll
+        for (int k = 0; k < 4; ++k) lds[t_lo * 64 + (((hi * 4 + a_lo) + 16 * k) ^ t_lo)] = u[k];
+    }
+    wave_lds_sync();
+#pragma unroll
+    for (int m = 0; m < 16; ++m) v[m] = lds[m * 64 + (t ^ m)];
+    wave_lds_sync();
+    dft16<INV>(v);
+}
+
+template <bool INV>
+__device__ __forceinline__ void fft512_wave(cd* v, int t, cd* lds, const cd* __restrict__ tw) {
+    dft8<INV>(v);
+#pragma unroll
+    for (int k = 1; k < 8; ++k) v[k] = tw_apply<INV>(v[k], tw[(k - 1) * 64 + t]);
+    digit_trade<0, 3>(v);
+    digit_trade<1, 4>(v);
+    digit_trade<2, 5>(v);
+    dft8<INV>(v);
+    const int t_lo = t & 7, a = t >> 3;   // the lane's high bits now hold k_a
+#pragma unroll
+    for (int k = 0; k < 8; ++k) {
+        if (k > 0) v[k] = tw_apply<INV>(v[k], tw[7 * 64 + (k - 1) * 8 + t_lo]);
+        lds[t_lo * 64 + ((a + 8 * k) ^ (2 * t_lo))] = v[k];
+    }
+    wave_lds_sync();
+#pragma unroll
+    for (int m = 0; m < 8; ++m) v[m] = lds[m * 64 + (t ^ (2 * m))];
+    wave_lds_sync();
+    dft8<INV>(v);
 }
 
 }  // namespace pa

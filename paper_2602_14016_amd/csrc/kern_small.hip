@@ -21,19 +21,6 @@ struct Small {
     static_assert(PITCH > SPARE, "a row's spare columns");
 };
 
-// Lanes with bit 3 set trade a with the b of lanes without (rotation by 8 in rows of 16).
-__device__ __forceinline__ void lane_swap8(double& a, double& b) {
-    const unsigned long long ua = __builtin_bit_cast(unsigned long long, a);
-    const unsigned long long ub = __builtin_bit_cast(unsigned long long, b);
-    const int al = (int)ua, ah = (int)(ua >> 32), bl = (int)ub, bh = (int)(ub >> 32);
-    const unsigned nal = (unsigned)__builtin_amdgcn_update_dpp(al, bl, 0x128, 0xf, 0xc, false);
-    const unsigned nah = (unsigned)__builtin_amdgcn_update_dpp(ah, bh, 0x128, 0xf, 0xc, false);
-    const unsigned nbl = (unsigned)__builtin_amdgcn_update_dpp(bl, al, 0x128, 0xf, 0x3, false);
-    const unsigned nbh = (unsigned)__builtin_amdgcn_update_dpp(bh, ah, 0x128, 0xf, 0x3, false);
-    a = __builtin_bit_cast(double, ((unsigned long long)nah << 32) | nal);
-    b = __builtin_bit_cast(double, ((unsigned long long)nbh << 32) | nbl);
-}
-
 // The neighbouring lane's value (lane bit 0).
 __device__ __forceinline__ double lane_next(double a) {
     const unsigned long long ua = __builtin_bit_cast(unsigned long long, a);
@@ -49,20 +36,6 @@ __device__ __forceinline__ void twin_trade(double& a, double& b, bool odd) {
 __device__ __forceinline__ void twin_trade(cd& a, cd& b, bool odd) {
     twin_trade(a.x, b.x, odd);
     twin_trade(a.y, b.y, odd);
-}
-
-// Trades register bit BIT with lane bit LANE.
-template <int BIT, int LANE>
-__device__ __forceinline__ void digit_trade(cd* v) {
-#pragma unroll
-    for (int r = 0; r < 8; ++r) {
-        if (r & (1 << BIT)) continue;
-        cd& a = v[r];
-        cd& b = v[r | (1 << BIT)];
-        if constexpr (LANE == 5) { lane_swap32(a.x, b.x); lane_swap32(a.y, b.y); }
-        else if constexpr (LANE == 4) { lane_swap16(a.x, b.x); lane_swap16(a.y, b.y); }
-        else { lane_swap8(a.x, b.x); lane_swap8(a.y, b.y); }
-    }
 }
 
 // Transform of a team's N = 8 T points; w[k - 1] = exp(-2 pi i k t / N).  Every

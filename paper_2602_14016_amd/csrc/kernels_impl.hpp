@@ -63,24 +63,37 @@ __device__ __forceinline__ const cd* stage_twiddles(cd* lds_tw, const cd* __rest
 template <int N, int V>
 __host__ __device__ constexpr bool wave256() { return N == 256 && V == 2; }
 
+// The 512-point plan and plan (1024, 3) are wavefront-resident too
+// (fft512_wave, fft1024_wave) and read their factors from an LDS table of
+// their own.
 template <int N, int V>
+__host__ __device__ constexpr bool wave_long() { return N == 512 || (N == 1024 && V == 3); }
+
+template <int N, int V, bool LONG = wave_long<N, V>()>
 struct RowTw {
     TwReg<N, V> r;
 };
+template <int N, int V>
+struct RowTw<N, V, true> {
+    const cd* r;
+};
 template <>
-struct RowTw<256, 2> {
+struct RowTw<256, 2, false> {
     Tw256 r;
 };
 
 template <int N, int V>
 __device__ __forceinline__ void row_twiddles(RowTw<N, V>& tr, int t, const cd* __restrict__ tw_g, cd* tw_lds) {
     if constexpr (wave256<N, V>()) load_tw256(tr.r, t, tw_g);
+    else if constexpr (wave_long<N, V>()) tr.r = stage_wave<N>(tw_lds, tw_g);
     else load_twiddles<N, V>(tr.r, t, stage_twiddles<N, V>(tw_lds, tw_g));
 }
 
 template <int N, int V, bool INV, bool WL>
 __device__ __forceinline__ void row_fft(cd* v, int t, cd* lds, const RowTw<N, V>& tr) {
     if constexpr (wave256<N, V>()) fft256_wave<INV>(v, t, lds, tr.r);
+    else if constexpr (N == 512) fft512_wave<INV>(v, t, lds, tr.r);
+    else if constexpr (wave_long<N, V>()) fft1024_wave<INV>(v, t, lds, tr.r);
     else fft<N, V, INV, WL>(v, t, lds, tr.r);
 }
 
@@ -235,20 +248,29 @@ __device__ __forceinline__ void store_jpart(const RowObs& o, int b, int y, doubl
         o.jpart[((size_t)b * o.n_times + o.slot) * o.M + y / o.stride] = 0.5 * s;
 }
 
+// LDS entries of a row team's exchange area: the padded one of the Stockham
+// plans, or in the product kernels N where the transform is wavefront-resident
+// (four workgroups of four 512-point rows, or two of four 1024-point rows,
+// with their tables fill a CU's 160 KiB).
+template <int N, int V>
+__host__ __device__ constexpr int padded_area() { return lds_team<N>(); }
+template <int N, int V>
+__host__ __device__ constexpr int product_area() { return wave_long<N, V>() ? N : lds_team<N>(); }
+
 // A workgroup holds `tpb` teams; the launcher guarantees tpb divides the
 // teams per member, so the member index is uniform over the workgroup and
 // member base pointers live in scalar registers (32-bit lane offsets).  A
 // team of at most 64 threads lies within one wavefront (WL): its exchanges
 // synchronise the wave only, and the one workgroup barrier is the twiddle
 // staging.
-#define PA_TEAM_SETUP(N, V, TEAMS_PER_MEMBER)                           \
+#define PA_TEAM_SETUP(N, V, TEAMS_PER_MEMBER, AREA)                     \
     constexpr int T = Plan<N, V>::T, E = Plan<N, V>::E;                 \
     constexpr bool WL = T <= 64 && 64 % T == 0;                         \
     extern __shared__ cd smem[];                                        \
     const int team = threadIdx.x / T, t = threadIdx.x % T;              \
-    cd* lds = smem + team * lds_team<N>();                              \
+    cd* lds = smem + team * AREA<N, V>();                               \
     const int tpb_ = blockDim.x / T;                                    \
-    cd* const tw_lds = smem + tpb_ * lds_team<N>();                     \
+    cd* const tw_lds = smem + tpb_ * AREA<N, V>();                      \
     const int g0 = blockIdx.x * tpb_;                                   \
     const int b = g0 / (TEAMS_PER_MEMBER);                              \
     const int w0 = g0 % (TEAMS_PER_MEMBER);                             \
@@ -260,7 +282,7 @@ __device__ __forceinline__ void store_jpart(const RowObs& o, int b, int y, doubl
 template <int N, int V>
 __global__ void __launch_bounds__(256) row_r2c_kernel(Dims d, const double* __restrict__ in,
                                                       cd* __restrict__ out, const cd* __restrict__ tw_g) {
-    PA_TEAM_SETUP(N, V, N / 2)
+    PA_TEAM_SETUP(N, V, N / 2, padded_area)
     const double* r0 = in + ((size_t)b * N + 2 * w0) * N;     // block base (uniform)
     const int ro = 2 * team * N;                               // this team's row pair
     cd z[E];
@@ -279,7 +301,7 @@ __global__ void __launch_bounds__(256) row_r2c_kernel(Dims d, const double* __re
 template <int N, int V>
 __global__ void __launch_bounds__(256) row_c2r_kernel(Dims d, const cd* __restrict__ in,
                                                       double* __restrict__ out, const cd* __restrict__ tw_g) {
-    PA_TEAM_SETUP(N, V, N / 2)
+    PA_TEAM_SETUP(N, V, N / 2, padded_area)
     const cd* i0 = in + ((size_t)b * N + 2 * wi) * kx_pad<N>();
     cd z[E];
     herm_load<N, V>(z, i0, i0 + kx_pad<N>(), t);
@@ -314,12 +336,6 @@ __global__ void __launch_bounds__(256) row_c2r_kernel(Dims d, const cd* __restri
 // z^2 and w conj(z)
 __device__ __forceinline__ cd csq(cd z) { return mk((z.x - z.y) * (z.x + z.y), 2.0 * z.x * z.y); }
 
-// Whether a row pass reads its twiddles from the LDS table instead of holding
-// them in registers: the eight-value plans at 512 and 1024 points have 14 and
-// 19 factors per thread, which spill beside two signals at three waves per SIMD.
-template <int N, int V>
-constexpr bool row_tw_lds() { return (N == 1024 || N == 512) && Plan<N, V>::E >= 8; }
-
 // Right-hand side products of one row.  Inputs yin[0..1] = the packed velocity
 // (u, v), outputs yout[0..1] = the row transform Z of z^2, unsplit
 // (pair_store): Z and conj Z(-k).  Observations are formed by row_obs_kernel
@@ -331,24 +347,16 @@ template <int N, int V>
 __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(sq_waves<N, V>())))
 row_sq_kernel(Dims d, RowArgs a) {
     const cd* __restrict__ tw_g = a.tw;
-    PA_TEAM_SETUP(N, V, N)
+    PA_TEAM_SETUP(N, V, N, product_area)
     const size_t roff = ((size_t)b * N + wi) * kx_pad<N>();
     cd z[E];
     packed_load<N, V>(z, a.yin[0] + roff, a.yin[1] + roff, t);
-    if constexpr (row_tw_lds<N, V>()) {
-        const cd* twl = stage_twiddles<N, V>(tw_lds, tw_g);
-        fft<N, V, true, WL>(z, t, lds, twl);
+    RowTw<N, V> tr;   // both transforms share the thread's twiddles
+    row_twiddles<N, V>(tr, t, tw_g, tw_lds);
+    row_fft<N, V, true, WL>(z, t, lds, tr);
 #pragma unroll
-        for (int m = 0; m < E; ++m) z[m] = csq(z[m]);
-        fft<N, V, false, WL>(z, t, lds, twl);
-    } else {
-        RowTw<N, V> tr;   // both transforms share the thread's twiddles
-        row_twiddles<N, V>(tr, t, tw_g, tw_lds);
-        row_fft<N, V, true, WL>(z, t, lds, tr);
-#pragma unroll
-        for (int m = 0; m < E; ++m) z[m] = csq(z[m]);
-        row_fft<N, V, false, WL>(z, t, lds, tr);
-    }
+    for (int m = 0; m < E; ++m) z[m] = csq(z[m]);
+    row_fft<N, V, false, WL>(z, t, lds, tr);
     pair_store<N, V>(z, t, a.yout[0] + roff, a.yout[1] + roff);
 }
 
@@ -357,7 +365,7 @@ row_sq_kernel(Dims d, RowArgs a) {
 template <int N, int V>
 __global__ void __launch_bounds__(256) row_obs_kernel(Dims d, RowArgs a) {
     const cd* __restrict__ tw_g = a.tw;
-    PA_TEAM_SETUP(N, V, a.obs.M)
+    PA_TEAM_SETUP(N, V, a.obs.M, padded_area)
     const int y = wi * a.obs.stride;
     const size_t roff = ((size_t)b * N + y) * kx_pad<N>();
     cd z[E];
@@ -385,27 +393,18 @@ template <int N, int V>
 __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(mul_waves<N, V>())))
 row_mul_kernel(Dims d, RowArgs a) {
     const cd* __restrict__ tw_g = a.tw;
-    PA_TEAM_SETUP(N, V, N)
+    PA_TEAM_SETUP(N, V, N, product_area)
     const size_t roff = ((size_t)b * N + wi) * kx_pad<N>();
     cd w[E], z[E];
     packed_load<N, V>(w, a.yin[2] + roff, a.yin[3] + roff, t);
     packed_load<N, V>(z, a.yin[0] + roff, a.yin[1] + roff, t);
-    if constexpr (row_tw_lds<N, V>()) {
-        const cd* twl = stage_twiddles<N, V>(tw_lds, tw_g);
-        fft<N, V, true, WL>(w, t, lds, twl);
-        fft<N, V, true, WL>(z, t, lds, twl);
+    RowTw<N, V> tr;   // the three transforms of the row share the thread's twiddles
+    row_twiddles<N, V>(tr, t, tw_g, tw_lds);
+    row_fft<N, V, true, WL>(w, t, lds, tr);
+    row_fft<N, V, true, WL>(z, t, lds, tr);
 #pragma unroll
-        for (int m = 0; m < E; ++m) w[m] = cmulc(w[m], z[m]);
-        fft<N, V, false, WL>(w, t, lds, twl);
-    } else {
-        RowTw<N, V> tr;   // the three transforms of the row share the thread's twiddles
-        row_twiddles<N, V>(tr, t, tw_g, tw_lds);
-        row_fft<N, V, true, WL>(w, t, lds, tr);
-        row_fft<N, V, true, WL>(z, t, lds, tr);
-#pragma unroll
-        for (int m = 0; m < E; ++m) w[m] = cmulc(w[m], z[m]);
-        row_fft<N, V, false, WL>(w, t, lds, tr);
-    }
+    for (int m = 0; m < E; ++m) w[m] = cmulc(w[m], z[m]);
+    row_fft<N, V, false, WL>(w, t, lds, tr);
     pair_store<N, V>(w, t, a.yout[0] + roff, a.yout[1] + roff);
 }
 
@@ -418,7 +417,7 @@ row_mul_kernel(Dims d, RowArgs a) {
 template <int N, int V, int MODE>
 __global__ void __launch_bounds__(256) row_src_kernel(Dims d, RowArgs a) {
     const cd* __restrict__ tw_g = a.tw;
-    PA_TEAM_SETUP(N, V, MODE == SRC_ADD ? a.obs.M : N)
+    PA_TEAM_SETUP(N, V, MODE == SRC_ADD ? a.obs.M : N, padded_area)
     const RowObs& o = a.obs;
     const int y = MODE == SRC_ADD ? wi * o.stride : wi;
     const size_t roff = ((size_t)b * N + y) * kx_pad<N>();
@@ -882,7 +881,9 @@ template <int N>
 struct Pipe {
     static constexpr int T = Plan<N, PIPE_V>::T, E = Plan<N, PIPE_V>::E;
     static constexpr int G = (T <= 64 && 64 % T == 0) ? 64 / T : 1;   // rows per wavefront
-    static constexpr bool OK = T <= 64 && 64 % T == 0 && G <= N;
+    // (from 512 points the wavefront plans are faster without the stage buffer: eight 512^2 members
+    // 19.4 against 25.2 us per adjoint row launch)
+    static constexpr bool OK = T <= 64 && 64 % T == 0 && G <= N && N <= 256;
     static constexpr int KXP = kx_pad<N>();
     static constexpr int SPAN = G * KXP;                   // elements of one field of a row group
     static constexpr int LOADS = (SPAN + 63) / 64;         // 64-lane loads per field
@@ -1016,84 +1017,109 @@ hipError_t pipe_launch(Kern kernel, int teams, const Dims& d, const RowArgs& a, 
 // ------------------------------------------------------------- launchers --
 
 // Teams per workgroup: must divide the teams per member (the kernels take the
-// member index from the workgroup's first team), fit 256 threads and 64 KiB
-// of LDS.
+// member index from the workgroup's first team), fit 256 threads and the LDS:
+// 64 KiB, or the device's limit for plan 3.
+template <int N>
+size_t row_lds(int area, int tpb) { return ((size_t)tpb * area + N) * sizeof(cd); }
+
 template <int N, int V>
-int row_tpb(int tpb, long teams_per_member) {
+int row_tpb(const Dims& d, int tpb, long teams_per_member, int area) {
     const int cap = 256 / Plan<N, V>::T;
+    const size_t most = V == 3 ? (size_t)d.lds_max : 65536;
     if (tpb > cap) tpb = cap;
     if (tpb < 1) tpb = 1;
-    while (tpb > 1 && ((size_t)tpb * lds_team<N>() + N) * sizeof(cd) > 65536) tpb >>= 1;
+    while (tpb > 1 && row_lds<N>(area, tpb) > most) tpb >>= 1;
     while (tpb > 1 && teams_per_member % tpb) tpb >>= 1;
     return tpb;
 }
 
-template <int N, int V>
-size_t row_lds(int tpb) { return ((size_t)tpb * lds_team<N>() + N) * sizeof(cd); }
+// A kernel whose workgroups take more than 64 KiB of LDS: its dynamic limit is
+// raised to the device's once per instantiation.
+template <auto Kernel>
+hipError_t raise_lds(const Dims& d, size_t lds) {
+    if (lds <= 65536) return hipSuccess;
+    static const hipError_t raised =
+        hipFuncSetAttribute(reinterpret_cast<const void*>(Kernel), hipFuncAttributeMaxDynamicSharedMemorySize, d.lds_max);
+    return raised;
+}
 
-#define PA_ROW_LAUNCH_V(V, TPB, KERNEL, ...)                                                   \
+#define PA_ROW_LAUNCH_V(V, TPB, KERNEL, AREA, ...)                                             \
     do {                                                                                       \
-        const int tpb = row_tpb<N, V>((TPB), tpm_);                                            \
+        const int tpb = row_tpb<N, V>(d, (TPB), tpm_, AREA<N, V>());                           \
         const dim3 grid_((unsigned)(teams_ / tpb));                                            \
         const dim3 block_((unsigned)(tpb * Plan<N, V>::T));                                    \
-        const size_t lds_ = row_lds<N, V>(tpb);                                                \
+        const size_t lds_ = row_lds<N>(AREA<N, V>(), tpb);                                     \
         launch_kernel(KERNEL<N, V>, grid_, block_, lds_, s, __VA_ARGS__);                       \
     } while (0)
 
 // VAR / TPB: the plan variant and rows per workgroup of the launching pass
 // (forward rows: d.var, d.tpb; adjoint rows: d.avar, d.atpb).  Variant 3
 // (pipelined) runs the plan of variant 2 in the kernels it does not cover.
-#define PA_ROW_LAUNCH(VAR, TPB, KERNEL, TEAMS_PER_MEMBER, ...)                                 \
+#define PA_ROW_LAUNCH(VAR, TPB, KERNEL, AREA, TEAMS_PER_MEMBER, ...)                           \
     do {                                                                                       \
         const long tpm_ = (TEAMS_PER_MEMBER);                                                  \
         const long teams_ = tpm_ * d.B;                                                        \
-        if ((VAR) == 0) PA_ROW_LAUNCH_V(0, TPB, KERNEL, __VA_ARGS__);                          \
-        else if ((VAR) == 1) PA_ROW_LAUNCH_V(1, TPB, KERNEL, __VA_ARGS__);                     \
-        else PA_ROW_LAUNCH_V(2, TPB, KERNEL, __VA_ARGS__);                                     \
+        if ((VAR) == 0) PA_ROW_LAUNCH_V(0, TPB, KERNEL, AREA, __VA_ARGS__);                    \
+        else if ((VAR) == 1) PA_ROW_LAUNCH_V(1, TPB, KERNEL, AREA, __VA_ARGS__);               \
+        else PA_ROW_LAUNCH_V(2, TPB, KERNEL, AREA, __VA_ARGS__);                               \
         return hipGetLastError();                                                              \
     } while (0)
 
+// Row products of 1024 points run on plan 3 whatever the tiles' variant, four
+// rows per workgroup: its Stockham plans exchange two or three times per
+// transform, across two wavefronts where a thread holds eight values.  Per
+// launch, best Stockham tiles -> plan 3: one member 14.0 -> 11.9 us (forward
+// rows) and 17.4 -> 14.6 (adjoint rows), four 30.8 -> 25.8 and 43.2 -> 37.7,
+// eight 53.1 -> 43.9 and 74.6 -> 61.2 (4.1 and 4.4 TB/s).
+template <int N, auto Kernel>
+hipError_t row_plan3_launch(const Dims& d, const RowArgs& a, hipStream_t s) {
+    constexpr int area = product_area<N, 3>();
+    const int tpb = row_tpb<N, 3>(d, 4, N, area);
+    const size_t lds = row_lds<N>(area, tpb);
+    const hipError_t e = raise_lds<Kernel>(d, lds);
+    if (e != hipSuccess) return e;
+    launch_kernel(Kernel, dim3((unsigned)((long)N * d.B / tpb)), dim3((unsigned)(tpb * Plan<N, 3>::T)), lds, s, d, a);
+    return hipGetLastError();
+}
+
 template <int N>
 hipError_t Launch<N>::row_r2c(const Dims& d, const double* in, cd* out, const cd* tw, hipStream_t s) {
-    PA_ROW_LAUNCH(d.var, d.tpb, row_r2c_kernel, N / 2, d, in, out, tw);
+    PA_ROW_LAUNCH(d.var, d.tpb, row_r2c_kernel, padded_area, N / 2, d, in, out, tw);
 }
 template <int N>
 hipError_t Launch<N>::row_c2r(const Dims& d, const cd* in, double* out, const cd* tw, hipStream_t s) {
-    PA_ROW_LAUNCH(d.var, d.tpb, row_c2r_kernel, N / 2, d, in, out, tw);
+    PA_ROW_LAUNCH(d.var, d.tpb, row_c2r_kernel, padded_area, N / 2, d, in, out, tw);
 }
 template <int N>
 hipError_t Launch<N>::row_sq(const Dims& d, const RowArgs& a, hipStream_t s) {
     if constexpr (Pipe<N>::OK)
         if (d.var == 3) return pipe_launch<N, 2>(row_sq_pipe_kernel<N>, d.tpb, d, a, s);
-    PA_ROW_LAUNCH(d.var, d.tpb, row_sq_kernel, N, d, a);
+    if constexpr (N == 1024) return row_plan3_launch<N, &row_sq_kernel<N, 3>>(d, a, s);
+    else PA_ROW_LAUNCH(d.var, d.tpb, row_sq_kernel, product_area, N, d, a);
 }
 template <int N>
 hipError_t Launch<N>::row_obs(const Dims& d, const RowArgs& a, hipStream_t s) {
-    PA_ROW_LAUNCH(d.var, d.tpb, row_obs_kernel, a.obs.M, d, a);
+    PA_ROW_LAUNCH(d.var, d.tpb, row_obs_kernel, padded_area, a.obs.M, d, a);
 }
 template <int N>
 hipError_t Launch<N>::row_mul(const Dims& d, const RowArgs& a, hipStream_t s) {
     if constexpr (Pipe<N>::OK)
         if (d.avar == 3) return pipe_launch<N, 4>(row_mul_pipe_kernel<N>, d.atpb, d, a, s);
-    PA_ROW_LAUNCH(d.avar, d.atpb, row_mul_kernel, N, d, a);
+    if constexpr (N == 1024) return row_plan3_launch<N, &row_mul_kernel<N, 3>>(d, a, s);
+    else PA_ROW_LAUNCH(d.avar, d.atpb, row_mul_kernel, product_area, N, d, a);
 }
 template <int N>
 hipError_t Launch<N>::row_src(const Dims& d, const RowArgs& a, int mode, hipStream_t s) {
-    if (mode == SRC_ADD) PA_ROW_LAUNCH(d.avar, d.atpb, row_src_add, a.obs.M, d, a);
-    if (mode == SRC_IMPULSE) PA_ROW_LAUNCH(d.avar, d.atpb, row_src_impulse, N, d, a);
-    PA_ROW_LAUNCH(d.avar, d.atpb, row_src_write, N, d, a);
+    if (mode == SRC_ADD) PA_ROW_LAUNCH(d.avar, d.atpb, row_src_add, padded_area, a.obs.M, d, a);
+    if (mode == SRC_IMPULSE) PA_ROW_LAUNCH(d.avar, d.atpb, row_src_impulse, padded_area, N, d, a);
+    PA_ROW_LAUNCH(d.avar, d.atpb, row_src_write, padded_area, N, d, a);
 }
 
-template <class Kern>
-hipError_t col_launch(Kern kernel, const Dims& d, const ColArgs& a, unsigned threads, size_t lds, hipStream_t s) {
-    // Workgroups beyond 64 KiB of LDS: the kernel's dynamic LDS limit is raised
-    // to the device's once per instantiation.
-    if (lds > 65536) {
-        static const hipError_t raised = hipFuncSetAttribute(
-            reinterpret_cast<const void*>(kernel), hipFuncAttributeMaxDynamicSharedMemorySize, d.lds_max);
-        if (raised != hipSuccess) return raised;
-    }
-    launch_kernel(kernel, dim3((unsigned)(d.KXP / a.cb) * (unsigned)d.B), dim3(threads), lds, s, d, a);
+template <auto Kernel>
+hipError_t col_launch(const Dims& d, const ColArgs& a, unsigned threads, size_t lds, hipStream_t s) {
+    const hipError_t e = raise_lds<Kernel>(d, lds);
+    if (e != hipSuccess) return e;
+    launch_kernel(Kernel, dim3((unsigned)(d.KXP / a.cb) * (unsigned)d.B), dim3(threads), lds, s, d, a);
     return hipGetLastError();
 }
 
@@ -1120,9 +1146,9 @@ hipError_t col_mode(const Dims& d, const ColArgs& a, hipStream_t s) {
         while (N >= 64 && ak.cb * T < 16) ak.cb *= 2;
         while (ak.cb > 1 && (2 * ak.cb * T > twin_threads<N, V>() || col_lds<N>(2 * ak.cb) > (size_t)d.lds_max))
             ak.cb /= 2;
-        return col_launch(col_twin_kernel<N, V, MODE>, d, ak, (unsigned)(2 * ak.cb * T), col_lds<N>(2 * ak.cb), s);
+        return col_launch<&col_twin_kernel<N, V, MODE>>(d, ak, (unsigned)(2 * ak.cb * T), col_lds<N>(2 * ak.cb), s);
     }
-    return col_launch(col_pass_kernel<N, V, MODE>, d, ak, (unsigned)(ak.cb * T), col_lds<N>(ak.cb), s);
+    return col_launch<&col_pass_kernel<N, V, MODE>>(d, ak, (unsigned)(ak.cb * T), col_lds<N>(ak.cb), s);
 }
 
 template <int N, int V>
