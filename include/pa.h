@@ -389,17 +389,22 @@ pa_status pa_shell_growth(pa_ctx* ctx, const double* shells, int32_t rows, int32
  * elements per thread, 1: more threads per transform, 2: four elements per
  * thread where the length allows; 3, row passes only: the plan of variant 2
  * run by persistent wavefronts that prefetch their next rows from HBM into
- * LDS, bitwise equal to variant 2); teams = rows per row-pass workgroup (1,
+ * LDS, bitwise equal to variant 2, where such a kernel exists: up to 256
+ * points); teams = rows per row-pass workgroup (1,
  * 2, 4 or 8, capped at 256 threads and 64 KiB of LDS per workgroup; with
  * variant 3, wavefronts per workgroup, capped at 4); col_block =
  * kx columns per column-pass workgroup (1, 2, 4 or 8, with col_block times
  * threads per transform <= 512 and LDS within the device's per-workgroup
- * limit, 160 KiB on gfx950; the default stays within 64 KiB); col_split: 1 =
+ * limit, 160 KiB on gfx950), until it or col_variant is set chosen per launch
+ * from its members; col_split: 1 =
  * one team of threads runs both signals of a column's packed pair, 2 or 4 =
  * twin teams run one each (with fewer columns per workgroup where col_block
  * of them would not fit), 0 = chosen per launch (twins where the launch has
  * fewer than two wavefronts per SIMD without).  Results do not depend on the choice
- * beyond rounding of the transforms, and not at all on col_split. */
+ * beyond rounding of the transforms, and not at all on col_block and col_split.
+ * The defaults depend on the grid, and the block on the batch.  Grids up to 64^2
+ * run their time loop in one kernel without these passes; the right-hand side and
+ * adjoint products of 512 and 1024 points have one plan whatever the variant. */
 typedef struct pa_tiles {
     int32_t row_variant, row_teams;
     int32_t adj_variant, adj_teams;

@@ -106,6 +106,7 @@ struct pa_ctx {
     pa_physics ph;
     hipStream_t stream;
     int device;
+    bool col_plan_set = false;   // a column plan was chosen by pa_set_tiles
     cd* tw;             // [N]
     double* invk2;      // [KY][KXP]
     double* ex2;        // [KXP]
@@ -1380,6 +1381,31 @@ void host_twiddles(int N, std::vector<cd>& tw) {
     }
 }
 
+// Tiles of a new context.  The plans (which set the rounding) depend on the
+// grid alone, so that a member's result does not depend on its batch; the
+// column block follows each launch (col_block_auto).  The grids up to 64^2 run
+// their time loop without these passes and keep the plan of fewest exchanges.
+// Against the sixteen-value plans for every grid, per launch (forward rows,
+// columns, adjoint rows, columns): one 128^2 member 6.8, 9.6, 6.5, 9.4 us -> 6.2,
+// 7.6, 5.0, 7.0; one 256^2 member 6.9, 11.6, 6.9, 11.0 -> 5.4, 8.6, 5.0, 8.4; 64 of
+// them 24.0, 46.0, 34.9, 42.2 -> 21.7, 28.9, 28.0, 26.9; one 1024^2 member's
+// columns 23.0, 22.5 -> 19.4, 18.5.  At 128 points the four-value column plan beats
+// the eight-value one below 64 members (eight members: 7.6 and 7.1 against 8.1 and
+// 7.7 us); from 256 points the eight-value plan does at every batch but one member
+// of 256^2 (8.4 against 8.6 us).
+void default_tiles(Dims& d) {
+    const bool loop = small_grid(d.N);
+    d.var = d.avar = loop ? 0 : 2;
+    d.tpb = d.atpb = 4;
+    d.cvar = loop ? 0 : d.N == 128 ? 2 : 1;
+    d.csplit = 0;
+    d.cb = 8;
+    d.cb_auto = !loop;
+    if (d.cb_auto) d.cb = col_block_auto(d);
+    while (d.cb > 1 && (d.cb * fft_threads(d.N, d.cvar) > 512 ||
+                        ((size_t)d.cb * (d.N + d.N / 16 + 1) + d.N) * sizeof(cd) > 65536)) d.cb >>= 1;
+}
+
 }  // namespace
 
 // ------------------------------------------------ allocation-free calls --
@@ -1462,15 +1488,7 @@ pa_status pa_create(const pa_physics* phys, int32_t N, int32_t B, void* hip_stre
     if (hipDeviceGetAttribute(&d.lds_max, hipDeviceAttributeMaxSharedMemoryPerBlock, dev) != hipSuccess ||
         d.lds_max < 65536)
         d.lds_max = 65536;
-    d.var = 0;
-    d.tpb = 4;
-    d.avar = 0;
-    d.atpb = 4;
-    d.cvar = 0;
-    d.cb = 8;
-    d.csplit = 0;
-    while (d.cb > 1 && (d.cb * fft_threads(N, d.cvar) > 512 ||
-                        ((size_t)d.cb * (N + N / 16 + 1) + N) * sizeof(cd) > 65536)) d.cb >>= 1;
+    default_tiles(d);
 
     std::vector<cd> tw;
     host_twiddles(N, tw);
@@ -1574,17 +1592,20 @@ pa_status pa_set_tiles(pa_ctx* c, const pa_tiles* t) try {
     if (t->adj_teams > 0) d.atpb = t->adj_teams;
     if (t->col_variant >= 0) d.cvar = t->col_variant;
     if (t->col_split >= 0) d.csplit = t->col_split;
-    const int T = fft_threads(d.N, d.cvar);
+    if (t->col_variant >= 0 || t->col_block > 0) d.cb_auto = 0;
     auto col_fits = [&](int cb) {
-        return cb * T <= 512 && ((size_t)cb * (d.N + d.N / 16 + 1) + d.N) * sizeof(cd) <= (size_t)d.lds_max;
+        return cb * fft_threads(d.N, d.cvar) <= 512 && ((size_t)cb * (d.N + d.N / 16 + 1) + d.N) * sizeof(cd) <= (size_t)d.lds_max;
     };
     if (t->col_block > 0) {
+        // a block too wide for the default plan takes the plan of fewest threads
+        if (!c->col_plan_set && t->col_variant < 0 && !col_fits(t->col_block)) d.cvar = 0;
         if (!col_fits(t->col_block)) return fail(PA_EINVAL, "col_block too large for this N and column FFT variant");
         d.cb = t->col_block;
     } else {
         while (d.cb > 1 && !col_fits(d.cb)) d.cb >>= 1;
     }
     c->d = d;
+    c->col_plan_set = c->col_plan_set || t->col_variant >= 0;
     return PA_OK;
 } PA_CATCH_HOST
 

@@ -481,6 +481,19 @@ __device__ __forceinline__ void lane_swap8(double& a, double& b) {
     b = __builtin_bit_cast(double, ((unsigned long long)nbh << 32) | nbl);
 }
 
+// Lanes with bit 2 set trade a with the b of lanes without (rotations by 4 and 12 in rows of 16).
+__device__ __forceinline__ void lane_swap4(double& a, double& b) {
+    const unsigned long long ua = __builtin_bit_cast(unsigned long long, a);
+    const unsigned long long ub = __builtin_bit_cast(unsigned long long, b);
+    const int al = (int)ua, ah = (int)(ua >> 32), bl = (int)ub, bh = (int)(ub >> 32);
+    const unsigned nal = (unsigned)__builtin_amdgcn_update_dpp(al, bl, 0x124, 0xf, 0xa, false);
+    const unsigned nah = (unsigned)__builtin_amdgcn_update_dpp(ah, bh, 0x124, 0xf, 0xa, false);
+    const unsigned nbl = (unsigned)__builtin_amdgcn_update_dpp(bl, al, 0x12c, 0xf, 0x5, false);
+    const unsigned nbh = (unsigned)__builtin_amdgcn_update_dpp(bh, ah, 0x12c, 0xf, 0x5, false);
+    a = __builtin_bit_cast(double, ((unsigned long long)nah << 32) | nal);
+    b = __builtin_bit_cast(double, ((unsigned long long)nbh << 32) | nbl);
+}
+
 // Trades register bit BIT of eight values with lane bit LANE (5, 4 or 3).
 template <int BIT, int LANE>
 __device__ __forceinline__ void digit_trade(cd* v) {
@@ -638,6 +651,116 @@ __device__ __forceinline__ void fft512_wave(cd* v, int t, cd* lds, const cd* __r
     for (int m = 0; m < 8; ++m) v[m] = lds[m * 64 + (t ^ (2 * m))];
     wave_lds_sync();
     dft8<INV>(v);
+}
+
+// ---- column transforms of 128 to 1024 points with eight values per thread ----
+// A column of N = 64 TL points is held by T = 8 TL threads, entry t + T m in
+// register m of thread t = t_lo + TL t_hi, t_hi on lane bits 5:3; t_lo and the
+// columns of the workgroup share the other lane bits and the wavefronts.
+//   * radix 8 over m gives k_a; twiddles w_N^(k_a t);
+//   * t_hi trades places with the register digit by lane swaps, radix 8 over
+//     t_hi gives k_b; twiddles w_T^(k_b t_lo);
+//   * one exchange through LDS, radix TL over t_lo gives k_c (at 1024 points
+//     4 x 4 with a second exchange): entry k = k_a + 8 k_b + 64 k_c ends in
+//     register k / T of thread k mod T, natural order.
+// One exchange less than the Stockham plans (8, 4, 4), (8, 8, 4), (8, 8, 8) and
+// (8, 8, 4, 4), and two workgroup barriers.  Every thread of the workgroup must
+// call it.  tw: the table of stage_trade.
+//
+// Slot of entry kappa = k_a + 8 k_b of block q = t_lo of a column's area: the
+// low four bits are spread so that sixteen neighbouring lanes meet sixteen bank
+// groups, on the write (they differ in the lowest bit of k_a, in the column and
+// in the nl low bits of t_lo that share the low lanes with it) and on the read
+// (in the column, the nl low bits of kappa and its bit LTL, t_hi's lowest).  No
+// padding: two workgroups of four 1024-point areas and their tables fill a CU's
+// 160 KiB.
+struct TradeSpread {
+    int nl, cols;   // t_lo bits in the low lanes; the column's bits, in place
+};
+template <int N>
+struct TradePlan {
+    static constexpr int T = N / 8, TL = T / 8, LTL = TL == 2 ? 1 : TL == 4 ? 2 : TL == 8 ? 3 : 4;
+    static __device__ __forceinline__ int at(int q, int kappa, TradeSpread z) {
+        const int fold = LTL > z.nl ? ((kappa >> LTL) & 1) << z.nl : 0;
+        return q * 64 + (kappa ^ fold ^ ((q & ((1 << z.nl) - 1)) << 1) ^ z.cols);
+    }
+};
+
+template <int N>
+__device__ __forceinline__ const cd* stage_trade(cd* lds_tw, const cd* __restrict__ tw) {
+    using P = TradePlan<N>;
+    constexpr int FIRST = 7 * P::T, SECOND = FIRST + 7 * P::TL, COUNT = SECOND + (P::TL > 8 ? 12 : 0);
+    for (int i = threadIdx.x; i < COUNT; i += blockDim.x) {
+        int n;
+        if (i < FIRST) {
+            const int t = i % P::T;   // stored as t_lo * 8 + t_hi
+            n = (i / P::T + 1) * (t / 8 + P::TL * (t % 8));
+        } else if (i < SECOND) {
+            n = 8 * ((i - FIRST) / P::TL + 1) * ((i - FIRST) % P::TL);
+        } else {
+            n = N / 16 * ((i - SECOND) / 4 + 1) * ((i - SECOND) % 4);
+        }
+        lds_tw[i] = tw[n & (N - 1)];
+    }
+    lds_sync();
+    return lds_tw;
+}
+
+template <int N, bool INV>
+__device__ __forceinline__ void fft_trade(cd* v, int t_lo, int t_hi, TradeSpread spread, cd* area, const cd* __restrict__ tw) {
+    using P = TradePlan<N>;
+    constexpr int T = P::T, TL = P::TL;
+    dft8<INV>(v);
+#pragma unroll
+    for (int k = 1; k < 8; ++k) v[k] = tw_apply<INV>(v[k], tw[(k - 1) * T + t_lo * 8 + t_hi]);
+    digit_trade<0, 3>(v);
+    digit_trade<1, 4>(v);
+    digit_trade<2, 5>(v);
+    dft8<INV>(v);
+#pragma unroll
+    for (int k = 0; k < 8; ++k) {   // the lane digit t_hi now holds k_a
+        if (k > 0) v[k] = tw_apply<INV>(v[k], tw[7 * T + (k - 1) * TL + t_lo]);
+        area[P::at(t_lo, t_hi + 8 * k, spread)] = v[k];
+    }
+    lds_sync();
+    const int t = t_lo + TL * t_hi;
+    if constexpr (TL <= 8) {
+#pragma unroll
+        for (int j = 0; j < 8 / TL; ++j) {
+            cd u[TL];
+#pragma unroll
+            for (int q = 0; q < TL; ++q) u[q] = area[P::at(q, t + T * j, spread)];
+            dft<TL, INV>(u);
+#pragma unroll
+            for (int q = 0; q < TL; ++q) v[j + 8 / TL * q] = u[q];
+        }
+    } else {   // t_lo = a + 4 b: radix 4 over b, in place, then over a
+#pragma unroll
+        for (int j = 0; j < 2; ++j) {
+            const int a = (t >> 6) + 2 * j, kappa = t & 63;
+            cd u[4];
+#pragma unroll
+            for (int q = 0; q < 4; ++q) u[q] = area[P::at(a + 4 * q, kappa, spread)];
+            dft<4, INV>(u);
+#pragma unroll
+            for (int q = 0; q < 4; ++q) {
+                if (q > 0) u[q] = tw_apply<INV>(u[q], tw[7 * T + 7 * TL + (q - 1) * 4 + a]);
+                area[P::at(a + 4 * q, kappa, spread)] = u[q];
+            }
+        }
+        lds_sync();
+#pragma unroll
+        for (int j = 0; j < 2; ++j) {
+            const int k1 = (t >> 6) + 2 * j, kappa = t & 63;
+            cd u[4];
+#pragma unroll
+            for (int q = 0; q < 4; ++q) u[q] = area[P::at(q + 4 * k1, kappa, spread)];
+            dft<4, INV>(u);
+#pragma unroll
+            for (int q = 0; q < 4; ++q) v[j + 2 * q] = u[q];
+        }
+    }
+    lds_sync();
 }
 
 }  // namespace pa

@@ -3,6 +3,8 @@
 // launch with a missing buffer is refused before it can touch memory.
 #include "kernels.hpp"
 
+#include <algorithm>
+
 namespace pa {
 
 DispatchEvents& dispatch_events() {
@@ -57,6 +59,18 @@ int fft_threads(int N, int var) {
         case 512: return Launch<512>::threads(var);
         default: return Launch<1024>::threads(var);
     }
+}
+
+bool col_twins(const Dims& d) {
+    if (d.csplit > 0) return d.csplit > 1;
+    const int T = fft_threads(d.N, d.cvar), cb = d.cb_auto ? std::max(1, 64 / T) : d.cb;
+    const long waves = (long)(d.KXP / cb) * d.B * ((cb * T + 63) / 64);
+    return waves < 8L * std::max(d.cus, 1);
+}
+
+int col_block_auto(const Dims& d) {
+    if (!col_twins(d)) return std::max(1, std::min(8, 256 / fft_threads(d.N, d.cvar)));
+    return (long)d.KXP / 4 * d.B >= std::max(d.cus, 1) / 2 ? 4 : 2;
 }
 
 hipError_t launch_row_r2c(const Dims& d, const double* in, cd* out, const cd* tw, hipStream_t s) {

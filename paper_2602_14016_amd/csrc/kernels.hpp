@@ -34,6 +34,7 @@ struct Dims {
     int var, tpb;    // forward row passes: FFT plan variant (0..3; 3 = pipelined), rows (waves) per workgroup
     int avar, atpb;  // adjoint row passes: FFT plan variant (0..3), rows (waves) per workgroup
     int cvar, cb;    // column pass: FFT plan variant, kx columns per workgroup
+    int cb_auto;     // column pass: the block is chosen per launch (col_block_auto), not by cb
     int csplit;      // column pass: a pair's signals on one team (1) or twin teams (2, 4); 0: chosen per launch
     int cus;         // compute units of the device (persistent grids)
     int lds_max;     // bytes of LDS a workgroup may use on the device (column blocks beyond 64 KiB)
@@ -118,6 +119,19 @@ struct Launch {
 
 // Threads per transform for grid size N and plan variant var.
 int fft_threads(int N, int var);
+
+// Whether a launch of d.B members runs a column's two signals on twin teams
+// (see col_twin_kernel).  The tile's col_split fixes it (1: no, 2 or 4: yes); 0
+// decides by the wavefronts that one team per column would give the launch.
+// Below two per SIMD twins are faster (32 x 256^2 at 1.4: 17.3 against 22.5 us
+// per forward stage; 8 x 512^2 at 1.4: 21.2 against 25.0), above one team is
+// (64 x 256^2 at 2.8: 29.0 against 30.0; 4 x 1024^2 at 2.7: 38.5 against 42.0).
+bool col_twins(const Dims& d);
+// kx columns per workgroup of a launch of d.B members: 256 threads with one
+// team per column; with twins four columns where that gives a workgroup to
+// every other CU, else two (4 x 512^2, 176 workgroups of four: 14.4 against 16.1
+// us; one 1024^2 member, 86: 21.9 against 19.4).
+int col_block_auto(const Dims& d);
 
 // launchers (kernels.hip)
 hipError_t launch_row_r2c(const Dims& d, const double* in, cd* out, const cd* tw, hipStream_t s);

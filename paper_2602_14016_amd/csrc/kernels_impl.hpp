@@ -625,6 +625,53 @@ __device__ __forceinline__ cd col_field(int kind, bool second, bool ins, const C
     return mk(s.x * fr - s.y * fi, s.x * fi + s.y * fr);
 }
 
+// Whether a column plan is the register-trading one (fft_trade): the plans of
+// eight values per thread from 128 points.
+template <int N, int V>
+__host__ __device__ constexpr bool col_trade() { return N >= 128 && Plan<N, V>::E == 8; }
+
+template <int N, int V>
+__host__ __device__ constexpr int col_area() { return col_trade<N, V>() ? N : lds_team<N>(); }
+
+template <int N, int V>
+__device__ __forceinline__ const cd* col_twiddles(cd* lds_tw, const cd* __restrict__ tw) {
+    if constexpr (col_trade<N, V>()) return stage_trade<N>(lds_tw, tw);
+    else return stage_twiddles<N, V>(lds_tw, tw);
+}
+
+// Where a thread of a column kernel works: column c of its workgroup, thread t of
+// the team.  The register-trading plan leaves `low` lane bits to columns and
+// t_lo (three, or two beside a twin bit); `id` counts the threads of a signal.
+struct ColPlace {
+    int c, t;
+    TradeSpread spread;
+};
+template <int N, int V>
+__device__ __forceinline__ ColPlace col_place(int CB, int id, int low, int twin) {
+    ColPlace p;
+    if constexpr (col_trade<N, V>()) {
+        const int lane = threadIdx.x & 63, g = (lane & ((1 << low) - 1)) + ((int)(threadIdx.x >> 6) << low);
+        p.c = g % CB;
+        p.t = g / CB + TradePlan<N>::TL * (lane >> 3);
+        const int lc = CB >= (1 << low) ? low : CB == 4 ? 2 : CB == 2 ? 1 : 0;   // column bits in the low lanes
+        p.spread.nl = low - lc;
+        p.spread.cols = ((p.c & ((1 << lc) - 1)) | (twin << lc)) << (low - lc + 1);
+    } else {
+        p.c = id % CB;
+        p.t = id / CB;
+        p.spread = TradeSpread{0, 0};
+    }
+    return p;
+}
+
+// A column transform by the thread at `p`.
+template <int N, int V, bool INV>
+__device__ __forceinline__ void col_fft(cd* v, const ColPlace& p, cd* lds, const cd* __restrict__ twl) {
+    if constexpr (col_trade<N, V>())
+        fft_trade<N, INV>(v, p.t % TradePlan<N>::TL, p.t / TradePlan<N>::TL, p.spread, lds, twl);
+    else fft<N, V, INV>(v, p.t, lds, twl);
+}
+
 // Two forms of the column pass, with the same arithmetic per value, so a
 // result does not depend on the form:
 //
@@ -640,16 +687,18 @@ __device__ __forceinline__ cd col_field(int kind, bool second, bool ins, const C
 // halves: pair p of registers (p, E-1-p) is exchanged such that twin 0 holds P
 // and Q of entry t + T p (ky >= 0) and twin 1 those of entry t + T (E-1-p)
 // (ky < 0).  Each mode is then loaded, combined and written once, and the same
-// exchange hands the output pair back to the transforms.  Twins sit 16 lanes
-// apart, so the exchange is one v_permlane16_swap per register pair and no LDS;
-// pairs that lie in the de-aliased gap are not exchanged at all.  The chain of a
+// exchange hands the output pair back to the transforms.  Twins sit 4 lanes
+// apart with the register-trading plan (a DPP rotation) and 16 with the others
+// (v_permlane16_swap): no LDS; pairs that lie in the de-aliased gap are not exchanged at all.  The chain of a
 // launch is two transforms instead of four: the form for launches with too few
 // columns to fill the chip (forward stage against one team per column: one
 // 256^2 member 8.1 against 11.2 us, 32 members 18.3 against 22.6; eight 512^2
 // members 21.9 against 25.6; one 1024^2 member 22.3 against 25.5).
-template <int N>
+template <int N, int V>
 __device__ __forceinline__ void twin_swap(double& a, double& b, int twin, int lanes) {
-    if constexpr (N >= 64) {
+    if constexpr (col_trade<N, V>()) {
+        lane_swap4(a, b);
+    } else if constexpr (N >= 64) {
         lane_swap16(a, b);
     } else {   // the smallest grids: teams of fewer than 16 lanes per twin
         const double got = __shfl_xor(twin ? a : b, lanes);
@@ -657,10 +706,10 @@ __device__ __forceinline__ void twin_swap(double& a, double& b, int twin, int la
         else b = got;
     }
 }
-template <int N>
+template <int N, int V>
 __device__ __forceinline__ void twin_swap(cd& a, cd& b, int twin, int lanes) {
-    twin_swap<N>(a.x, b.x, twin, lanes);
-    twin_swap<N>(a.y, b.y, twin, lanes);
+    twin_swap<N, V>(a.x, b.x, twin, lanes);
+    twin_swap<N, V>(a.y, b.y, twin, lanes);
 }
 
 // Most threads of a twin workgroup: plans of up to eight values per thread fit
@@ -668,8 +717,8 @@ __device__ __forceinline__ void twin_swap(cd& a, cd& b, int twin, int lanes) {
 template <int N, int V>
 constexpr int twin_threads() { return Plan<N, V>::E <= 8 ? 1024 : 512; }
 
-template <int N>
-__host__ __device__ constexpr size_t col_lds(int areas) { return ((size_t)areas * lds_team<N>() + N) * sizeof(cd); }
+template <int N, int V>
+__host__ __device__ constexpr size_t col_lds(int areas) { return ((size_t)areas * col_area<N, V>() + N) * sizeof(cd); }
 
 // One-dimensional grid of (member, column block), block fastest.  The hardware
 // hands workgroups to the XCDs round robin by id; each XCD is given a
@@ -694,11 +743,13 @@ __global__ void __launch_bounds__((twin_threads<N, V>())) col_twin_kernel(Dims d
     constexpr int T = Plan<N, V>::T, E = Plan<N, V>::E, EP = E / 2;
     extern __shared__ cd smem[];
     const int CB = a.cb;
-    const int lanes = N >= 64 ? 16 : (CB * T < 16 ? CB * T : 16);   // lanes of one twin in a row
+    constexpr bool TRADE = col_trade<N, V>();
+    const int lanes = TRADE ? 4 : N >= 64 ? 16 : (CB * T < 16 ? CB * T : 16);   // lanes of one twin in a row
     const int twin = ((int)threadIdx.x / lanes) & 1;
-    const int idx = (int)threadIdx.x % lanes + (int)threadIdx.x / (2 * lanes) * lanes;
-    const int c = idx % CB, t = idx / CB;
-    cd* lds = smem + (twin * CB + c) * lds_team<N>();
+    const ColPlace at =
+        col_place<N, V>(CB, (int)threadIdx.x % lanes + (int)threadIdx.x / (2 * lanes) * lanes, 2, twin);
+    const int c = at.c, t = at.t;
+    cd* lds = smem + (twin * CB + c) * col_area<N, V>();
     PA_COL_SETUP(N)
     // the mode this thread works on in pair p: its entry, whether it lies in the band, its compact row
     auto pair_on = [](int p) { return T * p <= K; };   // folds at compile time
@@ -730,12 +781,12 @@ __global__ void __launch_bounds__((twin_threads<N, V>())) col_twin_kernel(Dims d
         if constexpr (MT::NEED0) s0[p] = ldc(q.p0, cidx(p, t));
         if constexpr (MT::NEED1) s1[p] = ldc(q.p1, cidx(p, t));
     }
-    const cd* twl = stage_twiddles<N, V>(smem + 2 * CB * lds_team<N>(), a.tw);
+    const cd* twl = col_twiddles<N, V>(smem + 2 * CB * col_area<N, V>(), a.tw);
     if constexpr (MODE != COL_FROM_STATE) {
-        fft<N, V, false>(v, t, lds, twl);
+        col_fft<N, V, false>(v, at, lds, twl);
 #pragma unroll
         for (int p = 0; p < EP; ++p)
-            if (pair_on(p)) twin_swap<N>(v[p], v[E - 1 - p], twin, lanes);
+            if (pair_on(p)) twin_swap<N, V>(v[p], v[E - 1 - p], twin, lanes);
     }
     const int kind = a.nout > 0 ? a.fields[0] : F_OMEGA;
     const int tu = opaque(t);
@@ -759,8 +810,8 @@ __global__ void __launch_bounds__((twin_threads<N, V>())) col_twin_kernel(Dims d
     if (a.nout < 1) return;   // uniform over the grid
 #pragma unroll
     for (int p = 0; p < EP; ++p)
-        if (pair_on(p)) twin_swap<N>(v[p], v[E - 1 - p], twin, lanes);
-    fft<N, V, true>(v, t, lds, twl);
+        if (pair_on(p)) twin_swap<N, V>(v[p], v[E - 1 - p], twin, lanes);
+    col_fft<N, V, true>(v, at, lds, twl);
     if (colok && twin < a.nout) {
         cd* __restrict__ out = (twin ? a.yout[1] : a.yout[0]) + ymem;
 #pragma unroll
@@ -781,8 +832,9 @@ col_pass_kernel(Dims d, ColArgs a) {
     constexpr int T = Plan<N, V>::T, E = Plan<N, V>::E;
     extern __shared__ cd smem[];
     const int CB = a.cb;
-    const int c = threadIdx.x % CB, t = threadIdx.x / CB;
-    cd* lds = smem + c * lds_team<N>();
+    const ColPlace at = col_place<N, V>(CB, (int)threadIdx.x, 3, 0);
+    const int c = at.c, t = at.t;
+    cd* lds = smem + c * col_area<N, V>();
     PA_COL_SETUP(N)
     auto in_band = [&](int m, int t_) {
         return slot_in_band<N, V>(m) && colok && (t_ + T * m <= K || t_ + T * m >= N - K);
@@ -815,14 +867,14 @@ col_pass_kernel(Dims d, ColArgs a) {
     };
 #pragma unroll
     for (int m = 0; m < E; ++m) s0[m] = s1[m] = czero();
-    const cd* twl = stage_twiddles<N, V>(smem + CB * lds_team<N>(), a.tw);
+    const cd* twl = col_twiddles<N, V>(smem + CB * col_area<N, V>(), a.tw);
     // a stage's compact operand is in flight during the second input transform; a stage
     // with two issues them once the inputs are combined (held through a transform, or
     // beside both transformed inputs, they spill under the three-wave cap)
     constexpr bool BOTH = MT::NEED0 && MT::NEED1;
-    if constexpr (MODE != COL_FROM_STATE) fft<N, V, false>(v0, t, lds, twl);
+    if constexpr (MODE != COL_FROM_STATE) col_fft<N, V, false>(v0, at, lds, twl);
     if constexpr (!BOTH) load_compact();
-    if constexpr (MT::PAIR_IN) fft<N, V, false>(v1, t, lds, twl);
+    if constexpr (MT::PAIR_IN) col_fft<N, V, false>(v1, at, lds, twl);
     cd w[E];   // spectral values handed to the output transforms
     const int tp = opaque(t);
 #pragma unroll
@@ -855,7 +907,7 @@ col_pass_kernel(Dims d, ColArgs a) {
                        ? col_field<N>(a.fields[0], o == 1, ins, q, cidx(m, to), kx, ky_of(m, to), w[m])
                        : czero();
         }
-        fft<N, V, true>(v, t, lds, twl);
+        col_fft<N, V, true>(v, at, lds, twl);
         if (colok) {
             cd* __restrict__ out = a.yout[o] + ymem;
 #pragma unroll
@@ -1123,32 +1175,24 @@ hipError_t col_launch(const Dims& d, const ColArgs& a, unsigned threads, size_t 
     return hipGetLastError();
 }
 
-// Whether a launch runs its pairs on twin teams (see col_twin_kernel).  The
-// tile's col_split fixes it (1: no, 2 or 4: yes); 0 decides by the wavefronts
-// that one team per column would give the launch.  Below two per SIMD twins are
-// faster (32 x 256^2 at 1.4: 18.3 against 22.6 us; 8 x 512^2 at 1.4: 21.9
-// against 25.6), above one team is (64 x 256^2 at 2.8: 28.9 against 31.0;
-// 4 x 1024^2 at 2.7: 41.3 against 54).
-template <int N, int V>
-bool col_twins(const Dims& d) {
-    if (d.csplit > 0) return d.csplit > 1;
-    const long waves = (long)(d.KXP / d.cb) * d.B * ((d.cb * Plan<N, V>::T + 63) / 64);
-    return waves < 8L * std::max(d.cus, 1);   // two wavefronts per SIMD
-}
-
 template <int N, int V, int MODE>
 hipError_t col_mode(const Dims& d, const ColArgs& a, hipStream_t s) {
     constexpr int T = Plan<N, V>::T;
     ColArgs ak = a;
-    ak.cb = d.cb;
-    if (col_twins<N, V>(d)) {
-        // at least the columns that fill 16 lanes per twin, at most what threads and LDS allow
-        while (N >= 64 && ak.cb * T < 16) ak.cb *= 2;
-        while (ak.cb > 1 && (2 * ak.cb * T > twin_threads<N, V>() || col_lds<N>(2 * ak.cb) > (size_t)d.lds_max))
+    ak.cb = d.cb_auto ? col_block_auto(d) : d.cb;
+    // the columns that fill the lanes which a team leaves free (per twin)
+    const int fill = col_trade<N, V>() ? 64 : N >= 64 ? 16 : 1;
+    // a single field in and out has no second signal for a twin
+    const bool single = MODE == COL_FILTER || (MODE == COL_FROM_STATE && a.nout < 2);
+    if (col_twins(d) && !single) {
+        while (ak.cb * T < (col_trade<N, V>() ? 32 : fill)) ak.cb *= 2;
+        while (ak.cb > 1 && (2 * ak.cb * T > twin_threads<N, V>() || col_lds<N, V>(2 * ak.cb) > (size_t)d.lds_max))
             ak.cb /= 2;
-        return col_launch<&col_twin_kernel<N, V, MODE>>(d, ak, (unsigned)(2 * ak.cb * T), col_lds<N>(2 * ak.cb), s);
+        return col_launch<&col_twin_kernel<N, V, MODE>>(d, ak, (unsigned)(2 * ak.cb * T), col_lds<N, V>(2 * ak.cb), s);
     }
-    return col_launch<&col_pass_kernel<N, V, MODE>>(d, ak, (unsigned)(ak.cb * T), col_lds<N>(ak.cb), s);
+    if (col_trade<N, V>())
+        while (ak.cb * T < fill) ak.cb *= 2;
+    return col_launch<&col_pass_kernel<N, V, MODE>>(d, ak, (unsigned)(ak.cb * T), col_lds<N, V>(ak.cb), s);
 }
 
 template <int N, int V>
