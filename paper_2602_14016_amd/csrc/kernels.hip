@@ -65,7 +65,7 @@ bool col_twins(const Dims& d) {
     if (d.csplit > 0) return d.csplit > 1;
     const int T = fft_threads(d.N, d.cvar), cb = d.cb_auto ? std::max(1, 64 / T) : d.cb;
     const long waves = (long)(d.KXP / cb) * d.B * ((cb * T + 63) / 64);
-    return waves < 8L * std::max(d.cus, 1);
+    return waves < (d.N <= 256 ? 10L : 8L) * std::max(d.cus, 1);
 }
 
 int col_block_auto(const Dims& d) {

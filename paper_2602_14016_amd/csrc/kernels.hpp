@@ -122,10 +122,13 @@ int fft_threads(int N, int var);
 
 // Whether a launch of d.B members runs a column's two signals on twin teams
 // (see col_twin_kernel).  The tile's col_split fixes it (1: no, 2 or 4: yes); 0
-// decides by the wavefronts that one team per column would give the launch.
-// Below two per SIMD twins are faster (32 x 256^2 at 1.4: 17.3 against 22.5 us
-// per forward stage; 8 x 512^2 at 1.4: 21.2 against 25.0), above one team is
-// (64 x 256^2 at 2.8: 29.0 against 30.0; 4 x 1024^2 at 2.7: 38.5 against 42.0).
+// decides by the wavefronts that one team per column would give the launch: with
+// eight of them per CU the twins' workgroups fill every CU once, and from there
+// one team per column is faster at 512 and 1024 points (per forward stage, twins
+// against one: 10 x 512^2 at 6.9 per CU 21.0 and 24.9 us, 12 at 8.3 28.0 and 28.1;
+// 2 x 1024^2 at 5.4 23.9 and 28.0, 3 at 8.1 38.2 and 35.7).  Up to 256 points twins
+// still gain a little beyond (48 x 256^2 at 8.3: 22.2 and 26.2; 64 at 11: 30.0 and
+// 28.5; 96 x 128^2 at 9: 16.0 and 17.4; 128 at 12: 18.3 and 18.9).
 bool col_twins(const Dims& d);
 // kx columns per workgroup of a launch of d.B members: 256 threads with one
 // team per column; with twins four columns where that gives a workgroup to

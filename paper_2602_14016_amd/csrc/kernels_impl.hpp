@@ -518,8 +518,7 @@ __device__ __forceinline__ ColPtrs col_ptrs(const ColArgs& a, size_t cmem, int b
 // the nonlinear term of a forward stage, the cotangent of an adjoint stage, the
 // vorticity of probe velocities, or the one input itself.
 template <int MODE>
-__device__ __forceinline__ cd col_pair_value(const ColArgs& a, const ColPtrs& q, bool ins, unsigned ci, int kx, int ky_,
-                                             cd P, cd Q) {
+__device__ __forceinline__ cd col_pair_value(const ColArgs& a, bool ins, double ik2, int kx, int ky_, cd P, cd Q) {
     const double dkx = (double)kx, ky = (double)ky_;
     if constexpr (ColTraits<MODE>::FWD) {
         // -P u . grad w = beta (P + Q) + alpha (P - Q)/i with the spectra of z^2,
@@ -528,7 +527,7 @@ __device__ __forceinline__ cd col_pair_value(const ColArgs& a, const ColPtrs& q,
         return ins ? mk(be * (P.x + Q.x) + al * (P.y - Q.y), be * (P.y + Q.y) - al * (P.x - Q.x)) : czero();
     } else if constexpr (ColTraits<MODE>::ADJ) {
         // U^T and V^T of the products, ((kx - i ky) P - (kx + i ky) Q) / (2 |k|^2)
-        const double f = ins ? 0.5 * q.ik2[ci] : 0.0;
+        const double f = 0.5 * ik2;
         return ins ? mk(f * (dkx * (P.x - Q.x) + ky * (P.y + Q.y)), f * (dkx * (P.y - Q.y) - ky * (P.x + Q.x))) : czero();
     } else if constexpr (MODE == COL_FIRST_GUESS) {
         // vorticity of the low-passed probe velocity: i kx v_hat - i ky u_hat on S
@@ -545,10 +544,10 @@ __device__ __forceinline__ cd col_pair_value(const ColArgs& a, const ColPtrs& q,
 // row, ins: in the band and not the mean.
 template <int N, int MODE>
 __device__ __forceinline__ cd col_mode_update(const ColArgs& a, const ColPtrs& q, bool on, bool ins, unsigned ci,
-                                              int b, int kx, int r, int ky_, cd nl, cd s0, cd s1) {
+                                              int b, int kx, int r, int ky_, double ey2, cd nl, cd s0, cd s1) {
     constexpr int KXP = kx_pad<N>(), KY = 2 * band<N>() + 1;
     const double h = a.h;
-    const double e2 = q.ex * a.ey2[r], e1 = e2 * e2;
+    const double e2 = q.ex * ey2, e1 = e2 * e2;
     if constexpr (MODE == COL_INIT) {
         if (on) {
             if (q.om) stc(q.om, ci, nl);
@@ -607,15 +606,13 @@ __device__ __forceinline__ cd col_mode_update(const ColArgs& a, const ColPtrs& q
 // transform (it is linear): velocity u +- i v has (+-kx + i ky) / |k|^2, the
 // cotangent b +- i a has -2 kx ky +- i (kx^2 - ky^2).
 template <int N>
-__device__ __forceinline__ cd col_field(int kind, bool second, bool ins, const ColPtrs& q, unsigned ci, int kx, int ky_,
-                                        cd w) {
+__device__ __forceinline__ cd col_field(int kind, bool second, bool ins, double ik2, int kx, int ky_, cd w) {
     if (!ins) return czero();
     const double dkx = (double)kx, ky = (double)ky_;
     const cd s = cscale(w, 1.0 / ((double)N * (double)N));
     if (kind == F_OMEGA) return s;
     double fr, fi;
     if (kind == F_ZP) {
-        const double ik2 = q.ik2[ci];
         fr = (second ? -dkx : dkx) * ik2;
         fi = ky * ik2;
     } else {
@@ -774,12 +771,17 @@ __global__ void __launch_bounds__((twin_threads<N, V>())) col_twin_kernel(Dims d
     }
     const ColPtrs q = col_ptrs<MODE>(a, cmem, b, kx0, kx);
     cd s0[EP], s1[EP];
+    double ik2[EP], ey2[EP];   // 1/|k|^2 and the y factor of the integrating factor: loaded here as well, a
+                               // load after the transform would wait for memory once more
 #pragma unroll
     for (int p = 0; p < EP; ++p) {
         s0[p] = s1[p] = czero();
+        ik2[p] = ey2[p] = 0.0;
         if (!pair_on(p)) continue;
         if constexpr (MT::NEED0) s0[p] = ldc(q.p0, cidx(p, t));
         if constexpr (MT::NEED1) s1[p] = ldc(q.p1, cidx(p, t));
+        ik2[p] = q.ik2[cidx(p, t)];
+        ey2[p] = a.ey2[row_of(p, t)];
     }
     const cd* twl = col_twiddles<N, V>(smem + 2 * CB * col_area<N, V>(), a.tw);
     if constexpr (MODE != COL_FROM_STATE) {
@@ -802,10 +804,10 @@ __global__ void __launch_bounds__((twin_threads<N, V>())) col_twin_kernel(Dims d
         const unsigned ci = cidx(p, tu);
         const int r = row_of(p, tu), ky = ky_of(p, tu);
         const bool ins = on && !(kx == 0 && r == 0);
-        const cd nl = col_pair_value<MODE>(a, q, ins, ci, kx, ky, P, Q);
-        const cd w = col_mode_update<N, MODE>(a, q, on, ins, ci, b, kx, r, ky, nl, s0[p], s1[p]);
-        P = col_field<N>(kind, false, ins, q, ci, kx, ky, w);
-        Q = kind == F_OMEGA ? czero() : col_field<N>(kind, true, ins, q, ci, kx, ky, w);
+        const cd nl = col_pair_value<MODE>(a, ins, ik2[p], kx, ky, P, Q);
+        const cd w = col_mode_update<N, MODE>(a, q, on, ins, ci, b, kx, r, ky, ey2[p], nl, s0[p], s1[p]);
+        P = col_field<N>(kind, false, ins, ik2[p], kx, ky, w);
+        Q = kind == F_OMEGA ? czero() : col_field<N>(kind, true, ins, ik2[p], kx, ky, w);
     }
     if (a.nout < 1) return;   // uniform over the grid
 #pragma unroll
@@ -881,7 +883,8 @@ col_pass_kernel(Dims d, ColArgs a) {
     for (int m = 0; m < E; ++m) {
         const bool ins = in_band(m, tp) && !(kx == 0 && row_of(m, tp) == 0);
         w[m] = MODE != COL_FROM_STATE && slot_in_band<N, V>(m)
-                   ? col_pair_value<MODE>(a, q, ins, cidx(m, tp), kx, ky_of(m, tp), v0[m], MT::PAIR_IN ? v1[m] : czero())
+                   ? col_pair_value<MODE>(a, ins, MT::ADJ && ins ? q.ik2[cidx(m, tp)] : 0.0, kx, ky_of(m, tp), v0[m],
+                                          MT::PAIR_IN ? v1[m] : czero())
                    : czero();
     }
     if constexpr (BOTH) {
@@ -895,7 +898,7 @@ col_pass_kernel(Dims d, ColArgs a) {
         const bool on = in_band(m, tu);
         const int r = row_of(m, tu);
         const bool ins = on && !(kx == 0 && r == 0);
-        w[m] = col_mode_update<N, MODE>(a, q, on, ins, cidx(m, tu), b, kx, r, ky_of(m, tu), w[m], s0[m], s1[m]);
+        w[m] = col_mode_update<N, MODE>(a, q, on, ins, cidx(m, tu), b, kx, r, ky_of(m, tu), a.ey2[r], w[m], s0[m], s1[m]);
     }
     for (int o = 0; o < a.nout; ++o) {
         cd v[E];
@@ -904,7 +907,8 @@ col_pass_kernel(Dims d, ColArgs a) {
         for (int m = 0; m < E; ++m) {
             const bool ins = in_band(m, to) && !(kx == 0 && row_of(m, to) == 0);
             v[m] = slot_in_band<N, V>(m)
-                       ? col_field<N>(a.fields[0], o == 1, ins, q, cidx(m, to), kx, ky_of(m, to), w[m])
+                       ? col_field<N>(a.fields[0], o == 1, ins, ins && a.fields[0] == F_ZP ? q.ik2[cidx(m, to)] : 0.0, kx,
+                                      ky_of(m, to), w[m])
                        : czero();
         }
         col_fft<N, V, true>(v, at, lds, twl);
