@@ -583,6 +583,7 @@ RowObs row_obs_args(const ObsRange* r, int slot, double* obs_out, double* jpart)
     } else {
         o.stride = o.M = 1;
     }
+    while ((1 << o.ls) < o.stride) ++o.ls;   // the stride divides N: a power of two
     o.obs_out = obs_out;
     o.jpart = jpart;
     o.imp_x = o.imp_y = -1;

