@@ -1297,11 +1297,22 @@ pa_status backward_sweep(pa_ctx* c, WS& w, const cd* ckpt, int n_steps, int K, c
     return PA_OK;
 }
 
-// precondition with the multiplier table mult (computed before): one table
-// for every member, or with per_member one table per member ([B][KY][KXP])
+// precondition with the multiplier table mult: one table for every member, or
+// with per_member one table per member ([B][KY][KXP]).  fill: the table is
+// filled by this call's first launch (else it was computed before).  Fields
+// that partly overlap are transformed in full before any is written.
 pa_status apply_filter(pa_ctx* c, WS& w, const double* mult, const double* in, double* out,
-                       bool per_member = false) {
-    PA_HIP(launch_row_r2c(c->d, in, w.Y0, c->tw, c->stream));
+                       bool per_member = false, const MultSpec* fill = nullptr) {
+    const std::uintptr_t i0 = reinterpret_cast<std::uintptr_t>(in), o0 = reinterpret_cast<std::uintptr_t>(out);
+    const std::uintptr_t bytes = (std::uintptr_t)c->d.B * c->d.N * c->d.N * sizeof(double);
+    if (small_grid(c->d.N) && (i0 == o0 || i0 + bytes <= o0 || o0 + bytes <= i0)) {
+        MultSpec m{};
+        if (fill) m = *fill;
+        m.table = fill ? nullptr : const_cast<double*>(mult);
+        PA_HIP(launch_small_filter(c->d, SmallFilter{c->tw, in, out, m, per_member ? 1 : 0, c->d.B}, c->stream));
+        return PA_OK;
+    }
+    PA_HIP(launch_row_r2c(c->d, in, w.Y0, c->tw, c->stream, fill));
     ColArgs a = col_base(c);
     a.yin[0] = w.Y0;
     a.mult = mult;
@@ -1324,7 +1335,7 @@ pa_status valid_kernel(const pa_kernel* k) {
 
 // The multiplier (m^2 W)^power must be finite on the whole band of the
 // context's grid.  It is evaluated here with the operations of
-// make_mult_kernel (W, then m^2 W, then the power), before anything is
+// mult_value (W, then m^2 W, then the power), before anything is
 // enqueued: a kernel whose W underflows to zero where it is inverted, or whose
 // power leaves the double range, has no finite latent map on this grid and is
 // refused rather than turned into infinite fields.  The multiplier depends on
@@ -1962,8 +1973,8 @@ pa_status pa_precondition(pa_ctx* c, const pa_kernel* k, double power, const dou
     PA_TRY(require_device(c->stream, {{in, "in"}, {out, "out"}, {workspace, "workspace"}}));
     WS w;
     PA_TRY(check_ws(c, workspace, wbytes, 0, 1, 0, 0, &w));
-    PA_HIP(launch_make_mult(c->d, k->kind, k->metric, k->param, power, w.mult, c->stream));
-    return apply_filter(c, w, w.mult, in, out);
+    const MultSpec m{k->kind, k->metric, k->param, power, w.mult};
+    return apply_filter(c, w, w.mult, in, out, false, &m);
 } PA_CATCH_HOST
 
 }  // extern "C"
@@ -2127,8 +2138,8 @@ static pa_status assimilate_impl(pa_ctx* c, double* omega_inout, int32_t n_steps
     double* mult_m = w.mult + MTB;   // (m^2 W)^(-1/2)
     for (int b = 0; b < (per_member ? B : 1); ++b) {
         const pa_kernel* k = &kernels[b];
-        PA_HIP(launch_make_mult(c->d, k->kind, k->metric, k->param, 0.5, mult_p + b * MT, c->stream));
-        PA_HIP(launch_make_mult(c->d, k->kind, k->metric, k->param, -0.5, mult_m + b * MT, c->stream));
+        PA_HIP(launch_make_mult(c->d, MultSpec{k->kind, k->metric, k->param, 0.5, mult_p + b * MT}, c->stream));
+        PA_HIP(launch_make_mult(c->d, MultSpec{k->kind, k->metric, k->param, -0.5, mult_m + b * MT}, c->stream));
     }
     Opt o{c, w, n, B};
     const StatLayout stl = stat_layout(B);

@@ -356,6 +356,44 @@ __global__ void __launch_bounds__(Small<N>::THREADS) small_adjoint_kernel(SmallA
         if (th.on(p)) st[th.cidx(p)] = lam[p];
 }
 
+// A field, real signal of the packed pair (P = Q = its half spectrum), there and
+// back in one launch.  A call is bound by what the host spends on it: 18.6 us
+// for a 64^2 field in three launches (the first one filling the table), 11.9 here.
+template <int N>
+__global__ void __launch_bounds__(Small<N>::THREADS) small_filter_kernel(SmallFilter a) {
+    using S = Small<N>;
+    extern __shared__ cd smem[];
+    const SmallThread<N> th(a.tw, smem);
+    const size_t f0 = (size_t)blockIdx.x * N * N;
+    cd v[8];
+#pragma unroll
+    for (int m = 0; m < 8; ++m) v[m] = mk(th.row_on ? a.in[f0 + small_at<N>(th.row, th.t, m)] : 0.0, 0.0);
+    double f[S::MODES], none[S::MODES];
+    const double inv_n2 = 1.0 / ((double)N * (double)N);
+    const double* table = a.spec.table ? a.spec.table + (a.table_per_member ? (size_t)blockIdx.x * S::KY * S::KXP : 0) : nullptr;
+#pragma unroll
+    for (int p = 0; p < S::MODES; ++p) {
+        f[p] = table ? table[th.cidx(p)] : mult_value(a.spec, th.kx, th.ky(p));
+        f[p] = th.ins(p) ? f[p] * inv_n2 : 0.0;
+        none[p] = 0.0;
+    }
+    small_fft<N, false>(v, th.w);
+    th.row_write(v);
+    lds_sync();
+    th.col_in(v);
+    cd s[S::MODES];
+#pragma unroll
+    for (int p = 0; p < S::MODES; ++p) s[p] = th.on(p) ? v[p] : czero();
+    th.template col_out<false>(s, f, none);
+    lds_sync();
+    th.row_read(v);
+    small_fft<N, true>(v, th.w);
+    if (th.row_on) {
+#pragma unroll
+        for (int m = 0; m < 8; ++m) a.out[f0 + small_at<N>(th.row, th.t, m)] = v[m].x;
+    }
+}
+
 // Probes of one observed step: a wavefront per probe row and member, in the
 // order of the rows' probes.
 __global__ void __launch_bounds__(64) small_observe_kernel(int N, const cd* __restrict__ z, RowObs o) {
@@ -412,6 +450,13 @@ static hipError_t adjoint_n(const SmallArgs& a, hipStream_t s) {
     return hipGetLastError();
 }
 
+template <int N>
+static hipError_t filter_n(const SmallFilter& a, hipStream_t s) {
+    hipLaunchKernelGGL(small_filter_kernel<N>, dim3((unsigned)a.B), dim3(Small<N>::THREADS),
+                       2 * Small<N>::PLANE * sizeof(cd), s, a);
+    return hipGetLastError();
+}
+
 #define PA_SMALL_N(CALL)                       \
     switch (d.N) {                             \
         case 8: return CALL<8>(a, s);          \
@@ -431,6 +476,10 @@ hipError_t launch_small_adjoint(const Dims& d, const SmallArgs& a, hipStream_t s
         (a.from_source ? !a.src_u : (!a.store || a.steps < 1)))
         return hipErrorInvalidValue;
     PA_SMALL_N(adjoint_n);
+}
+hipError_t launch_small_filter(const Dims& d, const SmallFilter& a, hipStream_t s) {
+    if (!a.tw || !a.in || !a.out || a.B < 1 || (a.table_per_member && !a.spec.table)) return hipErrorInvalidValue;
+    PA_SMALL_N(filter_n);
 }
 hipError_t launch_small_observe(int N, int nb, const cd* z, const RowObs& o, hipStream_t s) {
     if (!z || nb < 1 || o.slot < 0 || o.stride < 1 || o.M < 1 || o.n_times <= o.slot) return hipErrorInvalidValue;

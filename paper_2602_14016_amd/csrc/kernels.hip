@@ -73,9 +73,9 @@ int col_block_auto(const Dims& d) {
     return (long)d.KXP / 4 * d.B >= std::max(d.cus, 1) / 2 ? 4 : 2;
 }
 
-hipError_t launch_row_r2c(const Dims& d, const double* in, cd* out, const cd* tw, hipStream_t s) {
-    if (!in || !out || !tw) return hipErrorInvalidValue;
-    PA_DISPATCH_N(row_r2c(d, in, out, tw, s));
+hipError_t launch_row_r2c(const Dims& d, const double* in, cd* out, const cd* tw, hipStream_t s, const MultSpec* m) {
+    if (!in || !out || !tw || (m && !m->table)) return hipErrorInvalidValue;
+    PA_DISPATCH_N(row_r2c(d, in, out, tw, m, s));
 }
 hipError_t launch_row_c2r(const Dims& d, const cd* in, double* out, const cd* tw, hipStream_t s) {
     if (!in || !out || !tw) return hipErrorInvalidValue;

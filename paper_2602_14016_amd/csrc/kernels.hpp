@@ -105,10 +105,34 @@ struct RowArgs {
     RowObs obs;
 };
 
+// A multiplier table (m^2 W)^power on the band, 0 elsewhere.  kind: 0 identity,
+// 1 exp(-p|k|), 2 |k|^(-2p), 3 exp(-p|k|^2); metric 0 velocity (m^2 = |k|^2),
+// 1 vorticity, 2 streamfunction.
+struct MultSpec {
+    int kind, metric;
+    double param, power;
+    double* table;           // [KY][KXP]
+};
+__device__ __forceinline__ double mult_value(const MultSpec& m, int kx, int ky) {   // kx, ky on the band
+    const double k2 = (double)kx * kx + (double)ky * ky;
+    if (k2 == 0.0) return 0.0;
+    const double kap = sqrt(k2);
+    double W = 1.0;
+    if (m.kind == 1) W = exp(-m.param * kap);
+    else if (m.kind == 2) W = pow(kap, -2.0 * m.param);
+    else if (m.kind == 3) W = exp(-m.param * k2);
+    const double base = (m.metric == 0 ? k2 : m.metric == 2 ? k2 * k2 : 1.0) * W;
+    return pow(base, m.power);
+}
+__device__ __forceinline__ void fill_mult(const Dims& d, const MultSpec& m, int i) {   // entry i of the table
+    const int r = i / d.KXP, kx = i % d.KXP;
+    m.table[i] = kx > d.K ? 0.0 : mult_value(m, kx, r <= d.K ? r : r - d.KY);
+}
+
 // Per-grid-size launchers, instantiated in kern_<N>.hip.
 template <int N>
 struct Launch {
-    static hipError_t row_r2c(const Dims& d, const double* in, cd* out, const cd* tw, hipStream_t s);
+    static hipError_t row_r2c(const Dims& d, const double* in, cd* out, const cd* tw, const MultSpec* m, hipStream_t s);
     static hipError_t row_c2r(const Dims& d, const cd* in, double* out, const cd* tw, hipStream_t s);
     static hipError_t row_sq(const Dims& d, const RowArgs& a, hipStream_t s);
     static hipError_t row_obs(const Dims& d, const RowArgs& a, hipStream_t s);
@@ -138,7 +162,9 @@ bool col_twins(const Dims& d);
 int col_block_auto(const Dims& d);
 
 // launchers (kernels.hip)
-hipError_t launch_row_r2c(const Dims& d, const double* in, cd* out, const cd* tw, hipStream_t s);
+// (m: a multiplier table that the same launch fills, or null)
+hipError_t launch_row_r2c(const Dims& d, const double* in, cd* out, const cd* tw, hipStream_t s,
+                          const MultSpec* m = nullptr);
 hipError_t launch_row_c2r(const Dims& d, const cd* in, double* out, const cd* tw, hipStream_t s);
 hipError_t launch_row_sq(const Dims& d, const RowArgs& a, hipStream_t s);
 hipError_t launch_row_obs(const Dims& d, const RowArgs& a, hipStream_t s);
@@ -150,8 +176,7 @@ hipError_t launch_col(const Dims& d, int mode, const ColArgs& a, hipStream_t s);
 hipError_t launch_reduce_j(int B, int n_rows, const double* jpart, double* J, hipStream_t s);
 hipError_t launch_fill(double* p, double v, size_t n, hipStream_t s);
 hipError_t launch_copy(double* dst, const double* src, size_t n, hipStream_t s);
-hipError_t launch_make_mult(const Dims& d, int kind, int metric, double param, double power,
-                            double* mult, hipStream_t s);
+hipError_t launch_make_mult(const Dims& d, const MultSpec& m, hipStream_t s);
 hipError_t launch_init_spectrum(const Dims& d, const uint64_t* seeds, int kind, double k0,
                                 cd* state, hipStream_t s);
 hipError_t launch_state_norm(const Dims& d, const cd* state, int kind, double* out, hipStream_t s);

@@ -265,7 +265,8 @@ __host__ __device__ constexpr int row_area() { return wave_long<N, V>() ? N : ld
 // team of at most 64 threads lies within one wavefront (WL): its exchanges
 // synchronise the wave only, and the one workgroup barrier is the twiddle
 // staging.
-#define PA_TEAM_SETUP(N, V, TEAMS_PER_MEMBER)                           \
+#define PA_TEAM_SETUP(N, V, TEAMS_PER_MEMBER) PA_TEAM_SETUP_AT(N, V, TEAMS_PER_MEMBER, blockIdx.x)
+#define PA_TEAM_SETUP_AT(N, V, TEAMS_PER_MEMBER, BLOCK)                 \
     constexpr int T = Plan<N, V>::T, E = Plan<N, V>::E;                 \
     constexpr bool WL = T <= 64 && 64 % T == 0;                         \
     extern __shared__ cd smem[];                                        \
@@ -273,18 +274,27 @@ __host__ __device__ constexpr int row_area() { return wave_long<N, V>() ? N : ld
     cd* lds = smem + team * row_area<N, V>();                           \
     const int tpb_ = blockDim.x / T;                                    \
     cd* const tw_lds = smem + tpb_ * row_area<N, V>();                  \
-    const int g0 = blockIdx.x * tpb_;                                   \
+    const int g0 = (int)(BLOCK) * tpb_;                                 \
     const int b = g0 / (TEAMS_PER_MEMBER);                              \
     const int w0 = g0 % (TEAMS_PER_MEMBER);                             \
     const int wi = w0 + team;
 
 // ------------------------------------------------------------ row passes --
 
-// physical rows (y0, y0+1) -> Y rows; team per row pair.
+// physical rows (y0, y0+1) -> Y rows; team per row pair.  The first `fill`
+// workgroups fill the multiplier table of the launch instead: one launch less
+// takes a preconditioner call from 19.9 to 18.8 us at 128^2 (the host enqueues a
+// launch in about 3 us, and such a call runs no faster than that).
 template <int N, int V>
-__global__ void __launch_bounds__(256) row_r2c_kernel(Dims d, const double* __restrict__ in,
-                                                      cd* __restrict__ out, const cd* __restrict__ tw_g) {
-    PA_TEAM_SETUP(N, V, N / 2)
+__global__ void __launch_bounds__(256) row_r2c_kernel(Dims d, const double* __restrict__ in, cd* __restrict__ out,
+                                                      const cd* __restrict__ tw_g, MultSpec mult, unsigned fill) {
+    if (blockIdx.x < fill) {   // uniform over the workgroup
+        const int n = d.KY * d.KXP;
+        for (unsigned i = blockIdx.x * blockDim.x + threadIdx.x; i < (unsigned)n; i += fill * blockDim.x)
+            fill_mult(d, mult, (int)i);
+        return;
+    }
+    PA_TEAM_SETUP_AT(N, V, N / 2, blockIdx.x - fill)
     const double* r0 = in + ((size_t)b * N + 2 * w0) * N;     // block base (uniform)
     const int ro = 2 * team * N;                               // this team's row pair
     cd z[E];
@@ -1123,13 +1133,13 @@ hipError_t raise_lds(const Dims& d, size_t lds) {
 }
 
 template <int N, int V, auto Kernel, class... Args>
-hipError_t row_launch(const Dims& d, int teams, long per_member, hipStream_t s, Args... args) {
+hipError_t row_launch(const Dims& d, int teams, long per_member, unsigned more, hipStream_t s, Args... args) {
     const int tpb = row_tpb<N, V>(d, teams, per_member);
     const size_t lds = row_lds<N, V>(tpb);
     const hipError_t e = raise_lds<Kernel>(d, lds);
     if (e != hipSuccess) return e;
-    launch_kernel(Kernel, dim3((unsigned)(per_member * d.B / tpb)), dim3((unsigned)(tpb * Plan<N, V>::T)), lds, s, d,
-                  args...);
+    launch_kernel(Kernel, dim3((unsigned)(per_member * d.B / tpb) + more), dim3((unsigned)(tpb * Plan<N, V>::T)), lds, s,
+                  d, args...);
     return hipGetLastError();
 }
 
@@ -1142,13 +1152,14 @@ hipError_t row_launch(const Dims& d, int teams, long per_member, hipStream_t s, 
 // launch, best Stockham tiles -> plan 3: one member 14.0 -> 11.9 us (forward
 // rows) and 17.4 -> 14.6 (adjoint rows), four 30.8 -> 25.8 and 43.2 -> 37.7,
 // eight 53.1 -> 43.9 and 74.6 -> 61.2 (4.1 and 4.4 TB/s).
-#define PA_ROW_LAUNCH(VAR, TPB, KERNEL, TEAMS_PER_MEMBER, ...)                                          \
-    do {                                                                                                \
-        const long tpm_ = (TEAMS_PER_MEMBER);                                                           \
-        if constexpr (N == 1024) return row_launch<N, 3, KERNEL(3)>(d, 4, tpm_, s, __VA_ARGS__);        \
-        else if ((VAR) == 0) return row_launch<N, 0, KERNEL(0)>(d, (TPB), tpm_, s, __VA_ARGS__);        \
-        else if ((VAR) == 1) return row_launch<N, 1, KERNEL(1)>(d, (TPB), tpm_, s, __VA_ARGS__);        \
-        else return row_launch<N, 2, KERNEL(2)>(d, (TPB), tpm_, s, __VA_ARGS__);                        \
+// (MORE: workgroups ahead of the rows').
+#define PA_ROW_LAUNCH(VAR, TPB, KERNEL, TEAMS_PER_MEMBER, MORE, ...)                                          \
+    do {                                                                                                      \
+        const long tpm_ = (TEAMS_PER_MEMBER);                                                                 \
+        if constexpr (N == 1024) return row_launch<N, 3, KERNEL(3)>(d, 4, tpm_, (MORE), s, __VA_ARGS__);      \
+        else if ((VAR) == 0) return row_launch<N, 0, KERNEL(0)>(d, (TPB), tpm_, (MORE), s, __VA_ARGS__);      \
+        else if ((VAR) == 1) return row_launch<N, 1, KERNEL(1)>(d, (TPB), tpm_, (MORE), s, __VA_ARGS__);      \
+        else return row_launch<N, 2, KERNEL(2)>(d, (TPB), tpm_, (MORE), s, __VA_ARGS__);                      \
     } while (0)
 
 #define PA_K_R2C(V) &row_r2c_kernel<N, V>
@@ -1161,34 +1172,35 @@ hipError_t row_launch(const Dims& d, int teams, long per_member, hipStream_t s, 
 #define PA_K_SRC_ADD(V) &row_src_kernel<N, V, SRC_ADD>
 
 template <int N>
-hipError_t Launch<N>::row_r2c(const Dims& d, const double* in, cd* out, const cd* tw, hipStream_t s) {
-    PA_ROW_LAUNCH(d.var, d.tpb, PA_K_R2C, N / 2, in, out, tw);
+hipError_t Launch<N>::row_r2c(const Dims& d, const double* in, cd* out, const cd* tw, const MultSpec* m, hipStream_t s) {
+    const unsigned fill = m ? (unsigned)std::min((d.KY * d.KXP + 63) / 64, 512) : 0;   // a value or so per thread
+    PA_ROW_LAUNCH(d.var, d.tpb, PA_K_R2C, N / 2, fill, in, out, tw, m ? *m : MultSpec{}, fill);
 }
 template <int N>
 hipError_t Launch<N>::row_c2r(const Dims& d, const cd* in, double* out, const cd* tw, hipStream_t s) {
-    PA_ROW_LAUNCH(d.var, d.tpb, PA_K_C2R, N / 2, in, out, tw);
+    PA_ROW_LAUNCH(d.var, d.tpb, PA_K_C2R, N / 2, 0u, in, out, tw);
 }
 template <int N>
 hipError_t Launch<N>::row_sq(const Dims& d, const RowArgs& a, hipStream_t s) {
     if constexpr (Pipe<N>::OK)
         if (d.var == 3) return pipe_launch<N, 2>(row_sq_pipe_kernel<N>, d.tpb, d, a, s);
-    PA_ROW_LAUNCH(d.var, d.tpb, PA_K_SQ, N, a);
+    PA_ROW_LAUNCH(d.var, d.tpb, PA_K_SQ, N, 0u, a);
 }
 template <int N>
 hipError_t Launch<N>::row_obs(const Dims& d, const RowArgs& a, hipStream_t s) {
-    PA_ROW_LAUNCH(d.var, d.tpb, PA_K_OBS, a.obs.M, a);
+    PA_ROW_LAUNCH(d.var, d.tpb, PA_K_OBS, a.obs.M, 0u, a);
 }
 template <int N>
 hipError_t Launch<N>::row_mul(const Dims& d, const RowArgs& a, hipStream_t s) {
     if constexpr (Pipe<N>::OK)
         if (d.avar == 3) return pipe_launch<N, 4>(row_mul_pipe_kernel<N>, d.atpb, d, a, s);
-    PA_ROW_LAUNCH(d.avar, d.atpb, PA_K_MUL, N, a);
+    PA_ROW_LAUNCH(d.avar, d.atpb, PA_K_MUL, N, 0u, a);
 }
 template <int N>
 hipError_t Launch<N>::row_src(const Dims& d, const RowArgs& a, int mode, hipStream_t s) {
-    if (mode == SRC_ADD) PA_ROW_LAUNCH(d.avar, d.atpb, PA_K_SRC_ADD, a.obs.M, a);
-    if (mode == SRC_IMPULSE) PA_ROW_LAUNCH(d.avar, d.atpb, PA_K_SRC_IMPULSE, N, a);
-    PA_ROW_LAUNCH(d.avar, d.atpb, PA_K_SRC_WRITE, N, a);
+    if (mode == SRC_ADD) PA_ROW_LAUNCH(d.avar, d.atpb, PA_K_SRC_ADD, a.obs.M, 0u, a);
+    if (mode == SRC_IMPULSE) PA_ROW_LAUNCH(d.avar, d.atpb, PA_K_SRC_IMPULSE, N, 0u, a);
+    PA_ROW_LAUNCH(d.avar, d.atpb, PA_K_SRC_WRITE, N, 0u, a);
 }
 
 template <auto Kernel>

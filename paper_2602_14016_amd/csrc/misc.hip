@@ -46,29 +46,13 @@ hipError_t launch_copy(double* dst, const double* src, size_t n, hipStream_t s) 
     return hipGetLastError();
 }
 
-// (m^2 W)^power on the band, 0 elsewhere.  kind: 0 identity, 1 exp(-p|k|),
-// 2 |k|^(-2p), 3 exp(-p|k|^2); metric 0 velocity (m^2 = |k|^2), 1 vorticity.
-__global__ void make_mult_kernel(Dims d, int kind, int metric, double param, double power,
-                                 double* __restrict__ mult) {
+__global__ void make_mult_kernel(Dims d, MultSpec m) {
     const int i = blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= d.KY * d.KXP) return;
-    const int r = i / d.KXP, kx = i % d.KXP;
-    const int ky = (r <= d.K) ? r : r - d.KY;
-    const double k2 = (double)kx * kx + (double)ky * ky;
-    if (kx > d.K || k2 == 0.0) { mult[i] = 0.0; return; }
-    const double kap = sqrt(k2);
-    double W = 1.0;
-    if (kind == 1) W = exp(-param * kap);
-    else if (kind == 2) W = pow(kap, -2.0 * param);
-    else if (kind == 3) W = exp(-param * k2);
-    const double base = (metric == 0 ? k2 : metric == 2 ? k2 * k2 : 1.0) * W;
-    mult[i] = pow(base, power);
+    if (i < d.KY * d.KXP) fill_mult(d, m, i);
 }
-hipError_t launch_make_mult(const Dims& d, int kind, int metric, double param, double power, double* mult,
-                            hipStream_t s) {
+hipError_t launch_make_mult(const Dims& d, const MultSpec& m, hipStream_t s) {
     const int n = d.KY * d.KXP;
-    hipLaunchKernelGGL(make_mult_kernel, dim3((n + 255) / 256), dim3(256), 0, s, d, kind, metric, param,
-                       power, mult);
+    hipLaunchKernelGGL(make_mult_kernel, dim3((n + 255) / 256), dim3(256), 0, s, d, m);
     return hipGetLastError();
 }
 

@@ -48,7 +48,19 @@ struct SmallArgs {
     int from_source;         // adjoint: lambda starts as U^T r_u + V^T r_v (steps = 0)
 };
 
+// A field through a multiplier on the band.  in and out are the same fields or
+// apart from each other: a member's workgroup reads while another writes.
+struct SmallFilter {
+    const cd* tw;
+    const double* in;        // [B][N][N]
+    double* out;
+    MultSpec spec;           // the table, or with a null table the multiplier itself
+    int table_per_member;    // spec.table [B][KY][KXP]
+    int B;
+};
+
 bool small_grid(int N);
+hipError_t launch_small_filter(const Dims& d, const SmallFilter& a, hipStream_t s);
 hipError_t launch_small_forward(const Dims& d, const SmallArgs& a, hipStream_t s);
 hipError_t launch_small_adjoint(const Dims& d, const SmallArgs& a, hipStream_t s);
 // Observations of members [0, nb) from velocities z [nb][N][N] (all pointers at the first member),
