@@ -141,6 +141,11 @@ pa_status pa_get_shape(const pa_ctx* ctx, int32_t* N, int32_t* B, int32_t* Kc);
  * L-BFGS memory lbfgs_m (0 when not assimilating).  Any call documented as
  * taking "a workspace" accepts one of at least this size for its arguments;
  * pa_precondition and pa_init_field need pa_workspace_bytes(ctx,0,1,0,0).
+ * From two segments of ckpt_every steps on, the size holds the stage fields
+ * of two: the last two are kept and the others recomputed beside the adjoint
+ * of the next, on a second stream that the context makes and joins to its own
+ * before the call's later work.  A gradient also accepts a workspace with room
+ * for one segment (the size that PA_ENOMEM names), with the same bits.
  * The size depends on the context's snapshot budget (pa_set_checkpoint_slots)
  * at the time of the query, which must not grow before the workspace is used. */
 pa_status pa_workspace_bytes(const pa_ctx* ctx, int32_t n_steps, int32_t ckpt_every,
@@ -196,8 +201,8 @@ pa_status pa_adjoint_gradient(pa_ctx* ctx, const double* omega0, int32_t n_steps
  * or freed, nor host memory on success (launch timing by pa_profile_start
  * creates its events).  The internal checkpoints keep one state per segment
  * boundary: PA_EINVAL if a snapshot budget (pa_set_checkpoint_slots) would
- * make a binomial schedule, and PA_EINVAL, with the size needed, when
- * pa_workspace_bytes(ctx, n_steps, ckpt_every, obs->n_times, 0) exceeds
+ * make a binomial schedule, and PA_EINVAL, with the size needed, when the
+ * workspace of such a gradient with room for one segment exceeds
  * PA_NOALLOC_SCRATCH_BYTES (lower ckpt_every or use pa_adjoint_gradient).
  * Every call on one device shares that device's array and leaves its
  * contents behind; calls that overlap in time on one device (other streams,
@@ -435,10 +440,11 @@ pa_status pa_set_sobolev(pa_ctx* ctx, double lambda);
 /* Snapshot budget of the checkpoints kept inside the workspace by
  * pa_adjoint_gradient, pa_adjoint_impulse and pa_assimilate* (the adjoint's
  * recomputation, Sec. I and Sec. II.A).  The horizon splits into L =
- * ceil(n_steps / ckpt_every) segments; each segment is recomputed once with
- * all its stage fields kept before the adjoint runs through it.  slots = 0
- * (the default), or slots > L: the state at every segment boundary is kept
- * (L + 1 spectral states per member) and the forward runs once more in all.
+ * ceil(n_steps / ckpt_every) segments; each segment but the last ones is
+ * recomputed once with all its stage fields kept before the adjoint runs
+ * through it.  slots = 0 (the default), or slots > L: the state at every
+ * segment boundary is kept (L + 1 spectral states per member) and the forward
+ * runs at most once more in all.
  * 1 <= slots <= L: only `slots` spectral states per member are kept (the
  * first holds the initial state) and the segments are reversed by the
  * binomial schedule of Griewank & Walther, which re-advances the fewest

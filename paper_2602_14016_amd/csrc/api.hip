@@ -131,6 +131,9 @@ struct pa_ctx {
     std::vector<hipEvent_t> prof_ev;   // pairs (start, stop)
     // (kind, metric, param, power) of multiplier tables already found finite on this grid
     std::vector<std::array<double, 4>> mult_checked;
+    // a second stream for segments recomputed beside the adjoint (made by the first use)
+    hipStream_t side = nullptr;
+    hipEvent_t fork = nullptr, join = nullptr;
     // pinned host staging of the optimiser's status reads and mask writes
     void* pin = nullptr;
     size_t pin_bytes = 0;
@@ -152,7 +155,8 @@ struct WS {
     cd* acc;
     cd* lam;
     cd* omb;
-    cd* seg;            // segment stage fields, (4K+1) slots x 2 fields (up to 64^2: x one physical velocity)
+    cd* seg;            // segment stage fields, tape_slots() x 2 fields (up to 64^2: x one physical velocity)
+    bool two;           // seg holds two segments
     cd* zf;             // up to 64^2: physical velocity of the current state
     cd* ckpt;           // internal checkpoints
     double* jpart;      // [B][n_obs][N]
@@ -218,7 +222,15 @@ size_t slot_values(const pa_ctx* c) {
     return (size_t)d.B * d.N * (small_grid(d.N) ? d.N : 2 * d.KXP);
 }
 
-WS carve(const pa_ctx* c, int n_steps, int ckpt_every, int n_obs, int m, void* base) {
+// Two segments' stage fields are kept where there are two segments or more:
+// the forward sweep then keeps its last two (under a schedule its last), and
+// the backward sweep recomputes one while it reverses the other.  A workspace
+// too small for both holds one.
+size_t tape_slots(int n_steps, int K, bool two) {
+    return two ? 4 * std::min<size_t>(2 * (size_t)K, (size_t)n_steps) + 2 : 4 * (size_t)K + 1;
+}
+
+WS carve(const pa_ctx* c, int n_steps, int ckpt_every, int n_obs, int m, void* base, bool two = true) {
     const Dims& d = c->d;
     const size_t SY = (size_t)d.B * d.N * d.KXP;
     const size_t SC = (size_t)d.B * d.KY * d.KXP;
@@ -239,7 +251,8 @@ WS carve(const pa_ctx* c, int n_steps, int ckpt_every, int n_obs, int m, void* b
     w.acc = cv.take<cd>(SC);
     w.lam = cv.take<cd>(SC);
     w.omb = cv.take<cd>(SC);
-    w.seg = n_steps > 0 ? cv.take<cd>((size_t)(4 * K + 1) * slot_values(c)) : nullptr;
+    w.two = two && nseg > 1;
+    w.seg = n_steps > 0 ? cv.take<cd>(tape_slots(n_steps, K, w.two) * slot_values(c)) : nullptr;
     w.zf = small_grid(d.N) ? cv.take<cd>(SP) : nullptr;
     w.ckpt = cv.take<cd>((size_t)ckpt_count(c, nseg) * SC);
     w.jpart = cv.take<double>((size_t)d.B * std::max(n_obs, 1) * d.N);
@@ -297,6 +310,17 @@ void seg_fields(const pa_ctx* c, const WS& w, int j, int s, cd* out[2]) {
 
 // up to 64^2: the physical velocity of segment slot (j, 0)
 cd* small_slot(const pa_ctx* c, const WS& w, int j) { return w.seg + (size_t)j * 4 * slot_values(c); }
+
+// The workspace seen from segment `seg`, its fields at v.seg: with room for two
+// segments they take the halves of the store in turn, and the last two of a
+// forward sweep that kept both follow each other (the second starts in the
+// first one's end state).
+WS segment_view(const pa_ctx* c, const WS& w, int nseg, int K, int seg, bool both_kept) {
+    WS v = w;
+    const int back = nseg - 1 - seg;
+    if (w.two && back % 2 == 0) v.seg += (size_t)(4 * K + (both_kept && back == 0 ? 0 : 1)) * slot_values(c);
+    return v;
+}
 
 // ------------------------------------------------- checkpoint schedule --
 // Binomial checkpointing (Griewank 1992; Griewank & Walther 2000).  With the
@@ -534,6 +558,7 @@ pa_status check_ws(const pa_ctx* c, void* ws, size_t bytes, int n_steps, int K, 
         return fail(PA_EINVAL, "binomial schedule over more than PA_MAX_SCHEDULE_SEGMENTS segments: "
                                "raise ckpt_every");
     WS w = carve(c, n_steps, K, n_obs, m, ws);
+    if (w.total > bytes) w = carve(c, n_steps, K, n_obs, m, ws, false);
     if (w.total > bytes)
         return fail(PA_ENOMEM, "workspace too small: need " + std::to_string(w.total) + " bytes");
     *out = w;
@@ -920,21 +945,24 @@ pa_status state_to_phys(pa_ctx* c, WS& w, const cd* state, double* out) {
 }
 
 // Forward sweep with checkpoints into `ckpt` and J into w.J (if values).
-// With store_last (and a segment buffer), the last checkpoint segment runs in
-// store mode: its stage fields go straight to the segment slots, so a
-// backward sweep that follows (last_ready) starts that segment without
-// recomputing it.  With ckpt_every >= n_steps the whole trajectory is kept
-// and the gradient needs no recomputation at all.  The stage fields are the
+// With store_last (and a segment buffer), the last checkpoint segment (the
+// last two with w.two) runs in store mode: its stage fields go straight to the
+// segment slots, so a backward sweep that follows (last_ready) starts without
+// recomputing.  With ckpt_every >= n_steps (half of them with w.two) the whole
+// trajectory is kept and the gradient needs no recomputation at all.  The stage fields are the
 // same either way (same kernels, only their output addresses differ).  With
 // a schedule (plan_for) the checkpoints are those of its first chain, in its
-// slots, and the last segment is always stored.
+// slots, and the last segment alone is always stored.
 pa_status forward_sweep(pa_ctx* c, WS& w, const double* omega0, int n_steps, const ObsPlan& op,
                         double* obs_out, cd* ckpt, int K, bool store_last,
                         const std::vector<PlanAct>* plan = nullptr) {
     if (plan && !(store_last && w.seg && n_steps > 0)) return fail(PA_EINVAL, "schedule needs the segment store");
     const CkptTarget tgt{ckpt, plan ? &c->plan_fwd_slot : nullptr};
     const bool store = store_last && w.seg && n_steps > 0;
-    const int n_last = store ? (n_segments(n_steps, K) - 1) * K : n_steps;   // first step of the stored segment
+    const int nseg = n_segments(n_steps, K), kept = w.two && !plan ? 2 : 1;
+    const int n_last = store ? (nseg - kept) * K : n_steps;   // first stored step
+    cd* const tape = w.seg;
+    if (store && kept == 1) w.seg = segment_view(c, w, nseg, K, nseg - 1, false).seg;
     bool final_obs = false;
     for (int i = 0; i < op.n; ++i) final_obs = final_obs || op.r[i].slot(n_steps) >= 0;
     const bool small = small_grid(c->d.N);
@@ -978,6 +1006,7 @@ pa_status forward_sweep(pa_ctx* c, WS& w, const double* omega0, int n_steps, con
         if (final_obs) PA_TRY(observe_step(c, w, op, n_steps, fH, obs_out));
     }
     if (op.values && op.n > 0) PA_TRY(reduce_cost(c, w, op));
+    w.seg = tape;
     if (reg) PA_HIP(launch_axpy(c->d.B, 1, nullptr, 1.0, w.J2, w.J, nullptr, c->stream));
     return PA_OK;
 }
@@ -1108,16 +1137,76 @@ pa_status add_sobolev_gradient(pa_ctx* c, WS& w, const cd* ckpt, const ObsPlan* 
     return PA_OK;
 }
 
+// Whether a segment is recomputed on a stream of its own beside the adjoint
+// steps of the next, made ready.  A small batch's launches are one chain of
+// latencies that leaves most of the chip idle, and a large one's row and column
+// passes lean on different units.  A gradient whose recomputed steps are a
+// quarter of its own, one after the other -> beside: 64^2 one member 10.4 ->
+// 8.5 ms, 128^2 five 5.35 -> 4.20, 256^2 one 6.50 -> 5.68, three 7.33 -> 6.31,
+// sixteen 14.4 -> 12.3, sixty-four 10.4 -> 10.0, 1024^2 one 9.29 -> 7.93, three
+// 11.8 -> 10.7: never slower.  A captured graph stays one chain.
+bool overlaps(pa_ctx* c) {
+    if (c->prof_class >= 0) return false;   // timed launches run alone
+    hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
+    if (c->stream && (hipStreamIsCapturing(c->stream, &cs) != hipSuccess || cs != hipStreamCaptureStatusNone)) return false;
+    if (!c->side) {
+        if (!c->fork && hipEventCreateWithFlags(&c->fork, hipEventDisableTiming) != hipSuccess) return false;
+        if (!c->join && hipEventCreateWithFlags(&c->join, hipEventDisableTiming) != hipSuccess) return false;
+        if (hipStreamCreateWithFlags(&c->side, hipStreamNonBlocking) != hipSuccess) {
+            c->side = nullptr;
+            return false;
+        }
+    }
+    return true;
+}
+
+// Work on the context's second stream, from fork() to join() in order with the
+// first one's; left early, it is joined all the same.
+struct Beside {
+    pa_ctx* c;
+    bool open = false;
+    explicit Beside(pa_ctx* ctx) : c(ctx) {}
+    Beside(const Beside&) = delete;
+    Beside& operator=(const Beside&) = delete;
+    ~Beside() { (void)join(); }
+    hipError_t fork() {
+        hipError_t e = hipEventRecord(c->fork, c->stream);
+        if (e == hipSuccess) e = hipStreamWaitEvent(c->side, c->fork, 0);
+        open = e == hipSuccess;
+        return e;
+    }
+    hipError_t join() {
+        if (!open) return hipSuccess;
+        open = false;
+        hipError_t e = hipEventRecord(c->join, c->side);
+        if (e == hipSuccess) e = hipStreamWaitEvent(c->stream, c->join, 0);
+        if (e != hipSuccess) (void)hipStreamSynchronize(c->side);
+        return e;
+    }
+    template <class F>
+    pa_status run(F&& f) {
+        struct Swap {   // undone also if f throws
+            pa_ctx* c;
+            hipStream_t first;
+            ~Swap() { c->stream = first; }
+        } swap{c, c->stream};
+        c->stream = c->side;
+        return f();
+    }
+};
+
 // Backward sweep from checkpoints: recompute each segment storing every
 // stage's fields, then run the adjoint steps of the segment in reverse.  With
 // last_ready the last segment's fields are already in the segment slots (a
-// forward sweep with store_last just ran in this workspace).  The final
+// forward sweep with store_last just ran in this workspace; with w.two those
+// of the last two, and with `beside` a segment is recomputed beside the next
+// one's adjoint steps where overlaps() says so).  The final
 // field (P lambda_0 times scale) is written to grad_out (physical).  With a
 // schedule (plan_for; needs last_ready) the segments are reversed in its
 // order, re-advancing from its snapshot slots in ckpt.
 pa_status backward_sweep(pa_ctx* c, WS& w, const cd* ckpt, int n_steps, int K, const ObsPlan* op, int impulse,
                          int ix, int iy, const double* scale, double* grad_out, const Shells& sh,
-                         bool last_ready, const std::vector<PlanAct>* plan = nullptr) {
+                         bool last_ready, const std::vector<PlanAct>* plan = nullptr, bool beside = true) {
     const int nseg = n_segments(n_steps, K);
     const int B = c->d.B;
     auto act = [&](int n) { return op ? op->act(n) : B; };
@@ -1172,122 +1261,208 @@ pa_status backward_sweep(pa_ctx* c, WS& w, const cd* ckpt, int n_steps, int K, c
     }
     if (!w.seg) return fail(PA_EINVAL, "workspace carved without a segment buffer");
     if (plan && !last_ready) return fail(PA_EINVAL, "a schedule's backward sweep follows its forward sweep");
-    // The same for grids up to 64^2: one launch from one step with sources, joining members or
-    // recorded shells to the next.
-    auto reverse_small = [&](int n0, int n1, const cd* src, bool recompute) -> pa_status {
-        if (recompute) {
-            if (src != w.omega)
-                PA_HIP(launch_copy(reinterpret_cast<double*>(w.omega), reinterpret_cast<const double*>(src),
+    // Segment `seg` from state src (src == w.omega: the live state), keeping its stage fields in
+    // v.seg: what precedes its steps, and its steps [m0, m1).
+    auto first = [&](int seg) { return seg * K; };
+    auto length = [&](int seg) { return std::min(n_steps, seg * K + K) - seg * K; };
+    auto recompute_start = [&](WS& v, int seg, const cd* src) -> pa_status {
+        const int n0 = first(seg);
+        if (small_grid(c->d.N)) {
+            if (src != v.omega)
+                PA_HIP(launch_copy(reinterpret_cast<double*>(v.omega), reinterpret_cast<const double*>(src),
                                    2 * (size_t)act(n0) * per_c(c), c->stream));
-            PA_TRY(small_run_steps(c, w, n0, n1, n_steps, K, true, op, false, nullptr, CkptTarget(), false));
+            return PA_OK;
         }
+        cd* f0[2];
+        seg_fields(c, v, 0, 0, f0);
+        ColArgs a = col_base(c);
+        a.state_in = src;
+        a.omega = src == v.omega ? nullptr : v.omega;
+        set_stage_fields(a, f0);
+        PA_HIP(launch_col(slice_dims(c, 0, act(n0)), COL_FROM_STATE, a, c->stream));
+        return PA_OK;
+    };
+    auto recompute_steps = [&](WS& v, int seg, int m0, int m1) -> pa_status {
+        if (m0 >= m1) return PA_OK;
+        const int n0 = first(seg), n1 = n0 + length(seg);
+        cd* const tape = v.seg;
+        v.seg = tape + 4 * (size_t)m0 * slot_values(c);
+        pa_status st;
+        if (small_grid(c->d.N)) {
+            st = small_run_steps(c, v, n0 + m0, n0 + m1, n_steps, K, true, op, false, nullptr, CkptTarget(), false);
+        } else {
+            // the fields of the segment's end state are needed when members join at its last step
+            const bool joins = seg < nseg - 1 && act(n1 - 1) > act(n1);
+            st = run_steps(c, v, n0 + m0, n0 + m1, n_steps, K, true, op, false, nullptr, CkptTarget(),
+                           n0 + m1 < n1 || seg == nseg - 1 || joins);
+        }
+        v.seg = tape;
+        return st;
+    };
+    // Adjoint steps of a segment whose fields are in v.seg, its steps [j0, j1) backwards.  Members
+    // join the sweep at the step after their last: their terminal state is formed there, from the
+    // stage-a fields of their final state.  Up to 64^2: one launch from one step with sources,
+    // joining members or recorded shells to the next.
+    auto adjoint_small = [&](WS& v, int seg, int j0, int j1) -> pa_status {
         auto seen = [&](int n) { return !impulse && op && op->values && observed(*op, n); };
-        for (int e = n1; e > n0;) {
+        const int n0 = first(seg);
+        for (int e = n0 + j1; e > n0 + j0;) {
             const int hi = act(e - 1), lo = e >= n_steps ? 0 : act(e);
             if (hi > lo) {
-                PA_TRY(small_terminal(c, w, op, e, small_slot(c, w, e - n0), impulse, ix, iy, lo, hi));
-                if (e == n_steps) PA_TRY(record_shells(c, w, sh, 0));
+                PA_TRY(small_terminal(c, v, op, e, small_slot(c, v, e - n0), impulse, ix, iy, lo, hi));
+                if (e == n_steps) PA_TRY(record_shells(c, v, sh, 0));
             }
             int n = e - 1;
-            while (n > n0 && e - n < SMALL_STEPS && !sh.out && !seen(n) && act(n - 1) == hi) --n;
-            SmallArgs a = small_base(c, w.lam, hi);
+            while (n > n0 + j0 && e - n < SMALL_STEPS && !sh.out && !seen(n) && act(n - 1) == hi) --n;
+            SmallArgs a = small_base(c, v.lam, hi);
             a.steps = e - n;
-            a.store = small_slot(c, w, n - n0);
+            a.store = small_slot(c, v, n - n0);
             bool any = false;
-            if (seen(n)) PA_TRY(small_sources(c, w, op, n, 0, hi, a.store, 0, ix, iy, &any));
+            if (seen(n)) PA_TRY(small_sources(c, v, op, n, 0, hi, a.store, 0, ix, iy, &any));
             if (any) {
-                a.src_u = w.P0;
-                a.src_v = w.P1;
+                a.src_u = v.P0;
+                a.src_v = v.P1;
             }
             PA_HIP(launch_small_adjoint(c->d, a, c->stream));
-            PA_TRY(record_shells(c, w, sh, n_steps - n));
+            PA_TRY(record_shells(c, v, sh, n_steps - n));
             e = n;
         }
         return PA_OK;
     };
-    // Recompute segment `seg` keeping its stage fields (from state src; src ==
-    // w.omega is the live state), unless its fields are already stored, then
-    // run the adjoint steps through it.  Members join the sweep at the step
-    // after their last: their terminal state is formed there, from the stage-a
-    // fields of their final state.
-    auto reverse_segment = [&](int seg, const cd* src, bool recompute) -> pa_status {
-        const int n0 = seg * K, n1 = std::min(n_steps, n0 + K), L = n1 - n0;
-        const bool last = seg == nseg - 1;
-        if (small_grid(c->d.N)) return reverse_small(n0, n1, src, recompute);
-        if (recompute) {
-            cd* f0[2];
-            seg_fields(c, w, 0, 0, f0);
-            ColArgs a = col_base(c);
-            a.state_in = src;
-            a.omega = src == w.omega ? nullptr : w.omega;
-            set_stage_fields(a, f0);
-            PA_HIP(launch_col(slice_dims(c, 0, act(n0)), COL_FROM_STATE, a, c->stream));
-            // the fields of the segment's end state are needed when members join at its last step
-            const bool joins = !last && act(n1 - 1) > act(n1);
-            PA_TRY(run_steps(c, w, n0, n1, n_steps, K, true, op, false, nullptr, CkptTarget(), last || joins));
-        }
-        for (int j = L - 1; j >= 0; --j) {
-            const int n = n0 + j;
+    auto adjoint_steps = [&](WS& v, int seg, int j0, int j1) -> pa_status {
+        if (small_grid(c->d.N)) return adjoint_small(v, seg, j0, j1);
+        for (int j = j1 - 1; j >= j0; --j) {
+            const int n = first(seg) + j;
             const int hi = act(n), lo = (n + 1 >= n_steps) ? 0 : act(n + 1);
             if (hi > lo) {
                 cd* fm[2];
-                seg_fields(c, w, j + 1, 0, fm);
-                PA_TRY(terminal(c, w, op, n + 1, fm, impulse, ix, iy, false, scale, lo, hi));
-                if (n + 1 == n_steps) PA_TRY(record_shells(c, w, sh, 0));
+                seg_fields(c, v, j + 1, 0, fm);
+                PA_TRY(terminal(c, v, op, n + 1, fm, impulse, ix, iy, false, scale, lo, hi));
+                if (n + 1 == n_steps) PA_TRY(record_shells(c, v, sh, 0));
             }
             cd* fs[2];
-            seg_fields(c, w, j, 3, fs);
-            PA_TRY(adj_stage(c, w, fs, COL_ADJ_C, op, n, 0, nullptr));
-            seg_fields(c, w, j, 2, fs);
-            PA_TRY(adj_stage(c, w, fs, COL_ADJ_B, op, n, 0, nullptr));
-            seg_fields(c, w, j, 1, fs);
-            PA_TRY(adj_stage(c, w, fs, COL_ADJ_A, op, n, 0, nullptr));
-            seg_fields(c, w, j, 0, fs);
-            PA_TRY(adj_stage(c, w, fs, COL_ADJ_N, impulse ? nullptr : op, n, n == 0 ? 1 : 0, scale));
-            PA_TRY(record_shells(c, w, sh, n_steps - n));
+            seg_fields(c, v, j, 3, fs);
+            PA_TRY(adj_stage(c, v, fs, COL_ADJ_C, op, n, 0, nullptr));
+            seg_fields(c, v, j, 2, fs);
+            PA_TRY(adj_stage(c, v, fs, COL_ADJ_B, op, n, 0, nullptr));
+            seg_fields(c, v, j, 1, fs);
+            PA_TRY(adj_stage(c, v, fs, COL_ADJ_A, op, n, 0, nullptr));
+            seg_fields(c, v, j, 0, fs);
+            PA_TRY(adj_stage(c, v, fs, COL_ADJ_N, impulse ? nullptr : op, n, n == 0 ? 1 : 0, scale));
+            PA_TRY(record_shells(c, v, sh, n_steps - n));
         }
         return PA_OK;
     };
+    // The adjoint steps of segment `seg` and what the next one needs first, pieces 0 .. n - 1 of
+    // work(i0, i1): beside each other, the launches of both enqueued in turn so that neither
+    // stream waits for the host, or one after the other.
+    auto reverse_with = [&](int seg, bool both_kept, int n, auto&& work) -> pa_status {
+        WS v = segment_view(c, w, nseg, K, seg, both_kept);
+        const int L = length(seg);
+        if (n == 0) return adjoint_steps(v, seg, 0, L);
+        if (!beside || !w.two || !overlaps(c)) {
+            PA_TRY(adjoint_steps(v, seg, 0, L));
+            return work(0, n);
+        }
+        Beside side(c);
+        PA_HIP(side.fork());
+        const int parts = small_grid(c->d.N) ? 1 : L;
+        for (int i = 0; i < parts; ++i) {
+            PA_TRY(side.run([&] { return work((int)((int64_t)n * i / parts), (int)((int64_t)n * (i + 1) / parts)); }));
+            PA_TRY(adjoint_steps(v, seg, L / parts * (parts - 1 - i), L / parts * (parts - i)));
+        }
+        PA_HIP(side.join());
+        return PA_OK;
+    };
+    // The workspace of recomputed segments: their products go to w.Yf (the adjoint's are in w.Yp),
+    // their state to the buffers that the adjoint does not use.
+    WS r = w;
+    for (int i = 0; i < 2; ++i) r.Yp[i] = w.Yf[i];
+    auto aim = [&](int seg, bool both_kept) { r.seg = segment_view(c, w, nseg, K, seg, both_kept).seg; };
+    // up to 64^2 a segment is one piece (run in few launches), else a step is
+    auto pieces = [&](int steps) { return small_grid(c->d.N) ? 1 : steps; };
+    auto per_piece = [&](int steps) { return small_grid(c->d.N) ? steps : 1; };
     if (!plan) {
-        for (int seg = nseg - 1; seg >= 0; --seg)
-            PA_TRY(reverse_segment(seg, ckpt_slot(c, ck, seg), !(seg == nseg - 1 && last_ready)));
+        const int kept = last_ready ? (w.two ? 2 : 1) : 0;   // segments whose fields the forward sweep left
+        auto recompute = [&](int seg, int i0, int i1) -> pa_status {
+            aim(seg, kept == 2);
+            if (i0 == 0) PA_TRY(recompute_start(r, seg, ckpt_slot(c, ck, seg)));
+            const int per = per_piece(length(seg));
+            return recompute_steps(r, seg, i0 * per, i1 * per);
+        };
+        if (kept == 0) PA_TRY(recompute(nseg - 1, 0, pieces(length(nseg - 1))));
+        for (int seg = nseg - 1; seg >= 0; --seg) {
+            const bool next = seg > 0 && nseg - seg >= kept;   // the next one is not kept
+            PA_TRY(reverse_with(seg, kept == 2, next ? pieces(length(seg - 1)) : 0,
+                                [&](int i0, int i1) { return i0 < i1 ? recompute(seg - 1, i0, i1) : PA_OK; }));
+        }
     } else {
         // the forward sweep ran the schedule up to its first REVERSE (segment nseg-1, stored)
-        size_t i = 0;
-        while (i < plan->size() && (*plan)[i].kind != ACT_REVERSE) ++i;
-        if (i == plan->size() || (*plan)[i].a != nseg - 1) return fail(PA_EINVAL, "internal: malformed checkpoint schedule");
-        PA_TRY(reverse_segment(nseg - 1, nullptr, false));
+        size_t at = 0;
+        while (at < plan->size() && (*plan)[at].kind != ACT_REVERSE) ++at;
+        if (at == plan->size() || (*plan)[at].a != nseg - 1) return fail(PA_EINVAL, "internal: malformed checkpoint schedule");
         std::vector<int> end_slot((size_t)nseg + 1, -1);
-        for (++i; i < plan->size(); ++i) {
-            const PlanAct& act_ = (*plan)[i];
-            const cd* src = act_.src >= 0 ? ckpt_slot(c, ck, act_.src) : w.omega;
-            if (act_.kind == ACT_REVERSE) {
-                PA_TRY(reverse_segment(act_.a, src, true));
-                continue;
-            }
-            if (small_grid(c->d.N)) {
-                if (act_.src >= 0)
-                    PA_HIP(launch_copy(reinterpret_cast<double*>(w.omega), reinterpret_cast<const double*>(src),
+        // Step m (up to 64^2: all steps) of an advance, the stage fields of whose state are in r.Yf
+        // (a live start has them there).
+        auto advance = [&](const PlanAct& x, int m, int steps) -> pa_status {
+            const int n0 = x.a * K;
+            if (m == 0 && x.src >= 0) {
+                const cd* src = ckpt_slot(c, ck, x.src);
+                if (small_grid(c->d.N)) {
+                    PA_HIP(launch_copy(reinterpret_cast<double*>(r.omega), reinterpret_cast<const double*>(src),
                                        2 * (size_t)B * per_c(c), c->stream));
-                if (act_.dst >= 0) end_slot[(size_t)act_.b] = act_.dst;
-                PA_TRY(small_run_steps(c, w, act_.a * K, std::min(n_steps, act_.b * K), n_steps, K, false, nullptr,
-                                       false, nullptr, CkptTarget{ck, &end_slot}, false));
-                end_slot[(size_t)act_.b] = -1;
-                continue;
+                } else {
+                    ColArgs a = col_base(c);
+                    a.state_in = src;
+                    a.omega = r.omega;
+                    set_stage_fields(a, r.Yf);
+                    PA_HIP(launch_col(c->d, COL_FROM_STATE, a, c->stream));
+                }
             }
-            // advance: the stage-a fields of the start state into w.Yf (a live start has them there)
-            cd* f0[2] = {w.Yf[0], w.Yf[1]};
-            if (act_.src >= 0) {
-                ColArgs a = col_base(c);
-                a.state_in = src;
-                a.omega = w.omega;
-                set_stage_fields(a, f0);
-                PA_HIP(launch_col(c->d, COL_FROM_STATE, a, c->stream));
+            end_slot[(size_t)x.b] = x.dst;
+            const CkptTarget t{ck, &end_slot};
+            const pa_status st =
+                small_grid(c->d.N) ? small_run_steps(c, r, n0, n0 + steps, n_steps, K, false, nullptr, false, nullptr, t, false)
+                                   : run_steps(c, r, n0 + m, n0 + m + 1, n_steps, K, false, nullptr, false, nullptr, t, true);
+            end_slot[(size_t)x.b] = -1;
+            return st;
+        };
+        for (; at < plan->size(); ) {
+            const int seg = (*plan)[at].a;   // its fields are in place
+            // the next REVERSE and the advances before it
+            size_t to = at + 1;
+            int n = 0;
+            auto steps_of = [&](const PlanAct& x) {
+                return x.kind == ACT_REVERSE ? length(x.a) : std::min(n_steps, x.b * K) - x.a * K;
+            };
+            for (; to < plan->size(); ++to) {
+                n += pieces(steps_of((*plan)[to]));
+                if ((*plan)[to].kind == ACT_REVERSE) break;
             }
-            if (act_.dst >= 0) end_slot[(size_t)act_.b] = act_.dst;
-            PA_TRY(run_steps(c, w, act_.a * K, std::min(n_steps, act_.b * K), n_steps, K, false, nullptr, false,
-                             nullptr, CkptTarget{ck, &end_slot}, true));
-            end_slot[(size_t)act_.b] = -1;
+            if (to == plan->size() && n > 0) return fail(PA_EINVAL, "internal: malformed checkpoint schedule");
+            if (n > 0) {
+                // an advance's fields: slot 1 of the half that the segment will fill
+                aim((*plan)[to].a, false);
+                if (!small_grid(c->d.N)) seg_fields(c, r, 0, 1, r.Yf);
+            }
+            PA_TRY(reverse_with(seg, false, n, [&](int i0, int i1) -> pa_status {
+                int i = 0;
+                for (size_t k = at + 1; k <= to && k < plan->size(); ++k) {
+                    const PlanAct& x = (*plan)[k];
+                    const int here = pieces(steps_of(x)), per = per_piece(steps_of(x));
+                    for (int m = std::max(i0 - i, 0); m < here && i + m < i1; ++m) {
+                        if (x.kind == ACT_ADVANCE) {
+                            PA_TRY(advance(x, m, steps_of(x)));
+                            continue;
+                        }
+                        if (m == 0) PA_TRY(recompute_start(r, x.a, x.src >= 0 ? ckpt_slot(c, ck, x.src) : r.omega));
+                        PA_TRY(recompute_steps(r, x.a, m * per, (m + 1) * per));
+                    }
+                    i += here;
+                }
+                return PA_OK;
+            }));
+            at = to;
         }
     }
     PA_TRY(finish_idle(act(0)));
@@ -1561,6 +1736,9 @@ pa_status pa_destroy(pa_ctx* c) try {
     if (!c) return PA_OK;
     (void)hipStreamSynchronize(c->stream);
     for (hipEvent_t e : c->prof_ev) (void)hipEventDestroy(e);
+    if (c->side) (void)hipStreamDestroy(c->side);
+    if (c->fork) (void)hipEventDestroy(c->fork);
+    if (c->join) (void)hipEventDestroy(c->join);
     if (c->pin) (void)hipHostFree(c->pin);
     (void)hipFree(c->tw);
     (void)hipFree(c->invk2);
@@ -1840,7 +2018,7 @@ pa_status pa_adjoint_gradient_noalloc(pa_ctx* c, const double* omega0, int32_t n
                            {obs ? obs->values : nullptr, "obs values"}}));
     ObsPlan op;
     PA_TRY(make_obs_plan(c, obs, n_steps, true, &op));
-    const size_t need = carve(c, n_steps, ckpt_every, op.max_times, 0, nullptr).total;
+    const size_t need = carve(c, n_steps, ckpt_every, op.max_times, 0, nullptr, false).total;
     if (need > PA_NOALLOC_SCRATCH_BYTES)
         return fail(PA_EINVAL, "this gradient needs " + std::to_string(need) +
                                    " bytes of scratch, more than the PA_NOALLOC_SCRATCH_BYTES the library holds "
@@ -1858,7 +2036,8 @@ pa_status pa_adjoint_gradient_noalloc(pa_ctx* c, const double* omega0, int32_t n
         if (op.n > 0) PA_HIP(launch_copy(J_out, w.J, c->d.B, c->stream));
         else PA_HIP(launch_fill(J_out, 0.0, c->d.B, c->stream));
     }
-    return backward_sweep(c, w, w.ckpt, n_steps, K, &op, 0, -1, -1, nullptr, grad_out, Shells(), true, nullptr);
+    return backward_sweep(c, w, w.ckpt, n_steps, K, &op, 0, -1, -1, nullptr, grad_out, Shells(), true, nullptr,
+                          false);   // (a second stream and its events are memory)
 } PA_CATCH_HOST
 
 pa_status pa_ensemble_acc_bytes(const pa_ctx* c, int32_t n_steps, int32_t n_shells, size_t* lambda_bytes,
