@@ -1150,6 +1150,8 @@ bool overlaps(pa_ctx* c) {
     hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
     if (c->stream && (hipStreamIsCapturing(c->stream, &cs) != hipSuccess || cs != hipStreamCaptureStatusNone)) return false;
     if (!c->side) {
+        int dev = -1;
+        if (hipGetDevice(&dev) != hipSuccess || dev != c->device) return false;
         if (!c->fork && hipEventCreateWithFlags(&c->fork, hipEventDisableTiming) != hipSuccess) return false;
         if (!c->join && hipEventCreateWithFlags(&c->join, hipEventDisableTiming) != hipSuccess) return false;
         if (hipStreamCreateWithFlags(&c->side, hipStreamNonBlocking) != hipSuccess) {
@@ -1736,7 +1738,10 @@ pa_status pa_destroy(pa_ctx* c) try {
     if (!c) return PA_OK;
     (void)hipStreamSynchronize(c->stream);
     for (hipEvent_t e : c->prof_ev) (void)hipEventDestroy(e);
-    if (c->side) (void)hipStreamDestroy(c->side);
+    if (c->side) {   // its work may precede another stream's than the current one
+        (void)hipStreamSynchronize(c->side);
+        (void)hipStreamDestroy(c->side);
+    }
     if (c->fork) (void)hipEventDestroy(c->fork);
     if (c->join) (void)hipEventDestroy(c->join);
     if (c->pin) (void)hipHostFree(c->pin);
