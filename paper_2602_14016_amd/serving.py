@@ -426,8 +426,8 @@ def tile_table(grids=GRIDS, device="cuda:0", batch=4):
     does not depend on its batch (the plan variants set the rounding).  It is tuned on a batch of
     `batch` members, the size the groups of a loaded server run at (tuned on one member, the
     1024^2 set took the one-wavefront adjoint-row plan and wide column blocks, 25-40 % slower per
-    launch at four to eight members); the column share count is left to each launch (0), which
-    gives one-member launches their shares."""
+    launch at four to eight members); the form of the column pass is left to each launch (0), which
+    gives small ones their twin teams."""
     from .autotune import autotune
     table = {}
     for N in grids:
