@@ -1581,11 +1581,16 @@ void host_twiddles(int N, std::vector<cd>& tw) {
 // columns 23.0, 22.5 -> 19.4, 18.5.  At 128 points the four-value column plan beats
 // the eight-value one below 64 members (eight members: 7.6 and 7.1 against 8.1 and
 // 7.7 us); from 256 points the eight-value plan does at every batch but one member
-// of 256^2 (8.4 against 8.6 us).
+// of 256^2 (8.4 against 8.6 us).  The 256-point rows of a wavefront share nothing,
+// so each is a workgroup of its own and waits for no other's: adjoint rows of one
+// member 5.3 -> 5.0 us against four per workgroup, of 64 30.0 -> 28.9, forward rows
+// 4.9 -> 4.8 and the same.  The other plans share a staged twiddle table: at four
+// rows 128^2 x 64 takes 12.7 and 13.0 us (15.6 and 18.1 at one), 512^2 x 2 8.1 and
+// 9.8 (9.0 and 10.5).
 void default_tiles(Dims& d) {
     const bool loop = small_grid(d.N);
     d.var = d.avar = loop ? 0 : 2;
-    d.tpb = d.atpb = 4;
+    d.tpb = d.atpb = d.N == 256 ? 1 : 4;
     d.cvar = loop ? 0 : d.N == 128 ? 2 : 1;
     d.csplit = 0;
     d.cb = 8;
