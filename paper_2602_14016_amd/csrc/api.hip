@@ -1144,9 +1144,16 @@ pa_status add_sobolev_gradient(pa_ctx* c, WS& w, const cd* ckpt, const ObsPlan* 
 // quarter of its own, one after the other -> beside: 64^2 one member 10.4 ->
 // 8.5 ms, 128^2 five 5.35 -> 4.20, 256^2 one 6.50 -> 5.68, three 7.33 -> 6.31,
 // sixteen 14.4 -> 12.3, sixty-four 10.4 -> 10.0, 1024^2 one 9.29 -> 7.93, three
-// 11.8 -> 10.7: never slower.  A captured graph stays one chain.
-bool overlaps(pa_ctx* c) {
+// 11.8 -> 10.7: never slower.  A fork and its join cost about 15 us, so where a step
+// is that short both sides need `steps` of two (128^2 and 64^2; 24 steps at 64^2 in
+// segments of one 1.93 ms either way, of two 1.71 -> 1.47), three (16^2 in segments of
+// two 0.69 against 0.75 ms, of three 0.63 -> 0.61, of six 0.57 -> 0.48) or five (8^2 in
+// segments of three 0.49 against 0.51, of six 0.43 -> 0.38).  A captured graph stays
+// one chain.
+bool overlaps(pa_ctx* c, int steps) {
     if (c->prof_class >= 0) return false;   // timed launches run alone
+    const int N = c->d.N;
+    if (steps < (N > 128 ? 1 : N >= 64 ? 2 : N >= 16 ? 3 : 5)) return false;
     hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
     if (c->stream && (hipStreamIsCapturing(c->stream, &cs) != hipSuccess || cs != hipStreamCaptureStatusNone)) return false;
     if (!c->side) {
@@ -1355,14 +1362,14 @@ pa_status backward_sweep(pa_ctx* c, WS& w, const cd* ckpt, int n_steps, int K, c
         }
         return PA_OK;
     };
-    // The adjoint steps of segment `seg` and what the next one needs first, pieces 0 .. n - 1 of
-    // work(i0, i1): beside each other, the launches of both enqueued in turn so that neither
+    // The adjoint steps of segment `seg` and what the next one needs first, `steps` steps as pieces
+    // 0 .. n - 1 of work(i0, i1): beside each other, the launches of both enqueued in turn so that neither
     // stream waits for the host, or one after the other.
-    auto reverse_with = [&](int seg, bool both_kept, int n, auto&& work) -> pa_status {
+    auto reverse_with = [&](int seg, bool both_kept, int steps, int n, auto&& work) -> pa_status {
         WS v = segment_view(c, w, nseg, K, seg, both_kept);
         const int L = length(seg);
         if (n == 0) return adjoint_steps(v, seg, 0, L);
-        if (!beside || !w.two || !overlaps(c)) {
+        if (!beside || !w.two || !overlaps(c, std::min(L, steps))) {
             PA_TRY(adjoint_steps(v, seg, 0, L));
             return work(0, n);
         }
@@ -1395,7 +1402,8 @@ pa_status backward_sweep(pa_ctx* c, WS& w, const cd* ckpt, int n_steps, int K, c
         if (kept == 0) PA_TRY(recompute(nseg - 1, 0, pieces(length(nseg - 1))));
         for (int seg = nseg - 1; seg >= 0; --seg) {
             const bool next = seg > 0 && nseg - seg >= kept;   // the next one is not kept
-            PA_TRY(reverse_with(seg, kept == 2, next ? pieces(length(seg - 1)) : 0,
+            const int steps = next ? length(seg - 1) : 0;
+            PA_TRY(reverse_with(seg, kept == 2, steps, next ? pieces(steps) : 0,
                                 [&](int i0, int i1) { return i0 < i1 ? recompute(seg - 1, i0, i1) : PA_OK; }));
         }
     } else {
@@ -1433,12 +1441,13 @@ pa_status backward_sweep(pa_ctx* c, WS& w, const cd* ckpt, int n_steps, int K, c
             const int seg = (*plan)[at].a;   // its fields are in place
             // the next REVERSE and the advances before it
             size_t to = at + 1;
-            int n = 0;
+            int n = 0, steps = 0;
             auto steps_of = [&](const PlanAct& x) {
                 return x.kind == ACT_REVERSE ? length(x.a) : std::min(n_steps, x.b * K) - x.a * K;
             };
             for (; to < plan->size(); ++to) {
                 n += pieces(steps_of((*plan)[to]));
+                steps += steps_of((*plan)[to]);
                 if ((*plan)[to].kind == ACT_REVERSE) break;
             }
             if (to == plan->size() && n > 0) return fail(PA_EINVAL, "internal: malformed checkpoint schedule");
@@ -1447,7 +1456,7 @@ pa_status backward_sweep(pa_ctx* c, WS& w, const cd* ckpt, int n_steps, int K, c
                 aim((*plan)[to].a, false);
                 if (!small_grid(c->d.N)) seg_fields(c, r, 0, 1, r.Yf);
             }
-            PA_TRY(reverse_with(seg, false, n, [&](int i0, int i1) -> pa_status {
+            PA_TRY(reverse_with(seg, false, steps, n, [&](int i0, int i1) -> pa_status {
                 int i = 0;
                 for (size_t k = at + 1; k <= to && k < plan->size(); ++k) {
                     const PlanAct& x = (*plan)[k];

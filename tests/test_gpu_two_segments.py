@@ -12,7 +12,7 @@ pytestmark = pytest.mark.gpu
 
 
 # two segments (both kept), three, and many; ragged last ones; one step per segment
-@pytest.mark.parametrize("N,B,H,K", [(8, 2, 9, 2), (32, 3, 13, 7), (64, 2, 21, 5), (64, 1, 5, 1), (128, 3, 11, 2),
+@pytest.mark.parametrize("N,B,H,K", [(8, 2, 9, 2), (8, 2, 17, 5), (16, 2, 10, 3), (32, 3, 13, 7), (64, 2, 21, 5), (64, 1, 5, 1), (128, 3, 11, 2),
                                      (128, 1, 12, 6), (256, 2, 9, 4), (512, 1, 7, 3), (1024, 1, 5, 2)])
 def test_same_bits_however_the_segments_run(N, B, H, K):
     from paper_2602_14016_amd import Observations, Solver
