@@ -1154,14 +1154,19 @@ bool overlaps(pa_ctx* c, int steps) {
     if (c->prof_class >= 0) return false;   // timed launches run alone
     const int N = c->d.N;
     if (steps < (N > 128 ? 1 : N >= 64 ? 2 : N >= 16 ? 3 : 5)) return false;
+    // a refused call leaves its error with the runtime, where the next launch would report it as its own
+    auto ok = [](hipError_t e) {
+        if (e != hipSuccess) (void)hipGetLastError();
+        return e == hipSuccess;
+    };
     hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
-    if (c->stream && (hipStreamIsCapturing(c->stream, &cs) != hipSuccess || cs != hipStreamCaptureStatusNone)) return false;
+    if (c->stream && (!ok(hipStreamIsCapturing(c->stream, &cs)) || cs != hipStreamCaptureStatusNone)) return false;
     if (!c->side) {
         int dev = -1;
-        if (hipGetDevice(&dev) != hipSuccess || dev != c->device) return false;
-        if (!c->fork && hipEventCreateWithFlags(&c->fork, hipEventDisableTiming) != hipSuccess) return false;
-        if (!c->join && hipEventCreateWithFlags(&c->join, hipEventDisableTiming) != hipSuccess) return false;
-        if (hipStreamCreateWithFlags(&c->side, hipStreamNonBlocking) != hipSuccess) {
+        if (!ok(hipGetDevice(&dev)) || dev != c->device) return false;
+        if (!c->fork && !ok(hipEventCreateWithFlags(&c->fork, hipEventDisableTiming))) return false;
+        if (!c->join && !ok(hipEventCreateWithFlags(&c->join, hipEventDisableTiming))) return false;
+        if (!ok(hipStreamCreateWithFlags(&c->side, hipStreamNonBlocking))) {
             c->side = nullptr;
             return false;
         }
