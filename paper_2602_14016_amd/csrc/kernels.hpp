@@ -37,6 +37,7 @@ struct Dims {
     int cb_auto;     // column pass: the block is chosen per launch (col_block_auto), not by cb
     int csplit;      // column pass: a pair's signals on one team (1) or twin teams (2, 4); 0: chosen per launch
     int cus;         // compute units of the device (persistent grids)
+    int device;      // the context's device
     int lds_max;     // bytes of LDS a workgroup may use on the device (column blocks beyond 64 KiB)
 };
 

@@ -17,6 +17,7 @@
 
 #include <hip/hip_ext.h>
 
+#include "device_once.hpp"
 #include "kernels.hpp"
 
 namespace pa {
@@ -1123,13 +1124,18 @@ int row_tpb(const Dims& d, int tpb, long teams_per_member) {
 }
 
 // A kernel whose workgroups take more than 64 KiB of LDS: its dynamic limit is
-// raised to the device's once per instantiation.
+// raised to the device's once per instantiation and device.  (The 1024-point
+// rows take 80 KiB by default, wide column blocks up to 144.)
 template <auto Kernel>
 hipError_t raise_lds(const Dims& d, size_t lds) {
     if (lds <= 65536) return hipSuccess;
-    static const hipError_t raised =
-        hipFuncSetAttribute(reinterpret_cast<const void*>(Kernel), hipFuncAttributeMaxDynamicSharedMemorySize, d.lds_max);
-    return raised;
+    static DeviceOnce raised;
+    return raised(d.device, [&] {
+        const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(Kernel),
+                                                 hipFuncAttributeMaxDynamicSharedMemorySize, d.lds_max);
+        if (e != hipSuccess) (void)hipGetLastError();   // returned here, not by the next launch too
+        return e;
+    });
 }
 
 template <int N, int V, auto Kernel, class... Args>
