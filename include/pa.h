@@ -496,6 +496,10 @@ pa_status pa_get_tiles(const pa_ctx* ctx, pa_tiles* tiles);
  * context stream (the stream the kernel runs on).  kernel_class 0: row pass
  * of the right-hand side; 1: column pass of the forward RK4 stages; 2: row
  * pass of the adjoint products; 3: column pass of the adjoint stages.
+ * Grids up to 64^2 launch no kernel of these classes (their time loop is one
+ * kernel): both counts stay 0.  Until it is stopped the timer keeps every launch
+ * on the context stream, so segments are recomputed in line and not beside the
+ * adjoint (the results are the same).
  * pa_profile_stop synchronises the stream and returns the number of timed
  * launches, the number of launches of that class seen, and the summed event
  * time in milliseconds. */
