@@ -1696,7 +1696,7 @@ pa_status pa_create(const pa_physics* phys, int32_t N, int32_t B, void* hip_stre
     if (hipDeviceGetAttribute(&d.lds_max, hipDeviceAttributeMaxSharedMemoryPerBlock, dev) != hipSuccess ||
         d.lds_max < 65536)
         d.lds_max = 65536;
-    d.device = dev;
+    d.device = (short)dev;
     default_tiles(d);
 
     std::vector<cd> tw;

@@ -34,12 +34,14 @@ struct Dims {
     int var, tpb;    // forward row passes: FFT plan variant (0..3; 3 = pipelined), rows (waves) per workgroup
     int avar, atpb;  // adjoint row passes: FFT plan variant (0..3), rows (waves) per workgroup
     int cvar, cb;    // column pass: FFT plan variant, kx columns per workgroup
-    int cb_auto;     // column pass: the block is chosen per launch (col_block_auto), not by cb
+    short cb_auto;   // column pass: the block is chosen per launch (col_block_auto), not by cb
+    short device;    // the context's device
     int csplit;      // column pass: a pair's signals on one team (1) or twin teams (2, 4); 0: chosen per launch
     int cus;         // compute units of the device (persistent grids)
-    int device;      // the context's device
     int lds_max;     // bytes of LDS a workgroup may use on the device (column blocks beyond 64 KiB)
 };
+
+static_assert(sizeof(Dims) == 64, "a kernel argument: what follows it stays 64-byte aligned");
 
 // Column-pass outputs: the field itself, or one half of a packed pair
 // (P = A + i B, Q = A - i B) with (A, B) = (u, v) or the adjoint's (b, a).

@@ -48,7 +48,7 @@ int main() {
     const struct { int device; bool refuse; } runs[] = {{0, true}, {0, false}, {0, false}, {1, true}, {1, false},
                                                         {1, false}, {0, false}, {70, false}, {70, false}};
     for (const auto& r : runs) {
-        d.device = r.device;
+        d.device = (short)r.device;
         refuse = r.refuse;
         const hipError_t e = pa::launch_row_sq(d, a, nullptr);
         std::printf("%%d %%d %%d\n", (int)e, asked, (int)hipGetLastError());
