@@ -1149,6 +1149,25 @@ hipError_t row_launch(const Dims& d, int teams, long per_member, unsigned more, 
     return hipGetLastError();
 }
 
+// The plans that differ among variants 0, 1 and 2 of a length are the first
+// plans<N>() of them.
+template <int N>
+__host__ __device__ constexpr int plans() { return N <= 32 || N == 512 ? 1 : N == 64 || N == 1024 ? 2 : 3; }
+template <int N>
+constexpr int plan_of(int variant) { return std::min(variant, plans<N>() - 1); }
+template <int N, int A, int B>
+constexpr bool same_plan() {
+    using P = Plan<N, A>;
+    using Q = Plan<N, B>;
+    return P::NS == Q::NS && P::T == Q::T && P::E == Q::E && P::R[0] == Q::R[0] && P::R[1] == Q::R[1] &&
+           P::R[2] == Q::R[2] && P::R[3] == Q::R[3];
+}
+
+// The grids whose time loop runs in one kernel (small.hpp) launch only the
+// transforms of fields and the columns between them.
+template <int N>
+constexpr bool loop_grid() { return N <= 64; }
+
 // VAR / TPB: the plan variant and rows per workgroup of the launching pass
 // (forward rows: d.var, d.tpb; adjoint rows: d.avar, d.atpb).  Variant 3
 // (pipelined) runs the plan of variant 2 in the kernels it does not cover.
@@ -1158,14 +1177,20 @@ hipError_t row_launch(const Dims& d, int teams, long per_member, unsigned more, 
 // launch, best Stockham tiles -> plan 3: one member 14.0 -> 11.9 us (forward
 // rows) and 17.4 -> 14.6 (adjoint rows), four 30.8 -> 25.8 and 43.2 -> 37.7,
 // eight 53.1 -> 43.9 and 74.6 -> 61.2 (4.1 and 4.4 TB/s).
+// Where the variants of a length are one plan (8 to 32 and 512 points; 1 and 2 at
+// 64), one of them is instantiated.
 // (MORE: workgroups ahead of the rows').
 #define PA_ROW_LAUNCH(VAR, TPB, KERNEL, TEAMS_PER_MEMBER, MORE, ...)                                          \
     do {                                                                                                      \
         const long tpm_ = (TEAMS_PER_MEMBER);                                                                 \
+        const int v_ = plan_of<N>(VAR);                                                                       \
         if constexpr (N == 1024) return row_launch<N, 3, KERNEL(3)>(d, 4, tpm_, (MORE), s, __VA_ARGS__);      \
-        else if ((VAR) == 0) return row_launch<N, 0, KERNEL(0)>(d, (TPB), tpm_, (MORE), s, __VA_ARGS__);      \
-        else if ((VAR) == 1) return row_launch<N, 1, KERNEL(1)>(d, (TPB), tpm_, (MORE), s, __VA_ARGS__);      \
-        else return row_launch<N, 2, KERNEL(2)>(d, (TPB), tpm_, (MORE), s, __VA_ARGS__);                      \
+        else if (v_ == 0) return row_launch<N, 0, KERNEL(0)>(d, (TPB), tpm_, (MORE), s, __VA_ARGS__);         \
+        else if constexpr (plans<N>() > 1) {                                                                  \
+            if (v_ == 1) return row_launch<N, 1, KERNEL(1)>(d, (TPB), tpm_, (MORE), s, __VA_ARGS__);          \
+            else if constexpr (plans<N>() > 2) return row_launch<N, 2, KERNEL(2)>(d, (TPB), tpm_, (MORE), s, __VA_ARGS__); \
+        }                                                                                                     \
+        return hipErrorInvalidValue;                                                                          \
     } while (0)
 
 #define PA_K_R2C(V) &row_r2c_kernel<N, V>
@@ -1188,25 +1213,35 @@ hipError_t Launch<N>::row_c2r(const Dims& d, const cd* in, double* out, const cd
 }
 template <int N>
 hipError_t Launch<N>::row_sq(const Dims& d, const RowArgs& a, hipStream_t s) {
-    if constexpr (Pipe<N>::OK)
-        if (d.var == 3) return pipe_launch<N, 2>(row_sq_pipe_kernel<N>, d.tpb, d, a, s);
-    PA_ROW_LAUNCH(d.var, d.tpb, PA_K_SQ, N, 0u, a);
+    if constexpr (loop_grid<N>()) return hipErrorInvalidValue;
+    else {
+        if constexpr (Pipe<N>::OK)
+            if (d.var == 3) return pipe_launch<N, 2>(row_sq_pipe_kernel<N>, d.tpb, d, a, s);
+        PA_ROW_LAUNCH(d.var, d.tpb, PA_K_SQ, N, 0u, a);
+    }
 }
 template <int N>
 hipError_t Launch<N>::row_obs(const Dims& d, const RowArgs& a, hipStream_t s) {
-    PA_ROW_LAUNCH(d.var, d.tpb, PA_K_OBS, a.obs.M, 0u, a);
+    if constexpr (loop_grid<N>()) return hipErrorInvalidValue;
+    else PA_ROW_LAUNCH(d.var, d.tpb, PA_K_OBS, a.obs.M, 0u, a);
 }
 template <int N>
 hipError_t Launch<N>::row_mul(const Dims& d, const RowArgs& a, hipStream_t s) {
-    if constexpr (Pipe<N>::OK)
-        if (d.avar == 3) return pipe_launch<N, 4>(row_mul_pipe_kernel<N>, d.atpb, d, a, s);
-    PA_ROW_LAUNCH(d.avar, d.atpb, PA_K_MUL, N, 0u, a);
+    if constexpr (loop_grid<N>()) return hipErrorInvalidValue;
+    else {
+        if constexpr (Pipe<N>::OK)
+            if (d.avar == 3) return pipe_launch<N, 4>(row_mul_pipe_kernel<N>, d.atpb, d, a, s);
+        PA_ROW_LAUNCH(d.avar, d.atpb, PA_K_MUL, N, 0u, a);
+    }
 }
 template <int N>
 hipError_t Launch<N>::row_src(const Dims& d, const RowArgs& a, int mode, hipStream_t s) {
-    if (mode == SRC_ADD) PA_ROW_LAUNCH(d.avar, d.atpb, PA_K_SRC_ADD, a.obs.M, 0u, a);
-    if (mode == SRC_IMPULSE) PA_ROW_LAUNCH(d.avar, d.atpb, PA_K_SRC_IMPULSE, N, 0u, a);
-    PA_ROW_LAUNCH(d.avar, d.atpb, PA_K_SRC_WRITE, N, 0u, a);
+    if constexpr (loop_grid<N>()) return hipErrorInvalidValue;
+    else {
+        if (mode == SRC_ADD) PA_ROW_LAUNCH(d.avar, d.atpb, PA_K_SRC_ADD, a.obs.M, 0u, a);
+        if (mode == SRC_IMPULSE) PA_ROW_LAUNCH(d.avar, d.atpb, PA_K_SRC_IMPULSE, N, 0u, a);
+        PA_ROW_LAUNCH(d.avar, d.atpb, PA_K_SRC_WRITE, N, 0u, a);
+    }
 }
 
 template <auto Kernel>
@@ -1241,27 +1276,35 @@ template <int N, int V>
 hipError_t col_variant(const Dims& d, int mode, const ColArgs& a, hipStream_t s) {
     switch (mode) {
         case COL_INIT: return col_mode<N, V, COL_INIT>(d, a, s);
-        case COL_A: return col_mode<N, V, COL_A>(d, a, s);
-        case COL_B: return col_mode<N, V, COL_B>(d, a, s);
-        case COL_C: return col_mode<N, V, COL_C>(d, a, s);
-        case COL_D: return col_mode<N, V, COL_D>(d, a, s);
         case COL_FILTER: return col_mode<N, V, COL_FILTER>(d, a, s);
         case COL_FROM_STATE: return col_mode<N, V, COL_FROM_STATE>(d, a, s);
-        case COL_ADJ_C: return col_mode<N, V, COL_ADJ_C>(d, a, s);
-        case COL_ADJ_B: return col_mode<N, V, COL_ADJ_B>(d, a, s);
-        case COL_ADJ_A: return col_mode<N, V, COL_ADJ_A>(d, a, s);
-        case COL_ADJ_N: return col_mode<N, V, COL_ADJ_N>(d, a, s);
-        case COL_ADJ_SRC: return col_mode<N, V, COL_ADJ_SRC>(d, a, s);
         case COL_FIRST_GUESS: return col_mode<N, V, COL_FIRST_GUESS>(d, a, s);
-        default: return hipErrorInvalidValue;
     }
+    if constexpr (!loop_grid<N>()) {
+        switch (mode) {
+            case COL_A: return col_mode<N, V, COL_A>(d, a, s);
+            case COL_B: return col_mode<N, V, COL_B>(d, a, s);
+            case COL_C: return col_mode<N, V, COL_C>(d, a, s);
+            case COL_D: return col_mode<N, V, COL_D>(d, a, s);
+            case COL_ADJ_C: return col_mode<N, V, COL_ADJ_C>(d, a, s);
+            case COL_ADJ_B: return col_mode<N, V, COL_ADJ_B>(d, a, s);
+            case COL_ADJ_A: return col_mode<N, V, COL_ADJ_A>(d, a, s);
+            case COL_ADJ_N: return col_mode<N, V, COL_ADJ_N>(d, a, s);
+            case COL_ADJ_SRC: return col_mode<N, V, COL_ADJ_SRC>(d, a, s);
+        }
+    }
+    return hipErrorInvalidValue;
 }
 
 template <int N>
 hipError_t Launch<N>::col(const Dims& d, int mode, const ColArgs& a, hipStream_t s) {
-    if (d.cvar == 0) return col_variant<N, 0>(d, mode, a, s);
-    if (d.cvar == 1) return col_variant<N, 1>(d, mode, a, s);
-    return col_variant<N, 2>(d, mode, a, s);
+    static_assert((plans<N>() > 1 || same_plan<N, 0, 1>()) && (plans<N>() > 2 || same_plan<N, 1, 2>()));
+    const int v = plan_of<N>(d.cvar);
+    if (v == 0) return col_variant<N, 0>(d, mode, a, s);
+    if constexpr (plans<N>() > 1)
+        if (v == 1) return col_variant<N, 1>(d, mode, a, s);
+    if constexpr (plans<N>() > 2) return col_variant<N, 2>(d, mode, a, s);
+    return hipErrorInvalidValue;
 }
 
 template <int N>
