@@ -38,7 +38,7 @@ def kernel_rw_bytes(name, N):
         return 4 * Yb, Yb
     if name.startswith("row_adj"):
         return 6 * Yb, 2 * Yb
-    m = re.match(r"col_pass_kernel<\d+, \d+, (\d+)>", name)
+    m = re.match(r"col_(?:pass|twin)_kernel<\d+, \d+, (\d+)>", name)
     if m:
         comp = {1: (1, 1), 2: (2, 1), 3: (2, 1), 4: (2, 1), 7: (1, 1), 8: (2, 1), 9: (2, 1), 10: (1, 1)}
         mode = comp.get(int(m.group(1)))
