@@ -33,8 +33,11 @@
  *     with PA_EINVAL (pa_is_device_memory).
  *   - "device" pointers are HIP device memory owned by the caller (e.g. torch
  *     tensors); "host" pointers are ordinary host memory.  The library owns only
- *     the opaque context (plans and small constant tables it allocates in
- *     pa_create and frees in pa_destroy).
+ *     the opaque context: plans and small constant tables it allocates in
+ *     pa_create, and what a first call that needs it adds (a second stream with
+ *     two events, the launch timer's events, the optimiser's pinned host staging),
+ *     all freed in pa_destroy; and per device the scratch of the allocation-free
+ *     calls (PA_NOALLOC_SCRATCH_BYTES).
  *   - Work is enqueued asynchronously on the context's HIP stream (set at
  *     creation or with pa_set_stream).  Functions that return host values
  *     synchronise that stream; the others do not.
@@ -404,12 +407,14 @@ pa_status pa_shell_growth(pa_ctx* ctx, const double* shells, int32_t rows, int32
  * from its members; col_split: 1 =
  * one team of threads runs both signals of a column's packed pair, 2 or 4 =
  * twin teams run one each (with fewer columns per workgroup where col_block
- * of them would not fit), 0 = chosen per launch (twins where the launch has
- * fewer than two wavefronts per SIMD without).  Results do not depend on the choice
+ * of them would not fit), 0 = chosen per launch (twins where one team per column
+ * gives the launch fewer than ten wavefronts per CU, from 512 points fewer than
+ * eight).  Results do not depend on the choice
  * beyond rounding of the transforms, and not at all on col_block and col_split.
  * The defaults depend on the grid, and the block on the batch.  Grids up to 64^2
- * run their time loop in one kernel without these passes; the right-hand side and
- * adjoint products of 512 and 1024 points have one plan whatever the variant. */
+ * run their time loop in one kernel without these passes; the row passes of 512
+ * and 1024 points have one plan whatever the variant, those of 1024 four rows per
+ * workgroup whatever the teams. */
 typedef struct pa_tiles {
     int32_t row_variant, row_teams;
     int32_t adj_variant, adj_teams;

@@ -1,8 +1,10 @@
 // api.hip -- host side of the C ABI declared in include/pa.h.
 //
-// The context owns only constant tables (twiddles, 1/|k|^2, integrating
-// factors, shell lists).  Every buffer a solve needs is carved from the
-// caller's workspace by one layout routine that also answers the size query.
+// The context owns constant tables (twiddles, 1/|k|^2, integrating factors,
+// shell lists) and, from the first call that needs them, a second stream with
+// two events, the launch timer's events and pinned host staging.  Every device
+// buffer a solve needs is carved from the caller's workspace by one layout
+// routine that also answers the size query.
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
@@ -787,8 +789,7 @@ pa_status run_steps(pa_ctx* c, WS& w, int n0, int n1, int n_total, int K, bool s
                     if (slot >= 0) a.ckpt = ckpt_slot(c, ckpt.base, slot);
                 }
                 if (nn == n1 && !final_fields) a.nout = 0;
-                // the new state goes to the other buffer, so that no workgroup of the launch
-                // overwrites a state another one still reads
+                // a launch reads the state from one buffer and writes it to the other
                 a.omega_out = w.omega2;
             }
             PA_HIP(timed(c, PROF_COL_FWD, [&] { return launch_col(dn, COL_A + s, a, c->stream); }));
@@ -1148,8 +1149,9 @@ pa_status add_sobolev_gradient(pa_ctx* c, WS& w, const cd* ckpt, const ObsPlan* 
 // is that short both sides need `steps` of two (128^2 and 64^2; 24 steps at 64^2 in
 // segments of one 1.93 ms either way, of two 1.71 -> 1.47), three (16^2 in segments of
 // two 0.69 against 0.75 ms, of three 0.63 -> 0.61, of six 0.57 -> 0.48) or five (8^2 in
-// segments of three 0.49 against 0.51, of six 0.43 -> 0.38).  A captured graph stays
-// one chain.
+// segments of three 0.49 against 0.51, of six 0.43 -> 0.38).  A call under capture is
+// recorded as one chain, as before there was a second stream: a forked graph was not
+// measured.
 bool overlaps(pa_ctx* c, int steps) {
     if (c->prof_class >= 0) return false;   // timed launches run alone
     const int N = c->d.N;

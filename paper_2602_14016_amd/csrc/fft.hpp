@@ -579,7 +579,7 @@ __device__ __forceinline__ void fft256_wave(cd* v, int t, cd* lds, const Tw256& 
 // slot's low four bits XOR t_lo, doubled at 512).  The Stockham plans of these
 // lengths exchange two or three times per transform, at 1024 points across two
 // wavefronts: 275 KB of LDS traffic per 1024-point row of a forward launch,
-// 94 KB here (times: row_plan3_launch; eight 512^2 members 15.6 -> 14.7 us per
+// 94 KB here (its times: PA_ROW_LAUNCH; eight 512^2 members 15.6 -> 14.7 us per
 // forward row launch and 21.4 -> 19.4 per adjoint one, sixteen 32.5 -> 30.2).
 // tw: the table of stage_wave in LDS.
 template <int N>
