@@ -94,6 +94,7 @@ def traffic(args):
             f"calib_copy_bytes: {calib}", f"calib_fetch_kib: {cf:.2f}", f"calib_write_kib: {cw:.2f}",
             f"scale_fetch: {sf:.4f}", f"scale_write: {sw:.4f}", "#",
             f"# {'kernel':34s} {'read_MB':>9s} {'alg_read_MB':>12s} {'write_MB':>9s} {'alg_write_MB':>13s}"]
+    same = []   # the dominant kernel's other plans, where the runs hold them (bench.py reports what it ran)
     for k in sorted(set(fetch) & set(write)):
         rw = kernel_rw_bytes(k, args.N)
         if rw is None:
@@ -102,6 +103,8 @@ def traffic(args):
         wr = sw * 1024 * sum(write[k]) / len(write[k]) / 1e6
         out.append(f"# {k[:34]:34s} {rd:9.2f} {rw[0] * args.members / 1e6:12.2f} {wr:9.2f} "
                    f"{rw[1] * args.members / 1e6:13.2f}")
+        if k != args.kernel and k.startswith(args.kernel.split("_kernel")[0].replace("_pipe", "")):
+            same.append(f"launch: {k} {int(round(1e6 * (rd + wr)))}")
     if args.kernel not in fetch or args.kernel not in write:
         raise SystemExit(f"kernel {args.kernel!r} not in the counter runs: {sorted(fetch)}")
     fk = sum(fetch[args.kernel]) / len(fetch[args.kernel])
@@ -109,7 +112,7 @@ def traffic(args):
     out += ["#", "# dominant kernel used by bench.py's roofline 'traffic':", f"class: {args.cls}", f"N: {args.N}",
             f"members: {args.members}", f"kernel: {args.kernel}", f"fetch_kib_per_launch: {fk:.2f}",
             f"write_kib_per_launch: {wk:.2f}", f"hbm_bytes_per_launch: {int(round(1024 * (sf * fk + sw * wk)))}",
-            f"source_sha: {kernel_source_sha()}"]
+            *same, f"source_sha: {kernel_source_sha()}"]
     return "\n".join(out) + "\n"
 
 

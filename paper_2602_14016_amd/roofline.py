@@ -76,14 +76,18 @@ TRAFFIC_PATH = os.path.join(ROOT, "profiles", "traffic_counters.txt")
 def read_traffic(cls, N, members, kernel=None, path=TRAFFIC_PATH):
     """HBM bytes per launch of class cls from the committed counter record, or
     None if the record is missing or was taken on other sources, another
-    class, shape or (if given) another kernel instantiation."""
+    class or shape, or (if given) holds no such kernel instantiation: the record's
+    own, or one that its launch lines name."""
     if not os.path.exists(path):
         return None
-    kv = {}
+    kv, launches = {}, {}
     with open(path) as fh:
         for line in fh:
             if ":" in line and not line.startswith("#"):
                 k, v = line.split(":", 1)
+                if k == "launch":
+                    name, _, value = v.strip().rpartition(" ")
+                    launches[name] = value
                 kv[k.strip()] = v.strip()
     if kv.get("source_sha") != kernel_source_sha():
         return None
@@ -91,7 +95,7 @@ def read_traffic(cls, N, members, kernel=None, path=TRAFFIC_PATH):
         if int(kv.get("class", -1)) != cls or int(kv.get("N", -1)) != N or int(kv.get("members", -1)) != members:
             return None
         if kernel is not None and kv.get("kernel") != kernel:
-            return None
+            return float(launches[kernel])
         return float(kv["hbm_bytes_per_launch"])
     except (KeyError, ValueError):
         return None
