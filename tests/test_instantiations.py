@@ -21,7 +21,8 @@ def test_kernels_of_each_grid():
     plans = lambda n, kernel: {k[1] for k in found[n] if k[0] == kernel}
     assert set(found) == {8, 16, 32, 64, 128, 256, 512, 1024}
     for N in (8, 16, 32, 64):
-        assert {k[0] for k in found[N]} == {"row_r2c_kernel", "row_c2r_kernel", "col_pass_kernel", "col_twin_kernel",
+        held = {("row_sq_pipe_kernel",), ("row_mul_pipe_kernel",)} if N == 64 else set()   # for test_lds_dma_codegen.py
+        assert {k[0] for k in found[N] - held} == {"row_r2c_kernel", "row_c2r_kernel", "col_pass_kernel", "col_twin_kernel",
                                             "small_forward_kernel", "small_adjoint_kernel", "small_filter_kernel"}, N
         assert columns(N) <= {0, 5, 6, 12}, N   # init, filter, from a state, first guess
     for N in (128, 256, 512, 1024):
